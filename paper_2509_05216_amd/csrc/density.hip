@@ -16,10 +16,13 @@
 //  scan   one block turns the block totals into exclusive block offsets and
 //         the grand totals (read back by the host to size the output);
 //  apply  classify again, rank each Gaussian inside its block in index order
-//         (ballot prefix counts), and write every output: originals and clones
-//         copy their 11 + 3(d+1)^2 parameter rows (and, for originals, both
-//         Adam moments); children get drawn means and reduced log-scales; the
-//         moments of new Gaussians are zero.
+//         (ballot prefix counts), list the block's outputs in LDS and write them
+//         row by row: originals and clones copy their 11 + 3(d+1)^2 parameter
+//         rows (and, for originals, both Adam moments); children get drawn means
+//         and reduced log-scales; the moments of new Gaussians are zero.
+#include <algorithm>
+#include <cmath>
+
 #include "internal.h"
 
 namespace isogs {
@@ -168,23 +171,38 @@ __device__ inline void box_muller64(uint32_t a, uint32_t b, double& z0, double& 
 }
 
 struct ApplyArgs {
-  gs_params p, m, v;           // inputs (n entries)
-  gs_params po, mo, vo;        // outputs (n_out entries)
+  gs_params in[3];             // parameters, first and second moments (n entries)
+  gs_params out[3];            // the same of the densified set (n_out entries)
   int32_t* src;                // optional source index per output
   const uint4* off;            // block offsets; off[nb] = totals
   int nb, rows, n_split;
   uint32_t k0, k1;             // Philox key
 };
 
-__global__ __launch_bounds__(kDB) void k_density_apply(DensityCfg c, ApplyArgs a) {
+constexpr int kRowsAhead = 4;  // rows whose loads a thread issues before its first store
+constexpr int kOut = 5;        // outputs per thread and run: 1280, a block's in one run as a rule
+
+// Bound by memory: every row of the parameters and both moments is read and written
+// once (24 B per parameter).  A block classifies its 1024 Gaussians again (cheap: five
+// values each), lists its kept originals, clones and split parents in LDS, and then
+// moves whole rows of all its outputs together: consecutive threads take consecutive
+// outputs, whose sources ascend, so both sides are coalesced, and a thread keeps its
+// outputs over all rows with kOut x kRowsAhead loads in flight.  blockIdx.y picks the set
+// (parameters, first, second moment) and one of `rsplit` runs of its rows, so that small
+// sets still fill the chip.  (One thread per Gaussian walking all 3 x 59 rows, a row's
+// load waiting for the row before it, took 1528 us for 1M Gaussians at degree 3; the
+// three lists moved one after the other 490 us.)
+__global__ __launch_bounds__(kDB) void k_density_apply(DensityCfg c, ApplyArgs a, int rsplit) {
   __shared__ uint32_t sh[kDW][3];
+  __shared__ uint16_t list[3][kDG];  // offsets in the block: kept, clones, split parents
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   const uint4 tot = a.off[a.nb];
   const uint4 bo = a.off[blockIdx.x];
-  uint32_t base0 = bo.x, base1 = bo.y, base2 = bo.z;
+  uint32_t n0 = 0, n1 = 0, n2 = 0;  // entries of the three lists so far
   for (int k = 0; k < kDI; ++k) {
-    const long long i = (long long)blockIdx.x * kDG + k * kDB + threadIdx.x;
+    const uint32_t li = k * kDB + threadIdx.x;
+    const long long i = (long long)blockIdx.x * kDG + li;
     const uint32_t f = i < c.n ? classify(c, i) : 0u;
     const unsigned long long b0 = __ballot((f & kKeep) != 0);
     const unsigned long long b1 = __ballot((f & kClone) != 0);
@@ -195,80 +213,108 @@ __global__ __launch_bounds__(kDB) void k_density_apply(DensityCfg c, ApplyArgs a
       sh[w][2] = popc(b2);
     }
     __syncthreads();
-    uint32_t p0 = 0, p1 = 0, p2 = 0, t0 = 0, t1 = 0, t2 = 0;
+    uint32_t p0 = n0, p1 = n1, p2 = n2;
     for (int q = 0; q < kDW; ++q) {
       if (q < w) {
         p0 += sh[q][0];
         p1 += sh[q][1];
         p2 += sh[q][2];
       }
-      t0 += sh[q][0];
-      t1 += sh[q][1];
-      t2 += sh[q][2];
+      n0 += sh[q][0];
+      n1 += sh[q][1];
+      n2 += sh[q][2];
     }
     __syncthreads();
-    if (f != 0) {
-      const size_t n = (size_t)c.n;
-      if (f & kKeep) {
-        const size_t o = base0 + p0 + popc(b0 & below);
-        for (int r = 0; r < a.rows; ++r) {
-          prow(a.po, r)[o] = prow(a.p, r)[i];
-          prow(a.mo, r)[o] = prow(a.m, r)[i];
-          prow(a.vo, r)[o] = prow(a.v, r)[i];
-        }
-        if (a.src) a.src[o] = (int32_t)i;
+    if (f & kKeep) list[0][p0 + popc(b0 & below)] = (uint16_t)li;
+    if (f & kClone) list[1][p1 + popc(b1 & below)] = (uint16_t)li;
+    if (f & kChild) list[2][p2 + popc(b2 & below)] = (uint16_t)li;
+  }
+  __syncthreads();
+  const int set = (int)blockIdx.y / rsplit, part = (int)blockIdx.y % rsplit;
+  const gs_params &in = a.in[set], &out = a.out[set];
+  const bool zero = set != 0;  // new Gaussians' moments
+  const int r0 = a.rows * part / rsplit, r1 = a.rows * (part + 1) / rsplit;
+  const uint32_t base = blockIdx.x * (uint32_t)kDG;
+  const uint32_t ns = (uint32_t)a.n_split;
+  const size_t oKeep = bo.x, oClone = (size_t)tot.x + bo.y;
+  const size_t oChild = (size_t)tot.x + tot.y + (size_t)ns * bo.z;
+  const uint32_t cnt = n0 + n1 + n2 * ns;
+  for (uint32_t j0 = 0; j0 < cnt; j0 += kOut * kDB) {
+    uint32_t src[kOut];
+    size_t dst[kOut];
+    bool ok[kOut], zer[kOut], own6[kOut];  // own6: rows 0 .. 5 come from elsewhere (children)
+#pragma unroll
+    for (int k = 0; k < kOut; ++k) {
+      const uint32_t j = j0 + k * kDB + threadIdx.x;
+      ok[k] = j < cnt;
+      zer[k] = zero && j >= n0;
+      own6[k] = !zero && j >= n0 + n1;
+      uint32_t l = 0;  // threads without an output load the block's first Gaussian
+      if (j < n0) {
+        l = list[0][j];
+        dst[k] = oKeep + j;
+      } else if (j < n0 + n1) {
+        l = list[1][j - n0];
+        dst[k] = oClone + (j - n0);
+      } else {
+        const uint32_t c2 = j - n0 - n1;
+        if (ok[k]) l = list[2][c2 / ns];
+        dst[k] = oChild + c2;
       }
-      if (f & kClone) {
-        const size_t o = (size_t)tot.x + base1 + p1 + popc(b1 & below);
-        for (int r = 0; r < a.rows; ++r) {
-          prow(a.po, r)[o] = prow(a.p, r)[i];
-          prow(a.mo, r)[o] = 0.f;
-          prow(a.vo, r)[o] = 0.f;
-        }
-        if (a.src) a.src[o] = (int32_t)i;
+      src[k] = base + l;
+    }
+    for (int r = r0; r < r1; r += kRowsAhead) {
+      float val[kRowsAhead][kOut];
+#pragma unroll
+      for (int u = 0; u < kRowsAhead; ++u) {
+        const float* row = prow(in, min(r + u, r1 - 1));
+#pragma unroll
+        for (int k = 0; k < kOut; ++k) val[u][k] = row[src[k]];
       }
-      if (f & kChild) {
-        const size_t o0 = (size_t)tot.x + tot.y +
-                          (size_t)a.n_split * (base2 + p2 + popc(b2 & below));
-        // parent's rotation R(q / |q|) and scales, in float64
-        double q[4];
-        for (int r = 0; r < 4; ++r) q[r] = (double)a.p.quats[(size_t)r * n + i];
-        const double qn = sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
-        const double qw = q[0] / qn, qx = q[1] / qn, qy = q[2] / qn, qz = q[3] / qn;
-        const double R[3][3] = {
-            {1 - 2 * (qy * qy + qz * qz), 2 * (qx * qy - qw * qz), 2 * (qx * qz + qw * qy)},
-            {2 * (qx * qy + qw * qz), 1 - 2 * (qx * qx + qz * qz), 2 * (qy * qz - qw * qx)},
-            {2 * (qx * qz - qw * qy), 2 * (qy * qz + qw * qx), 1 - 2 * (qx * qx + qy * qy)}};
-        double ls[3], s[3], mu[3];
-        for (int r = 0; r < 3; ++r) {
-          ls[r] = (double)a.p.log_scales[(size_t)r * n + i];
-          s[r] = exp(ls[r]);
-          mu[r] = (double)a.p.means[(size_t)r * n + i];
-        }
-        for (int ch = 0; ch < a.n_split; ++ch) {
-          const size_t o = o0 + ch;
-          uint32_t ctr[4] = {(uint32_t)i, 16u + (uint32_t)ch, 0u, 0u};
-          philox4x32_10(ctr, a.k0, a.k1);
-          double z[4];
-          box_muller64(ctr[0], ctr[1], z[0], z[1]);
-          box_muller64(ctr[2], ctr[3], z[2], z[3]);
-          const double l0 = s[0] * z[0], l1 = s[1] * z[1], l2 = s[2] * z[2];
-          for (int r = 0; r < 3; ++r) {
-            prow(a.po, r)[o] = (float)(mu[r] + (R[r][0] * l0 + R[r][1] * l1 + R[r][2] * l2));
-            prow(a.po, 3 + r)[o] = (float)(ls[r] - c.log_div);
-          }
-          for (int r = 6; r < a.rows; ++r) prow(a.po, r)[o] = prow(a.p, r)[i];
-          for (int r = 0; r < a.rows; ++r) {
-            prow(a.mo, r)[o] = 0.f;
-            prow(a.vo, r)[o] = 0.f;
-          }
-          if (a.src) a.src[o] = (int32_t)i;
-        }
+#pragma unroll
+      for (int u = 0; u < kRowsAhead; ++u) {
+        if (r + u >= r1) break;
+        float* row = prow(out, r + u);
+#pragma unroll
+        for (int k = 0; k < kOut; ++k)
+          if (ok[k] && !(own6[k] && r + u < 6)) row[dst[k]] = zer[k] ? 0.f : val[u][k];
       }
     }
-    base0 += t0;
-    base1 += t1;
-    base2 += t2;
+  }
+  if (set != 0 || part != 0) return;
+  if (a.src != nullptr) {
+    for (uint32_t j = threadIdx.x; j < n0; j += kDB) a.src[oKeep + j] = (int32_t)(base + list[0][j]);
+    for (uint32_t j = threadIdx.x; j < n1; j += kDB) a.src[oClone + j] = (int32_t)(base + list[1][j]);
+    for (uint32_t j = threadIdx.x; j < n2 * ns; j += kDB)
+      a.src[oChild + j] = (int32_t)(base + list[2][j / ns]);
+  }
+  for (uint32_t j = threadIdx.x; j < n2 * ns; j += kDB) {
+    const uint32_t i = base + list[2][j / ns], ch = j % ns;
+    const size_t n = (size_t)c.n, o = oChild + j;
+    // parent's rotation R(q / |q|) and scales, in float64
+    double q[4];
+    for (int r = 0; r < 4; ++r) q[r] = (double)a.in[0].quats[(size_t)r * n + i];
+    const double qn = sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
+    const double qw = q[0] / qn, qx = q[1] / qn, qy = q[2] / qn, qz = q[3] / qn;
+    const double R[3][3] = {
+        {1 - 2 * (qy * qy + qz * qz), 2 * (qx * qy - qw * qz), 2 * (qx * qz + qw * qy)},
+        {2 * (qx * qy + qw * qz), 1 - 2 * (qx * qx + qz * qz), 2 * (qy * qz - qw * qx)},
+        {2 * (qx * qz - qw * qy), 2 * (qy * qz + qw * qx), 1 - 2 * (qx * qx + qy * qy)}};
+    uint32_t ctr[4] = {i, 16u + ch, 0u, 0u};
+    philox4x32_10(ctr, a.k0, a.k1);
+    double z[4];
+    box_muller64(ctr[0], ctr[1], z[0], z[1]);
+    box_muller64(ctr[2], ctr[3], z[2], z[3]);
+    double l[3], ls[3];
+    for (int r = 0; r < 3; ++r) {
+      ls[r] = (double)a.in[0].log_scales[(size_t)r * n + i];
+      l[r] = exp(ls[r]) * z[r];
+    }
+    for (int r = 0; r < 3; ++r) {
+      const double mu = (double)a.in[0].means[(size_t)r * n + i];
+      prow(a.out[0], r)[o] = (float)(mu + (R[r][0] * l[0] + R[r][1] * l[1] + R[r][2] * l[2]));
+      prow(a.out[0], 3 + r)[o] = (float)(ls[r] - c.log_div);
+    }
   }
 }
 
@@ -384,12 +430,12 @@ gs_status densify_run(Ctx* ctx, const gs_params& p, const gs_params& m, const gs
   }
   if (nb == 0) return GS_OK;
   ApplyArgs a;
-  a.p = p;
-  a.m = m;
-  a.v = v;
-  a.po = *p_out;
-  a.mo = *m_out;
-  a.vo = *v_out;
+  a.in[0] = p;
+  a.in[1] = m;
+  a.in[2] = v;
+  a.out[0] = *p_out;
+  a.out[1] = *m_out;
+  a.out[2] = *v_out;
   a.src = src_index;
   a.off = off;
   a.nb = nb;
@@ -397,7 +443,9 @@ gs_status densify_run(Ctx* ctx, const gs_params& p, const gs_params& m, const gs
   a.n_split = o.n_split;
   a.k0 = (uint32_t)o.seed;
   a.k1 = (uint32_t)(o.seed >> 32);
-  hipLaunchKernelGGL(k_density_apply, dim3(nb), dim3(kDB), 0, s, c, a);
+  // rows are split over enough blocks to fill the chip (about 2048 resident ones)
+  const int rsplit = std::max(1, std::min(a.rows / kRowsAhead, 2048 / (3 * nb)));
+  hipLaunchKernelGGL(k_density_apply, dim3(nb, 3 * rsplit), dim3(kDB), 0, s, c, a, rsplit);
   GS_LAUNCHED("density_apply");
   return GS_OK;
 }
