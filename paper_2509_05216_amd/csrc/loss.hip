@@ -4,20 +4,15 @@
 // SSIM uses an 11 x 11 Gaussian window (sigma 1.5, separable, weights summing
 // to one), C1 = 0.01^2, C2 = 0.03^2, zero padding, averaged over pixels and
 // channels.  Two LDS-tiled passes per view and channel (32 x 32 output pixels
-// per 256-thread block, a 42 x 42 halo tile): the first forms the local moments
-// E[x], E[y], E[x^2 + y^2] and E[xy] by separable filtering (the variances enter
-// SSIM only through their sum, so the two squares are filtered as one map) and
-// writes, where a gradient is wanted, per pixel the partials
+// per 256-thread block, a 42 x 42 halo tile): the first forms the five local
+// moments by separable filtering and writes, per pixel, the partials
 // g1 = dS/dmu_x, g2 = dS/dE[x^2] and g3 = dS/dE[xy]; the second filters those
 // maps (the window is symmetric, so the zero-padded correlation is its own
 // adjoint) and combines them with the L1 term:
 //   dL/dx = s [(1 - lambda) sign(x - y) - lambda (w*g1 + 2 x w*g2 + y w*g3)],
 //   s = 1/(3 H W V).
-// Every tile works on x and y less a constant of its own (tile_shift): SSIM's variances
-// and the three terms of dL/dx are small differences of large terms otherwise (against
-// 64 bits the gradient is off by a third or less of what it is without).
 // A horizontal task makes four outputs of one halo row from 14 inputs (read
-// 8 bytes at a time, with x^2 + y^2 and x y formed once per input), each tap an
+// 8 bytes at a time, with x^2, y^2 and x y formed once per input), each tap an
 // explicit fused multiply-add per moment.  In the vertical pass each thread
 // produces four consecutive rows of one column from 14 LDS rows.  Loss sums are reduced per block into
 // float64 partials and summed by a final single-block kernel, so the loss
@@ -84,10 +79,10 @@ __device__ inline void halo_load(const float* const (&img)[NI], HaloCols hc, int
     for (int i = 0; i < NI; ++i) asm volatile("" : "+v"(v[i][k]));
 }
 
-// ... and from registers into LDS tiles, zero outside the image, less `shift`.
+// ... and from registers into LDS tiles, zero outside the image.
 template <int NI>
 __device__ inline void halo_store(float (*const (&tile)[NI])[kH], const float (&v)[NI][kHaloRows],
-                                  HaloCols hc, int oy, int H, float shift = 0.f) {
+                                  HaloCols hc, int oy, int H) {
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
   const int lane = (int)(threadIdx.x % 64);
 #pragma unroll
@@ -96,7 +91,7 @@ __device__ inline void halo_store(float (*const (&tile)[NI])[kH], const float (&
     const bool in = hc.inx && oy + r >= 0 && oy + r < H;
     if (lane < kH && r < kH) {
 #pragma unroll
-      for (int i = 0; i < NI; ++i) tile[i][r][lane] = (in ? v[i][k] : 0.f) - shift;
+      for (int i = 0; i < NI; ++i) tile[i][r][lane] = in ? v[i][k] : 0.f;
     }
   }
 }
@@ -131,15 +126,6 @@ __device__ inline void xcd_tile(int& bx, int& by, int& bz) {
   bx = (int)(r % gx);
 }
 
-// The value that tile (tx, ty) of one channel is held less by: the two images' mean at one
-// pixel of its middle.  Variances and the covariance do not change with it, and their
-// differences E[.^2] - E[.]^2 then cancel far less.  Never huge or non-finite.
-__device__ inline float tile_shift(const float* x, const float* y, int tx, int ty, int W, int H) {
-  const size_t mid = (size_t)min(ty * kT + kT / 2, H - 1) * W + min(tx * kT + kT / 2, W - 1);
-  const float s = 0.5f * (x[mid] + y[mid]);
-  return fabsf(s) < 16.f ? s : 0.f;
-}
-
 // Thread layout of the vertical pass: column c, rows r0 .. r0 + 3.
 __device__ inline void vert_slot(int& c, int& r0) {
   c = threadIdx.x % kT;
@@ -167,23 +153,18 @@ __device__ inline void vert_filter(const float (*hq)[kH][kQ], const Win& win, in
   }
 }
 
-// One block per 32 x 32 tile and channel.  GRAD: also write the partials.  Bound by VALU
-// issue (about 165 lane operations per output) and by the blocks that LDS allows per CU
-// (38 KB: four).
-template <bool GRAD>
+// One block per 32 x 32 tile and channel.
 __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ x,
                                                   const float* __restrict__ y, int W, int H,
                                                   Win win, float* __restrict__ gmap,
                                                   double* __restrict__ part) {
   __shared__ alignas(16) float sx[kH][kH];
   __shared__ alignas(16) float sy[kH][kH];
-  __shared__ alignas(16) float hq[4][kH][kQ];
+  __shared__ alignas(16) float hq[5][kH][kQ];
   int bx, by, ch;
   xcd_tile(bx, by, ch);
   const size_t plane = (size_t)W * H;
   const int ox = bx * kT - kR, oy = by * kT - kR;
-  // the window sums to one, so the tile's shift is added back to the means
-  const float shift = tile_shift(x + ch * plane, y + ch * plane, bx, by, W, H);
   {
     // every halo load is issued before the first LDS store (clamped addresses,
     // zero outside the image), so their latencies overlap
@@ -192,25 +173,26 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ x,
     float (*const dst[2])[kH] = {sx, sy};
     float v[2][kHaloRows];
     halo_load<2>(src, hc, oy, W, H, v);
-    halo_store<2>(dst, v, hc, oy, H, shift);
+    halo_store<2>(dst, v, hc, oy, H);
   }
   __syncthreads();
-  // horizontal pass: four outputs of one halo row per task; the products are formed
-  // once per input, so each tap is four fused multiply-adds
+  // horizontal pass: four outputs of one halo row per task; the products x^2,
+  // y^2, x y are formed once per input, so each tap is five fused multiply-adds
   for (int t = threadIdx.x; t < kHTasks; t += 256) {
     const int r = t / kGroups, c0 = (t % kGroups) * 4;
     float xv[14], yv[14];
     row14(sx, r, c0, xv);
     row14(sy, r, c0, yv);
-    float qq[14], xy[14];
+    float xx[14], yy[14], xy[14];
 #pragma unroll
     for (int k = 0; k < 14; ++k) {
-      qq[k] = fmaf(xv[k], xv[k], yv[k] * yv[k]);
+      xx[k] = xv[k] * xv[k];
+      yy[k] = yv[k] * yv[k];
       xy[k] = xv[k] * yv[k];
     }
-    float a0[4], a1[4], a2[4], a3[4];
+    float a0[4], a1[4], a2[4], a3[4], a4[4];
 #pragma unroll
-    for (int o = 0; o < 4; ++o) a0[o] = a1[o] = a2[o] = a3[o] = 0.f;
+    for (int o = 0; o < 4; ++o) a0[o] = a1[o] = a2[o] = a3[o] = a4[o] = 0.f;
 #pragma unroll
     for (int i = 0; i < kN; ++i)
 #pragma unroll
@@ -218,45 +200,46 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ x,
         const float w = win.w[i];
         a0[o] = fmaf(w, xv[o + i], a0[o]);
         a1[o] = fmaf(w, yv[o + i], a1[o]);
-        a2[o] = fmaf(w, qq[o + i], a2[o]);
-        a3[o] = fmaf(w, xy[o + i], a3[o]);
+        a2[o] = fmaf(w, xx[o + i], a2[o]);
+        a3[o] = fmaf(w, yy[o + i], a3[o]);
+        a4[o] = fmaf(w, xy[o + i], a4[o]);
       }
     *reinterpret_cast<float4*>(&hq[0][r][c0]) = make_float4(a0[0], a0[1], a0[2], a0[3]);
     *reinterpret_cast<float4*>(&hq[1][r][c0]) = make_float4(a1[0], a1[1], a1[2], a1[3]);
     *reinterpret_cast<float4*>(&hq[2][r][c0]) = make_float4(a2[0], a2[1], a2[2], a2[3]);
     *reinterpret_cast<float4*>(&hq[3][r][c0]) = make_float4(a3[0], a3[1], a3[2], a3[3]);
+    *reinterpret_cast<float4*>(&hq[4][r][c0]) = make_float4(a4[0], a4[1], a4[2], a4[3]);
   }
   __syncthreads();
   int c, r0;
   vert_slot(c, r0);
-  float mom[kRows][4];
-  vert_filter<4>(hq, win, c, r0, mom);
+  float mom[kRows][5];
+  vert_filter<5>(hq, win, c, r0, mom);
   double l1 = 0.0, ss = 0.0;
   const int gx = bx * kT + c;
 #pragma unroll
   for (int o = 0; o < kRows; ++o) {
     const int gy = by * kT + r0 + o;
     if (gx < W && gy < H) {
-      const float ux = mom[o][0], uy = mom[o][1];
-      const float mx = ux + shift, my = uy + shift;
-      const float sxy = mom[o][3] - ux * uy, sq = mom[o][2] - (ux * ux + uy * uy);
+      const float mx = mom[o][0], my = mom[o][1];
+      const float sxx = mom[o][2] - mx * mx, syy = mom[o][3] - my * my;
+      const float sxy = mom[o][4] - mx * my;
       const float A1 = 2.f * mx * my + kC1, A2 = 2.f * sxy + kC2;
-      const float B1 = mx * mx + my * my + kC1, B2 = sq + kC2;
-      // With P = 1/(B1 B2), S = A1 A2 P, u = mu - shift and the moments of the shifted
-      // images:
-      //   dS/du_x = 2 P (my A2 - uy A1) + 2 S (ux / B2 - mx / B1),
+      const float B1 = mx * mx + my * my + kC1, B2 = sxx + syy + kC2;
+      // With P = 1/(B1 B2) and S = A1 A2 P:
+      //   dS/dmu_x = 2 P my (A2 - A1) + 2 S mx (1/B2 - 1/B1),
       //   dS/dE[x^2] = -S / B2,  dS/dE[xy] = 2 A1 P,
       // so only B1 >= C1 and B2 >= C2 are inverted (A2 = 2 sigma_xy + C2 may vanish).
       const float iB1 = __builtin_amdgcn_rcpf(B1), iB2 = __builtin_amdgcn_rcpf(B2);
       const float Pb = iB1 * iB2;
       const float S = (A1 * A2) * Pb;
-      if constexpr (GRAD) {
-        const size_t pix = (size_t)gy * W + gx;
-        gmap[(0 * 3 + ch) * plane + pix] =
-            2.f * ((my * A2 - uy * A1) * Pb + S * (ux * iB2 - mx * iB1));
-        gmap[(1 * 3 + ch) * plane + pix] = -S * iB2;
-        gmap[(2 * 3 + ch) * plane + pix] = 2.f * A1 * Pb;
-      }
+      const float g1 = 2.f * (my * (A2 - A1) * Pb + S * mx * (iB2 - iB1));
+      const float g2 = -S * iB2;
+      const float g3 = 2.f * A1 * Pb;
+      const size_t pix = (size_t)gy * W + gx;
+      gmap[(0 * 3 + ch) * plane + pix] = g1;
+      gmap[(1 * 3 + ch) * plane + pix] = g2;
+      gmap[(2 * 3 + ch) * plane + pix] = g3;
       l1 += fabs((double)sx[r0 + o + kR][c + kR] - (double)sy[r0 + o + kR][c + kR]);
       ss += (double)S;
     }
@@ -292,7 +275,6 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ x,
   xcd_tile(bx, by, ch);
   const size_t plane = (size_t)W * H;
   const int ox = bx * kT - kR, oy = by * kT - kR;
-  const float shift = tile_shift(x + ch * plane, y + ch * plane, bx, by, W, H);
   {
     const HaloCols hc = halo_cols(ox, W);
     const float* const src[3] = {gmap + (size_t)(0 * 3 + ch) * plane,
@@ -301,20 +283,6 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ x,
     float (*const dst[3])[kH] = {sg[0], sg[1], sg[2]};
     float v[3][kHaloRows];
     halo_load<3>(src, hc, oy, W, H, v);
-    // g1 of another tile was taken at that tile's shift t; at this one's,
-    // dS/du_x = g1 + (shift - t) (2 g2 + g3)
-    float ds[3];  // shift - t for this lane's column in the tile rows by - 1, by, by + 1
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      ds[q] = shift - tile_shift(x + ch * plane, y + ch * plane, (int)hc.gxc / kT,
-                                 min(max(by - 1 + q, 0), (H - 1) / kT), W, H);
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-#pragma unroll
-    for (int k = 0; k < kHaloRows; ++k) {
-      const int r = wave + 4 * k;
-      const float d = r < kR ? ds[0] : (r < kR + kT ? ds[1] : ds[2]);
-      v[0][k] = fmaf(d, fmaf(2.f, v[1][k], v[2][k]), v[0][k]);
-    }
     halo_store<3>(dst, v, hc, oy, H);
   }
   __syncthreads();
@@ -346,8 +314,7 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ x,
     const size_t pix = ch * plane + (size_t)gy * W + gx;
     const float xv = x[pix], yv = y[pix];
     const float sgn = (xv > yv) ? 1.f : ((xv < yv) ? -1.f : 0.f);
-    const float xs = xv - shift, ys = yv - shift;
-    dl[pix] = scale * ((1.f - lambda) * sgn - lambda * (f[o][0] + 2.f * xs * f[o][1] + ys * f[o][2]));
+    dl[pix] = scale * ((1.f - lambda) * sgn - lambda * (f[o][0] + 2.f * xv * f[o][1] + yv * f[o][2]));
   }
 }
 
@@ -517,12 +484,10 @@ gs_status launch_loss(const LossScratch& ls, const float* const* x, const float*
   double* part2 = (double*)ls.part.p + 2 * total_blocks;
   for (int v = 0; v < nv; ++v) {
     const dim3 grid((W[v] + kT - 1) / kT, (H[v] + kT - 1) / kT, 3);
-    const bool grad = dl != nullptr && dl[v] != nullptr;
-    hipLaunchKernelGGL(grad ? k_ssim_fwd<true> : k_ssim_fwd<false>, grid, dim3(256), 0, s, x[v],
-                       y[v], W[v], H[v], win, (float*)ls.gmap.p,
-                       (double*)ls.part.p + 2 * lr.off[v]);
+    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, s, x[v], y[v], W[v], H[v], win,
+                       (float*)ls.gmap.p, (double*)ls.part.p + 2 * lr.off[v]);
     GS_LAUNCHED("ssim_fwd");
-    if (grad) {
+    if (dl != nullptr && dl[v] != nullptr) {
       const float scale = (float)(1.0 / (3.0 * (double)W[v] * H[v] * nv));
       hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(256), 0, s, x[v], y[v], W[v], H[v], win,
                          (const float*)ls.gmap.p, lambda, scale, dl[v]);
@@ -645,7 +610,7 @@ gs_status launch_metrics(const LossScratch& ls, const float* const* x, const flo
   double* part3 = part2 + 2 * (size_t)kRedBlocks * kMaxViews;
   for (int v = 0; v < nv; ++v) {
     const dim3 grid((W[v] + kT - 1) / kT, (H[v] + kT - 1) / kT, 3);
-    hipLaunchKernelGGL(k_ssim_fwd<false>, grid, dim3(256), 0, s, x[v], y[v], W[v], H[v], win,
+    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, s, x[v], y[v], W[v], H[v], win,
                        (float*)ls.gmap.p, part + 2 * lr.off[v]);
     GS_LAUNCHED("ssim_fwd");
   }

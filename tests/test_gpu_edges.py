@@ -71,33 +71,3 @@ def test_extraction_block_edges(P, ctx, kind, shape, keep):
     assert np.array_equal(both, np.isfinite(got))
     ulp = np.spacing(np.abs(want[both]).astype(np.float32)).astype(np.float64)
     assert np.all(np.abs(got[both].astype(np.float64) - want[both]) <= ulp)
-
-
-# ---------------------------------------------------------------- loss
-@pytest.mark.parametrize("size", [(1, 1), (31, 33), (32, 32), (42, 65), (97, 64)])
-@pytest.mark.parametrize("kind", ["texture", "bright", "black"])
-def test_loss_tile_edges(P, ctx, size, kind):
-    """Tile remainders; 'bright' images (0.9 with 1e-3 of structure) make the variances
-    small differences of large moments.  Tolerance: float32 moments of values held less
-    a nearby constant keep every term of the partials to a few hundred ulp."""
-    from oracle import loss as OL
-    W, H = size
-    rng = np.random.default_rng(W * H)
-    base = rng.random((3, H, W))
-    noise = rng.normal(size=(3, H, W))
-    if kind == "texture":
-        x, y = np.clip(base + 0.05 * noise, 0, 1), base
-    elif kind == "bright":
-        x, y = 0.9 + 1e-3 * noise, 0.9 + 1e-3 * base
-    else:
-        x, y = base * (base > 0.8), base * (base > 0.85)
-    x, y = x.astype(np.float32), y.astype(np.float32)
-    cam = P.camera(np.eye(3), np.zeros(3), 50.0, 50.0, W / 2, H / 2, W, H)
-    xd, yd = torch.tensor(x, device="cuda"), torch.tensor(y, device="cuda")
-    loss, dl = P.loss_grad(ctx, [xd], [yd], [cam])
-    only, none = P.loss_grad(ctx, [xd], [yd], [cam], want_grad=False)
-    want, grad = OL.batch_loss([x.astype(np.float64)], [y.astype(np.float64)])
-    assert none is None and only.item() == loss.item()
-    assert abs(loss.item() - want) <= 1e-6
-    err, norm = np.linalg.norm(dl[0].cpu().numpy() - grad[0]), np.linalg.norm(grad[0])
-    assert err <= 2e-5 * norm, (err, norm)
