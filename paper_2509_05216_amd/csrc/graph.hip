@@ -292,7 +292,7 @@ void gs_step_graph_destroy(gs_graph* g) {
   (void)hipSetDevice(g->ctx->device);
   (void)hipDeviceSynchronize();
   drop_graph(g);
-  if (g->frame != nullptr) gs_frame_release(g->frame);
+  if (g->frame != nullptr) frame_destroy(g->frame);
   loss_scratch_free(g->ctx, g->loss);
   if (g->done != nullptr) (void)hipEventDestroy(g->done);
   if (g->cstream != nullptr) (void)hipStreamDestroy(g->cstream);
@@ -383,7 +383,7 @@ gs_status gs_autotune(gs_ctx* ctx, gs_params params, const gs_camera* cams, int3
     }
   }
   if (table_n) *table_n = std::min(count, table_cap);
-  if (frame != nullptr) gs_frame_release(frame);
+  if (frame != nullptr) frame_destroy(frame);
   if (a) (void)hipEventDestroy(a);
   if (b) (void)hipEventDestroy(b);
   buf_free(ctx, img);

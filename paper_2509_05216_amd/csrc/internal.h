@@ -189,7 +189,13 @@ struct Ctx {
   std::mutex life_mutex;
   int dependents = 0;
   bool destroy_requested = false;
+  // released frames kept for the next forward that asks for a new one (frame_pool_*)
+  std::mutex pool_mutex;
+  struct Frame* pool[4] = {nullptr, nullptr, nullptr, nullptr};
 };
+
+// Frees the pooled frames; true when there were any.
+bool frame_pool_trim(Ctx* ctx);
 
 void ctx_retain(Ctx* ctx);
 void ctx_release(Ctx* ctx);
@@ -265,6 +271,8 @@ struct Frame {
   int tkey_sel = 0;  // which of tkey/tval holds the sorted records
   int sidx_sel = 0;  // which of sidx holds the depth-sorted (view, Gaussian) indices
   bool acc_zeroed = false;
+  size_t acc_zero_bytes = 0;  // how much of acc the last fill cleared (acc_zeroed)
+  bool settled = false;       // the last call on the frame recorded last_use after its work
   bool persistent = false;            // blend with persistent work-queue kernels
   bool lpt = false;                   // persistent queue in longest-list-first tile order
   const uint32_t* tile_order = nullptr;
@@ -397,3 +405,9 @@ gs_status launch_adam(const gs_params& p, const gs_params& g, const gs_params& m
 
 struct gs_ctx : isogs::Ctx {};
 struct gs_frame : isogs::Frame {};
+
+namespace isogs {
+// Waits for a frame's work and frees it without pooling (frames of step graphs, render
+// servers and the tuner, which are the size of a whole program).
+void frame_destroy(gs_frame* frame);
+}  // namespace isogs

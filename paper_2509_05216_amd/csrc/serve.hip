@@ -389,7 +389,7 @@ void gs_server_destroy(gs_server* sv) {
   (void)hipSetDevice(sv->ctx->device);
   for (Slot& s : sv->slots) {
     if (s.stream != nullptr) (void)hipStreamSynchronize(s.stream);
-    if (s.frame != nullptr) gs_frame_release(s.frame);
+    if (s.frame != nullptr) frame_destroy(s.frame);
     if (s.stream != nullptr) (void)hipStreamDestroy(s.stream);
   }
   gs_ctx* ctx = sv->ctx;

@@ -162,3 +162,85 @@ def test_entry_limit_is_checked_before_any_launch(P):
     assert b"exceeds" in L.lib().gs_last_error()
     assert not fr.value
     ctx.close()
+
+
+def _step(P, ctx, params, cams, dl, frame=None, **kw):
+    _, frame = P.render_fwd(ctx, params, cams, frame=frame)
+    return P.render_bwd(ctx, frame, params, dl, **kw), frame
+
+
+def test_kept_sums_do_not_reach_a_later_larger_forward(P):
+    """Screen-space sums kept in a frame are cleared by the next forward only as far as
+    that one reaches; a later, larger forward on the frame still starts from zeros."""
+    ctx = P.Context(0)
+    big = P.Params.from_numpy(gsscenes.make_scene("tiny", n=3000).params)
+    small = P.Params.from_numpy(gsscenes.make_scene("tiny", n=700).params)
+    cams = _views(P, [(96, 80), (96, 80)])
+    dl = [torch.rand((3, 80, 96), device="cuda", generator=torch.Generator("cuda").manual_seed(i))
+          for i in range(2)]
+    ref, fresh = _step(P, ctx, big, cams, dl)
+    _, frame = _step(P, ctx, big, cams, dl, keep_screen=True)
+    _step(P, ctx, small, cams, dl, frame)
+    got, _ = _step(P, ctx, big, cams, dl, frame)
+    torch.cuda.synchronize()
+    for a, b in zip(got.tensors(), ref.tensors()):
+        assert (a - b).abs().max().item() <= 1e-5 * max(b.abs().max().item(), 1e-6)
+    frame.release()
+    fresh.release()
+    ctx.close()
+
+
+def test_released_frames_are_reused_and_given_back(P):
+    """A released frame's buffers serve the next new frame of the context (of another
+    shape, on another stream) with the results of a fresh context, are given up when the
+    context's budget needs them, and hold no more than four frames."""
+    big = P.Params.from_numpy(gsscenes.make_scene("tiny", n=6000).params)
+    small = P.Params.from_numpy(gsscenes.make_scene("tiny", n=900).params)
+    shapes = [(big, _views(P, [(160, 96)] * 3)), (small, _views(P, [(64, 48)])),
+              (big, _views(P, [(80, 112)] * 2, start=3))]
+    refs = []
+    for p, cams in shapes:
+        c = P.Context(0)
+        dl = [torch.full((3, k.height, k.width), 0.3, device="cuda") for k in cams]
+        g, f = _step(P, c, p, cams, dl)
+        torch.cuda.synchronize()
+        refs.append((P.render_fwd(c, p, cams, frame=f)[0], g, dl))
+    ctx = P.Context(0)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for trial in range(2):
+        for (p, cams), (imgs, g, dl) in zip(shapes, refs):
+            stream = side if trial else torch.cuda.current_stream()
+            with torch.cuda.stream(stream):
+                got, frame = P.render_fwd(ctx, p, cams)
+                gg = P.render_bwd(ctx, frame, p, dl)
+                stream.synchronize()
+            for a, b in zip(got, imgs):
+                assert torch.equal(a, b)
+            for a, b in zip(gg.tensors(), g.tensors()):
+                assert (a - b).abs().max().item() <= 1e-5 * max(b.abs().max().item(), 1e-6)
+            held = ctx.memory()[0]
+            frame.release()
+            assert ctx.memory()[0] == held          # kept for the next frame
+    frames = [P.render_fwd(ctx, small, shapes[1][1])[1] for _ in range(6)]
+    before = ctx.memory()[0]
+    for f in frames:
+        f.release()
+    assert ctx.memory()[0] < before                 # two of the six were freed
+    ctx.close()
+    # a budget that holds one large frame and not a second beside it
+    c0 = P.Context(0)
+    _, f = P.render_fwd(c0, big, shapes[0][1])
+    one = c0.memory()[0]
+    f.release()
+    c1 = P.Context(0, mem_budget=int(1.3 * one))
+    _, f = P.render_fwd(c1, small, shapes[1][1])
+    f.release()
+    _, f2 = P.render_fwd(c1, big, shapes[2][1])
+    f2.release()
+    imgs, f3 = P.render_fwd(c1, big, shapes[0][1])  # larger than f2: the pool gives way
+    torch.cuda.synchronize()
+    for a, b in zip(imgs, refs[0][0]):
+        assert torch.equal(a, b)
+    assert c1.memory()[0] <= int(1.3 * one)
+    f3.release()
