@@ -359,6 +359,8 @@ static void ctx_free(gs_ctx* ctx) {
   if (ctx->dens_host != nullptr) (void)hipHostFree(ctx->dens_host);
   ctx->dens_host = nullptr;
   buf_free(ctx, ctx->iso_blk);
+  buf_free(ctx, ctx->ray_blk);
+  if (ctx->ray_use != nullptr) (void)hipEventDestroy(ctx->ray_use);
   if (ctx->iso_host != nullptr) (void)hipHostFree(ctx->iso_host);
   ctx->iso_host = nullptr;
   (void)timing_collect(ctx);
@@ -1383,7 +1385,7 @@ gs_status gs_raycast(gs_ctx* ctx, gs_volume vol, float iso, const gs_camera* cam
   }
   gs_status st = set_device(ctx);
   if (st != GS_OK) return st;
-  return launch_raycast(vol, iso, cams, n_views, images, (double)step, (hipStream_t)stream);
+  return launch_raycast(ctx, vol, iso, cams, n_views, images, (double)step, (hipStream_t)stream);
 }
 
 gs_status gs_opacity_reset(gs_ctx* ctx, gs_params p, gs_params m, gs_params v,

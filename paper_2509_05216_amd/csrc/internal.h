@@ -172,6 +172,9 @@ struct Ctx {
   DevBuf dens_blk;                 // gs_densify: block totals and offsets
   uint32_t* dens_host = nullptr;   // gs_densify: pinned read-back of the totals
   DevBuf iso_blk;                  // gs_iso_extract: block totals and offsets
+  DevBuf ray_blk;                  // gs_raycast: cell classes (guarded by ray_mutex)
+  hipEvent_t ray_use = nullptr;    // last use of ray_blk, on any stream
+  std::mutex ray_mutex;
   DevBuf init_xyz;                 // gs_init_from_points: device copy of host points
   unsigned long long* iso_host = nullptr;  // gs_iso_extract: pinned read-back of the count
   // set while a graph is being captured: no allocation, no stage events
@@ -378,7 +381,7 @@ gs_status launch_loss(const LossScratch& ls, const float* const* x, const float*
 gs_status iso_extract_run(Ctx* ctx, const gs_volume& vol, float iso, float keep_prob,
                           uint64_t seed, float* xyz, int64_t cap, int64_t* n_kept,
                           hipStream_t s);
-gs_status launch_raycast(const gs_volume& vol, float iso, const gs_camera* cams, int nv,
+gs_status launch_raycast(Ctx* ctx, const gs_volume& vol, float iso, const gs_camera* cams, int nv,
                          float* const* images, double step, hipStream_t s);
 // density.hip
 gs_status launch_density_accumulate(const Frame& f, const gs_density_stats& st, float scale,

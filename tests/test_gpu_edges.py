@@ -71,3 +71,61 @@ def test_extraction_block_edges(P, ctx, kind, shape, keep):
     assert np.array_equal(both, np.isfinite(got))
     ulp = np.spacing(np.abs(want[both]).astype(np.float32)).astype(np.float64)
     assert np.all(np.abs(got[both].astype(np.float64) - want[both]) <= ulp)
+
+
+def _ray_volume(kind, shape, rng):
+    """float32 (nz, ny, nx) around the level 0.5 (or 0 for "zero")."""
+    nz, ny, nx = shape
+    z, y, x = np.meshgrid(*(np.linspace(-1, 1, k) for k in shape), indexing="ij")
+    if kind == "shell":              # long one-sided runs, then a thin wall
+        v = 0.5 + 0.4 * np.cos(9 * x) - 0.3 * y * z - 0.25
+    elif kind == "noise":            # a crossing in most cells
+        v = rng.random(shape)
+    elif kind == "ties":             # samples that equal the level exactly
+        v = rng.integers(0, 3, shape) * 0.25 + 0.25
+    elif kind == "zero":             # level 0, values of very different size
+        v = (x + 0.1 * y) * 10.0 ** (6 * z)
+    else:                            # not finite in places
+        v = 0.5 + 0.4 * np.cos(7 * x)
+        v[nz // 2, ny // 2, nx // 3] = np.nan
+        v[nz // 3, ny // 2, nx // 2] = np.inf
+        v[0, ny // 2, (2 * nx) // 3] = -np.inf
+    return v.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind,shape,step", [
+    ("shell", (5, 6, 421), 0.006), ("shell", (390, 4, 9), 0.0051), ("shell", (2, 401, 5), 0.004),
+    ("noise", (6, 7, 400), 0.005), ("ties", (7, 395, 6), 0.005), ("zero", (5, 8, 403), 0.0055),
+    ("odd", (6, 9, 400), 0.005), ("shell", (17, 16, 18), 0.11), ("ties", (9, 8, 7), 0.05),
+    ("odd", (12, 11, 13), 0.07), ("zero", (2, 2, 2), 0.03),
+])
+def test_raycast_routes_match_oracle(P, kind, shape, step):
+    """Rays through cell classes (long volumes) and without them (small ones), from
+    outside and inside the box, along an axis, and at one-sided, level-valued and
+    non-finite samples: the float64 oracle's image, to the rounding of a float32 image."""
+    from oracle import camera as ocam
+    from oracle import iso as OI
+    from paper_2509_05216_amd import iso
+    rng = np.random.default_rng(7)
+    vol = _ray_volume(kind, shape, rng)
+    level = 0.0 if kind == "zero" else 0.5
+    step = float(np.float32(step))
+    cams = [ocam.to_float32(c) for c in ocam.orbit_cameras(5, 2.5, 60.0, 13, 9)][1:3]
+    inside = dict(cams[0])
+    inside["R"], inside["t"] = np.eye(3), np.array([0.1, 0.05, 0.2])
+    along = dict(inside)             # the middle pixel's ray runs along z alone
+    along.update(t=np.array([0.0, 0.0, 2.0]), cx=6.5, cy=4.5)
+    cams += [ocam.to_float32(inside), ocam.to_float32(along)]
+    V = iso.Volume(torch.tensor(vol, device="cuda"))
+    ctx = P.Context(0)
+    imgs = iso.raycast(ctx, V, [P.camera_from_dict(c) for c in cams], level, step)
+    again = iso.raycast(ctx, V, [P.camera_from_dict(c) for c in cams], level, step)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        want = [OI.raycast(vol, (-1, -1, -1), (1, 1, 1), level, c, step) for c in cams]
+    for img, rep, w in zip(imgs, again, want):
+        got = img.cpu().numpy().astype(np.float64)
+        assert np.array_equal(np.isnan(got), np.isnan(w))
+        assert np.nanmax(np.abs(got - w)) < 1e-5
+        assert torch.equal(img.nan_to_num(), rep.nan_to_num())
+    assert any(w.max() > 0 for w in want) or kind == "zero"
