@@ -457,7 +457,6 @@ static gs_frame* frame_new(Ctx* ctx, int64_t entries) {
     }
   }
   if (fr != nullptr) {
-    fr->acc_zeroed = false;
     fr->visible = 0;
   } else {
     fr = new (std::nothrow) gs_frame();

@@ -10,10 +10,12 @@
 // records gives, at a fraction of the traffic.
 //
 // Radix passes use 8-bit digits, 256 threads (4 waves of 64) and 16 keys per
-// thread per block.  Stable ranking inside a block uses wave ballots: for each
+// thread per block (4 in small sorts).  Stable ranking inside a block uses wave ballots: for each
 // item slot the lanes holding the same digit are found with 8 ballots, the
 // group's leader bumps a per-wave LDS counter, and lanes take their rank from
 // the popcount of lower peer lanes.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace isogs {
@@ -103,13 +105,13 @@ __global__ __launch_bounds__(kThreads) void k_scan_partials(uint64_t* partial, u
 
 // Down-sweep.  With few blocks each forms its carry-in by summing the totals of
 // the blocks before it (read from L2), so no separate scan of the totals is
-// launched, and the last block writes the grand total when d_total is given;
-// with many (prescanned), k_scan_partials has already turned the totals into
+// launched, and the last block writes the grand total when d_total is given
+// (`per` totals stand for one block's elements); with many (prescanned), k_scan_partials has already turned the totals into
 // the carries and written the grand total.
 template <class F>
 __global__ __launch_bounds__(kThreads) void k_scan_down(F f, uint32_t n, const uint64_t* partial,
                                                         uint32_t* out, uint64_t* d_total,
-                                                        int prescanned) {
+                                                        int prescanned, uint32_t per) {
   __shared__ uint64_t sw[kWaves];
   // striped (coalesced) loads and stores, transposed through LDS so that each
   // thread scans kItems consecutive elements; one pad word per 32 avoids bank conflicts
@@ -135,7 +137,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(F f, uint32_t n, const u
     ctot = partial[blockIdx.x];
   } else {
     uint64_t carry = 0;
-    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kThreads) carry += partial[b];
+    for (uint32_t b = threadIdx.x; b < blockIdx.x * per; b += kThreads) carry += partial[b];
     block_exclusive_scan(carry, sw, ctot);  // ctot: the sum over all threads
   }
   uint64_t total;
@@ -164,15 +166,24 @@ __global__ __launch_bounds__(256) void k_counts(const uint32_t* __restrict__ sid
                                                 const uint2* __restrict__ rect, uint32_t n,
                                                 uint32_t* __restrict__ counts,
                                                 uint32_t* __restrict__ srx,
-                                                uint32_t* __restrict__ sry) {
+                                                uint32_t* __restrict__ sry,
+                                                uint64_t* __restrict__ partial) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint2 r = rect[sidx[i]];
-  srx[i] = r.x;
-  sry[i] = r.y;
-  const int x0 = (int)(r.x & 0xffffu), y0 = (int)(r.x >> 16);
-  const int x1 = (int)(r.y & 0xffffu), y1 = (int)(r.y >> 16);
-  counts[i] = (x1 < x0 || y1 < y0) ? 0u : (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1));
+  uint32_t m = 0;
+  if (i < n) {
+    const uint2 r = rect[sidx[i]];
+    srx[i] = r.x;
+    sry[i] = r.y;
+    const int x0 = (int)(r.x & 0xffffu), y0 = (int)(r.x >> 16);
+    const int x1 = (int)(r.y & 0xffffu), y1 = (int)(r.y >> 16);
+    m = (x1 < x0 || y1 < y0) ? 0u : (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1));
+    counts[i] = m;
+  }
+  if (partial == nullptr) return;
+  __shared__ uint64_t sw[kWaves];
+  uint64_t total;
+  block_exclusive_scan(m, sw, total);
+  if (threadIdx.x == 0) partial[blockIdx.x] = total;
 }
 
 // ---------------------------------------------------------------- radix sort
@@ -185,9 +196,11 @@ __device__ inline uint32_t xcd_chunk(uint32_t nblocks) {
   return blockIdx.x < 8 * n8 ? (blockIdx.x % 8) * n8 + blockIdx.x / 8 : blockIdx.x;
 }
 
+template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void k_radix_hist(const uint32_t* __restrict__ keys,
                                                          uint32_t n_max, const uint32_t* d_n,
                                                          int shift, uint32_t nblocks,
+                                                         uint32_t stride,
                                                          uint32_t* __restrict__ hist) {
   __shared__ uint32_t h[kWaves][kRadix];
   const int wave = threadIdx.x / 64, lane = __lane_id();
@@ -198,12 +211,12 @@ __global__ __launch_bounds__(kThreads) void k_radix_hist(const uint32_t* __restr
   // counts of neighbouring chunks, adjacent in every digit's row of the table,
   // are written through the same L2
   const uint32_t chunk = xcd_chunk(nblocks);
-  // the wave's 1024 keys as four 16-byte reads per lane, all issued before the
+  // the wave's keys as 16-byte reads, all issued before the
   // counting (the order of counting does not matter)
-  const uint32_t base = chunk * (uint32_t)kChunk + wave * 64 * kItems;
-  uint4 q[kItems / 4];
+  const uint32_t base = chunk * (uint32_t)(kThreads * ITEMS) + wave * 64 * ITEMS;
+  uint4 q[ITEMS / 4];
 #pragma unroll
-  for (int j = 0; j < kItems / 4; ++j) {
+  for (int j = 0; j < ITEMS / 4; ++j) {
     const uint32_t i = base + 4u * (j * 64 + lane);
     if (i + 4 <= n) {
       q[j] = *reinterpret_cast<const uint4*>(keys + i);
@@ -219,7 +232,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_hist(const uint32_t* __restr
   // word: the lanes holding lane 0's digit, and those holding the digit of the
   // first lane left, are counted by one atomic each; the rest add one apiece.
 #pragma unroll
-  for (int j = 0; j < kItems / 4; ++j) {
+  for (int j = 0; j < ITEMS / 4; ++j) {
     const uint32_t i = base + 4u * (j * 64 + lane);
     const uint32_t kk[4] = {q[j].x, q[j].y, q[j].z, q[j].w};
 #pragma unroll
@@ -246,7 +259,84 @@ __global__ __launch_bounds__(kThreads) void k_radix_hist(const uint32_t* __restr
   for (int d = threadIdx.x; d < kRadix; d += kThreads) {
     uint32_t s = 0;
     for (int w = 0; w < kWaves; ++w) s += h[w][d];
-    hist[(size_t)d * nblocks + chunk] = s;
+    uint32_t* row = hist + (size_t)d * stride;
+    row[chunk] = s;
+    if (chunk == nblocks - 1)
+      for (uint32_t c = nblocks; c < stride; ++c) row[c] = 0u;
+  }
+}
+
+// Rows of the digit table: row d (stride words, a multiple of four) holds digit d's count
+// in every chunk, and the totals of the rows follow the table.  One block per digit turns
+// its row into the exclusive prefix over the chunks and writes the total; the scatter
+// itself scans the 256 totals.  One launch instead of the two of a scan over the whole
+// table (passes over 16M and 42M keys: 7 us on average instead of 18).
+__global__ __launch_bounds__(kThreads) void k_digit_rows(uint32_t* __restrict__ hist,
+                                                         uint32_t stride) {
+  __shared__ uint32_t sw[2][kWaves];
+  uint4* row = reinterpret_cast<uint4*>(hist + (size_t)blockIdx.x * stride);
+  const uint32_t quads = stride / 4;
+  const int lane = __lane_id(), wave = threadIdx.x / 64;
+  uint32_t carry = 0;
+  int buf = 0;
+  for (uint32_t q0 = 0; q0 < quads; q0 += kThreads * 4, buf ^= 1) {  // 4096 counts a round
+    uint4 v[4];
+    uint32_t sum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t q = q0 + threadIdx.x * 4 + j;
+      v[j] = q < quads ? row[q] : make_uint4(0u, 0u, 0u, 0u);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sum += v[j].x + v[j].y + v[j].z + v[j].w;
+    uint32_t inc = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = (uint32_t)__shfl_up((int)inc, d, 64);
+      if (lane >= d) inc += y;
+    }
+    if (lane == 63) sw[buf][wave] = inc;
+    __syncthreads();  // one barrier a round: the next round's sums go to the other buffer
+    uint32_t run = carry + inc - sum;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const uint32_t t = sw[buf][w];
+      if (w < wave) run += t;
+      carry += t;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint4 o;
+      o.x = run;
+      o.y = o.x + v[j].x;
+      o.z = o.y + v[j].y;
+      o.w = o.z + v[j].z;
+      run = o.w + v[j].w;
+      const uint32_t q = q0 + threadIdx.x * 4 + j;
+      if (q < quads) row[q] = o;
+    }
+  }
+  if (threadIdx.x == 0) hist[(size_t)kRadix * stride + blockIdx.x] = carry;
+}
+
+// This chunk's prefix in row d, and the row's total: from the scanned table and its
+// totals, or (RAW, small tables) summed here from the counts.
+template <bool RAW>
+__device__ inline void digit_row(const uint32_t* __restrict__ hist, uint32_t stride,
+                                 uint32_t chunk, int d, uint32_t& before, uint32_t& total) {
+  if constexpr (!RAW) {
+    before = hist[(size_t)d * stride + chunk];
+    total = hist[(size_t)kRadix * stride + d];
+    return;
+  }
+  const uint4* row = reinterpret_cast<const uint4*>(hist + (size_t)d * stride);
+  before = total = 0;
+  for (uint32_t q = 0; q < stride / 4; ++q) {
+    const uint4 v = row[q];
+    const uint32_t c = 4 * q;
+    total += v.x + v.y + v.z + v.w;
+    before += (c < chunk ? v.x : 0u) + (c + 1 < chunk ? v.y : 0u) + (c + 2 < chunk ? v.z : 0u) +
+              (c + 3 < chunk ? v.w : 0u);
   }
 }
 
@@ -256,15 +346,17 @@ __global__ __launch_bounds__(kThreads) void k_radix_hist(const uint32_t* __restr
 // of one digit's run: the global writes are coalesced.
 static_assert(kThreads == kRadix, "one thread per digit in the offset scan");
 
+template <bool RAW, int ITEMS>
 __global__ __launch_bounds__(kThreads) void k_radix_scatter(
     const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
     uint32_t* __restrict__ vout, uint32_t n_max, const uint32_t* d_n, int shift, uint32_t nblocks,
-    const uint32_t* __restrict__ hist_scanned) {
+    uint32_t stride, const uint32_t* __restrict__ hist) {
+  constexpr int CHUNK = kThreads * ITEMS;
   __shared__ uint32_t cnt[kWaves][kRadix];
   __shared__ uint32_t gofs[kRadix];    // global position of local index 0 of digit d's run
   __shared__ uint32_t lstart[kRadix];  // block-local start of digit d
   __shared__ uint64_t scan_tmp[kWaves];
-  __shared__ uint32_t sk[kChunk], sv[kChunk];
+  __shared__ uint32_t sk[CHUNK], sv[CHUNK];
   const int wave = threadIdx.x / 64, lane = __lane_id();
   for (int d = threadIdx.x; d < kWaves * kRadix; d += kThreads) (&cnt[0][0])[d] = 0;
   const uint32_t n = load_n(n_max, d_n);
@@ -272,11 +364,13 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(
   // output, meet in the same L2, and the cache lines they share are written
   // back whole
   const uint32_t chunk = xcd_chunk(nblocks);
-  const uint32_t base = chunk * (uint32_t)kChunk + wave * 64 * kItems;
-  if (chunk * (uint32_t)kChunk >= n) return;  // whole block empty (uniform)
-  uint32_t key[kItems], val[kItems], rank[kItems];
+  const uint32_t base = chunk * (uint32_t)CHUNK + wave * 64 * ITEMS;
+  if (chunk * (uint32_t)CHUNK >= n) return;  // whole block empty (uniform)
+  uint32_t before, total_d;  // thread d: digit d's keys in earlier chunks, and in all
+  digit_row<RAW>(hist, stride, chunk, threadIdx.x, before, total_d);
+  uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
 #pragma unroll
-  for (int j = 0; j < kItems; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const uint32_t i = base + j * 64 + lane;
     const bool ok = i < n;
     key[j] = ok ? kin[i] : 0u;
@@ -285,7 +379,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(
   __syncthreads();
   const uint64_t lt = lanemask_lt();
 #pragma unroll
-  for (int j = 0; j < kItems; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const uint32_t i = base + j * 64 + lane;
     const bool ok = i < n;
     const uint32_t d = (key[j] >> shift) & 0xffu;
@@ -322,14 +416,17 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(
       cnt[w][d] = run;
       run += c;
     }
+    // one scan for both: this block's keys of lower digits (at most 4096) in the low
+    // 16 bits, all chunks' keys of lower digits above them
     uint64_t total;
-    const uint32_t start = (uint32_t)block_exclusive_scan(run, scan_tmp, total);
+    const uint64_t low = block_exclusive_scan(((uint64_t)total_d << 16) | run, scan_tmp, total);
+    const uint32_t start = (uint32_t)low & 0xffffu;
     lstart[d] = start;
-    gofs[d] = hist_scanned[(size_t)d * nblocks + chunk] - start;
+    gofs[d] = (uint32_t)(low >> 16) + before - start;
   }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kItems; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const uint32_t i = base + j * 64 + lane;
     if (i < n) {
       const uint32_t d = (key[j] >> shift) & 0xffu;
@@ -339,7 +436,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_scatter(
     }
   }
   __syncthreads();
-  const uint32_t nloc = min((uint32_t)kChunk, n - chunk * (uint32_t)kChunk);
+  const uint32_t nloc = min((uint32_t)CHUNK, n - chunk * (uint32_t)CHUNK);
   for (uint32_t t = threadIdx.x; t < nloc; t += kThreads) {
     const uint32_t k = sk[t];
     const uint32_t pos = gofs[(k >> shift) & 0xffu] + t;
@@ -363,9 +460,12 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
                                               const uint32_t* __restrict__ offs, uint32_t count,
                                               uint32_t cap, uint32_t* __restrict__ tkey,
                                               uint32_t* __restrict__ tval,
-                                              uint32_t* overflow) {
+                                              uint32_t* overflow, uint2* __restrict__ ranges,
+                                              uint32_t tiles) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = __lane_id();
+  // the tiles' ranges start empty (k_ranges, after the sort, writes those with records)
+  for (uint32_t t = i; t < tiles; t += gridDim.x * blockDim.x) ranges[t] = make_uint2(0u, 0u);
   uint32_t need = 0, o = 0, idx = 0, key0 = 0, w = 1, tx = 0;
   if (i < count) {
     idx = sidx[i];
@@ -503,14 +603,35 @@ inline uint32_t nblocks_of(uint32_t n) {
   return (uint32_t)(((uint64_t)n + kChunk - 1) / kChunk);
 }
 
-// The scanned digit table of a sort's last pass holds, at (digit d, chunk 0),
-// the number of keys whose top byte is below d.  After a depth sort (positive
-// float32 depths, untouched entries keyed 0xffffffff) the entry of digit 0xff
-// is the count of touched entries; an empty table (every key below 0xff) gives n.
-__global__ void k_visible_count(const uint32_t* __restrict__ hist_scanned, uint32_t nblocks,
-                                uint32_t n, uint32_t* __restrict__ dst) {
-  const uint32_t below = hist_scanned[(size_t)255 * nblocks];
-  *dst = below <= n ? below : n;
+// After a depth sort (positive float32 depths, untouched entries keyed 0xffffffff) the
+// keys whose top byte is below 0xff are the touched entries: all but the total of the last
+// pass's row 255.
+template <bool RAW>
+__global__ void k_visible_count(const uint32_t* __restrict__ hist, uint32_t stride, uint32_t n,
+                                uint32_t* __restrict__ dst) {
+  uint32_t before, total;
+  digit_row<RAW>(hist, stride, 0u, 255, before, total);
+  *dst = n - total;
+}
+
+// Digit tables of up to this many chunks are summed by each scatter block itself instead
+// of scanned by a launch of their own (16-key passes: 17 chunks 9.5 us against 9.5 and 3 for
+// the launch, 147 chunks 20.5 against 12.6 and 3).
+constexpr uint32_t kRawChunks = 64;
+
+inline uint32_t row_stride(uint32_t nb) { return (nb + 3u) & ~3u; }
+
+// Keys per thread of a sort of n pairs: a block's chain of ranking steps sets the time of
+// a small sort (a scatter pass with 4 instead of 16 keys a thread: 10k pairs 5.0 instead of
+// 9.6 us, 600k 9.8 instead of 12.5, 1M 9.7 instead of 11.1), the lengths of the digit runs
+// that it writes that of a large one.
+constexpr uint32_t kSmallSort = 1u << 20;
+
+inline int sort_items(uint32_t n) { return n <= kSmallSort ? 4 : kItems; }
+
+inline uint32_t sort_chunks(uint32_t n) {
+  const uint32_t c = (uint32_t)(kThreads * sort_items(n));
+  return (uint32_t)(((uint64_t)n + c - 1) / c);
 }
 
 }  // namespace
@@ -525,26 +646,9 @@ gs_status launch_fill_u32(void* p, uint32_t value, size_t count, hipStream_t s) 
   return GS_OK;
 }
 
-// Exclusive scan of f over n values into out (in place when out is f's array):
-// block totals, then either the down-sweep summing its predecessors (up to
-// kDirectBlocks blocks) or a one-block scan of the totals first.
+// Up to this many blocks a down-sweep sums its predecessors' totals itself; above that a
+// one-block scan of the totals comes first.
 constexpr uint32_t kDirectBlocks = 2048;
-
-static gs_status scan_launch(ArrayIn f, uint32_t n, uint64_t* partial, uint32_t* out,
-                             uint64_t* d_total, hipStream_t s) {
-  const uint32_t nb = nblocks_of(n);
-  hipLaunchKernelGGL(k_scan_reduce<ArrayIn>, dim3(nb), dim3(kThreads), 0, s, f, n, partial);
-  GS_LAUNCHED("scan_reduce");
-  const int pre = nb > kDirectBlocks ? 1 : 0;
-  if (pre) {
-    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kThreads), 0, s, partial, nb, d_total);
-    GS_LAUNCHED("scan_partials");
-  }
-  hipLaunchKernelGGL(k_scan_down<ArrayIn>, dim3(nb), dim3(kThreads), 0, s, f, n,
-                     (const uint64_t*)partial, out, d_total, pre);
-  GS_LAUNCHED("scan_down");
-  return GS_OK;
-}
 
 static gs_status ensure_scratch(Ctx* ctx, SortScratch& ss, uint32_t nb, size_t hist_entries,
                                 hipStream_t s) {
@@ -558,14 +662,34 @@ static gs_status ensure_scratch(Ctx* ctx, SortScratch& ss, uint32_t nb, size_t h
 gs_status scan_tile_counts(Ctx* ctx, SortScratch& ss, const uint32_t* sidx, const uint2* rect,
                            uint32_t n, uint32_t* offs, uint32_t* srx, uint32_t* sry,
                            uint64_t* d_total, hipStream_t s) {
-  const uint32_t nb = nblocks_of(n);
-  gs_status st = ensure_scratch(ctx, ss, nb, 0, s);
+  const uint32_t nb = nblocks_of(n), ng = (n + 255) / 256;
+  // few entries: the gather's blocks leave their totals, which the down-sweep sums (16 to
+  // a block of its own); many: totals per chunk by a launch of their own (the gather runs
+  // best at one entry per thread)
+  const bool fused = ng <= kDirectBlocks;
+  gs_status st = ensure_scratch(ctx, ss, fused ? ng : nb, 0, s);
   if (st != GS_OK) return st;
+  auto* partial = (uint64_t*)ss.partial.p;
   // gather the counts once (random rect reads), then scan them in place, coalesced
-  hipLaunchKernelGGL(k_counts, dim3((n + 255) / 256), dim3(256), 0, s, sidx, rect, n, offs, srx,
-                     sry);
+  hipLaunchKernelGGL(k_counts, dim3(ng), dim3(256), 0, s, sidx, rect, n, offs, srx, sry,
+                     fused ? partial : nullptr);
   GS_LAUNCHED("counts");
-  return scan_launch(ArrayIn{offs}, n, (uint64_t*)ss.partial.p, offs, d_total, s);
+  const ArrayIn f{offs};
+  int pre = 0;
+  if (!fused) {
+    hipLaunchKernelGGL(k_scan_reduce<ArrayIn>, dim3(nb), dim3(kThreads), 0, s, f, n, partial);
+    GS_LAUNCHED("scan_reduce");
+    pre = nb > kDirectBlocks ? 1 : 0;
+    if (pre) {
+      hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kThreads), 0, s, partial, nb, d_total);
+      GS_LAUNCHED("scan_partials");
+    }
+  }
+  hipLaunchKernelGGL(k_scan_down<ArrayIn>, dim3(nb), dim3(kThreads), 0, s, f, n,
+                     (const uint64_t*)partial, offs, d_total, pre,
+                     fused ? (uint32_t)(kChunk / 256) : 1u);
+  GS_LAUNCHED("scan_down");
+  return GS_OK;
 }
 
 gs_status sort_pairs_u32(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const uint32_t* vin,
@@ -573,25 +697,29 @@ gs_status sort_pairs_u32(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const u
                          const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s) {
   *result_in_b = 0;
   if (n == 0) return GS_OK;
-  const uint32_t nb = nblocks_of(n);
-  const uint32_t hist_n = (uint32_t)kRadix * nb;
-  const uint32_t hb = nblocks_of(hist_n);
-  gs_status st = ensure_scratch(ctx, ss, hb > nb ? hb : nb, hist_n, s);
+  gs_status st = sort_reserve(ctx, ss, n, s);
   if (st != GS_OK) return st;
+  const uint32_t nb = sort_chunks(n), stride = row_stride(nb);
+  const bool raw = nb <= kRawChunks, small = sort_items(n) == 4;
   auto* hist = (uint32_t*)ss.hist.p;
-  auto* partial = (uint64_t*)ss.partial.p;
   uint32_t* kb[2] = {kA, kB};
   uint32_t* vb[2] = {vA, vB};
   const uint32_t* ki = kin;
   const uint32_t* vi = vin;
   int out = 0;
   for (int shift = 0; shift < bits; shift += 8) {
-    hipLaunchKernelGGL(k_radix_hist, dim3(nb), dim3(kThreads), 0, s, ki, n, d_n, shift, nb, hist);
+    auto count = small ? k_radix_hist<4> : k_radix_hist<kItems>;
+    hipLaunchKernelGGL(count, dim3(nb), dim3(kThreads), 0, s, ki, n, d_n, shift, nb,
+                       stride, hist);
     GS_LAUNCHED("radix_hist");
-    st = scan_launch(ArrayIn{hist}, hist_n, partial, hist, nullptr, s);
-    if (st != GS_OK) return st;
-    hipLaunchKernelGGL(k_radix_scatter, dim3(nb), dim3(kThreads), 0, s, ki, vi, kb[out], vb[out],
-                       n, d_n, shift, nb, hist);
+    if (!raw) {
+      hipLaunchKernelGGL(k_digit_rows, dim3(kRadix), dim3(kThreads), 0, s, hist, stride);
+      GS_LAUNCHED("digit_rows");
+    }
+    auto scatter = small ? (raw ? k_radix_scatter<true, 4> : k_radix_scatter<false, 4>)
+                         : (raw ? k_radix_scatter<true, kItems> : k_radix_scatter<false, kItems>);
+    hipLaunchKernelGGL(scatter, dim3(nb), dim3(kThreads), 0, s, ki, vi, kb[out], vb[out], n, d_n,
+                       shift, nb, stride, (const uint32_t*)hist);
     GS_LAUNCHED("radix_scatter");
     ki = kb[out];
     vi = vb[out];
@@ -608,14 +736,13 @@ gs_status launch_emit(const ViewTable& vt, Frame& f, const uint32_t* sidx, const
   const uint32_t cap = (uint32_t)(cap_bytes / sizeof(uint32_t));
   hipLaunchKernelGGL(k_emit, dim3((count + 255) / 256), dim3(256), 0, s, vt, sidx, srx,
                      sry, (const uint32_t*)f.offs.p, count, cap, (uint32_t*)f.tkey[0].p,
-                     (uint32_t*)f.tval[0].p, overflow);
+                     (uint32_t*)f.tval[0].p, overflow, (uint2*)f.ranges.p,
+                     (uint32_t)f.vt.total_tiles);
   GS_LAUNCHED("emit");
   return GS_OK;
 }
 
 gs_status launch_ranges(Frame& f, uint32_t n_rec, const uint32_t* d_K, hipStream_t s) {
-  gs_status st = launch_fill_u32(f.ranges.p, 0u, (size_t)f.vt.total_tiles * 2, s);
-  if (st != GS_OK) return st;
   if (n_rec == 0) return GS_OK;
   const uint32_t quads = (n_rec + 3) / 4;
   hipLaunchKernelGGL(k_ranges, dim3((quads + 255) / 256), dim3(256), 0, s,
@@ -632,16 +759,17 @@ gs_status launch_clamp_count(const uint64_t* total, uint32_t cap, uint32_t* K,
 }
 
 gs_status sort_reserve(Ctx* ctx, SortScratch& ss, uint32_t n, hipStream_t s) {
-  const uint32_t nb = nblocks_of(n);
-  const uint32_t hist_n = (uint32_t)kRadix * nb;
-  const uint32_t hb = nblocks_of(hist_n);
-  return ensure_scratch(ctx, ss, hb > nb ? hb : nb, hist_n, s);
+  // (any smaller sort's table fits too: the small form's is of at most 1024 chunks)
+  const uint32_t nb = std::max(sort_chunks(n), sort_chunks(std::min(n, kSmallSort)));
+  return ensure_scratch(ctx, ss, nblocks_of(n), (size_t)kRadix * (row_stride(nb) + 1), s);
 }
 
 gs_status launch_visible_count(const SortScratch& ss, uint32_t n, uint32_t* dst, hipStream_t s) {
   if (n == 0) return launch_fill_u32(dst, 0u, 1, s);
-  hipLaunchKernelGGL(k_visible_count, dim3(1), dim3(1), 0, s, (const uint32_t*)ss.hist.p,
-                     nblocks_of(n), n, dst);
+  const uint32_t nb = sort_chunks(n);
+  auto kern = nb <= kRawChunks ? k_visible_count<true> : k_visible_count<false>;
+  hipLaunchKernelGGL(kern, dim3(1), dim3(1), 0, s, (const uint32_t*)ss.hist.p, row_stride(nb), n,
+                     dst);
   GS_LAUNCHED("visible_count");
   return GS_OK;
 }

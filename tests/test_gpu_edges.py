@@ -129,3 +129,41 @@ def test_raycast_routes_match_oracle(P, kind, shape, step):
         assert np.nanmax(np.abs(got - w)) < 1e-5
         assert torch.equal(img.nan_to_num(), rep.nan_to_num())
     assert any(w.max() > 0 for w in want) or kind == "zero"
+
+
+# ---------------------------------------------------------------- binning
+@pytest.mark.parametrize("n", [
+    1, 1023, 1025,                # one block of four keys a thread, and one key more
+    65536, 65537,                 # digit tables summed by the scatter itself, then scanned
+    524288, 524289,               # the gather's blocks leave the totals, then a launch does
+    1048576, 1048577])            # four, then sixteen keys a thread
+def test_binning_at_sort_sizes(P, ctx, n):
+    """Records, ranges and counts of n Gaussians against a stable sort of the exported
+    rectangles and depths (whole numbers: equal)."""
+    g = torch.Generator("cuda").manual_seed(n)
+    means = torch.rand((3, n), device="cuda", generator=g) * 3 - 1.5     # some off the view
+    p = P.Params(means, torch.full((3, n), -4.6, device="cuda"),
+                 torch.tensor([[1.], [0], [0], [0]], device="cuda").repeat(1, n).contiguous(),
+                 torch.zeros(n, device="cuda"), torch.zeros((3, n), device="cuda"), 0)
+    cam = P.orbit_cameras(4, 2.5, 60.0, 200, 120)[2]
+    _, frame = P.render_fwd(ctx, p, [cam], tile=8, lds_depth=64)
+    st = frame.stats()
+    rect = frame.export("rects").view(n, 2).long() & 0xffffffff
+    depth = frame.export("depths").long() & 0xffffffff
+    x0, y0, x1, y1 = rect[:, 0] & 0xffff, rect[:, 0] >> 16, rect[:, 1] & 0xffff, rect[:, 1] >> 16
+    w, h = (x1 - x0 + 1).clamp(min=0), (y1 - y0 + 1).clamp(min=0)
+    m = w * h
+    assert st["n_visible"] == int((m > 0).sum()) and st["n_records"] == int(m.sum())
+    order = torch.sort(depth, stable=True)[1]
+    e = torch.repeat_interleave(order, m[order])
+    r = torch.arange(e.numel(), device="cuda") - torch.repeat_interleave(
+        m[order].cumsum(0) - m[order], m[order])
+    tile = (y0[e] + r // w[e].clamp(min=1)) * 25 + x0[e] + r % w[e].clamp(min=1)
+    tile, by = torch.sort(tile, stable=True)
+    assert torch.equal(frame.export("values").long(), e[by])
+    assert torch.equal(frame.export("keys"), (tile << 32) | depth[e[by]])
+    count = torch.bincount(tile, minlength=st["n_tiles"])
+    end = count.cumsum(0)
+    want = torch.stack([end - count, end], 1) * (count > 0)[:, None]
+    assert torch.equal(frame.export("ranges").view(-1, 2).long(), want)
+    frame.release()
