@@ -509,6 +509,20 @@ gs_status gs_densify(gs_ctx* ctx, gs_params p, gs_params m, gs_params v,
                      gs_params m_out, gs_params v_out, int32_t* src_index,
                      gs_density_info* info, void* stream);
 
+/* gs_densify in one call, with the output sets allocated by the caller between the counts
+ * and the writing (gs_densify with p_out.means = NULL and then again counts twice): `alloc`
+ * is called once, on the calling thread, after the counts are in *info; it fills
+ * sets[0..2] (p_out, m_out, v_out as for gs_densify, n equal to info->n_out) and, if
+ * wanted, *src_index, and returns 0, or anything else to end the call with GS_ERR_NOMEM.
+ * With info->n_out == 0 nothing is written, whatever it fills in.  It must not make
+ * another densification on the same context. */
+typedef int32_t (*gs_densify_sets_fn)(void* user, const gs_density_info* info, gs_params* sets,
+                                      int32_t** src_index);
+gs_status gs_densify_alloc(gs_ctx* ctx, gs_params p, gs_params m, gs_params v,
+                           gs_density_stats stats, const gs_density_opts* opts,
+                           gs_densify_sets_fn alloc, void* user, gs_density_info* info,
+                           void* stream);
+
 /* Opacity reset of the same training: opacity = min(opacity, max_opacity)
  * (in logit form, max_opacity in (0, 1), 0.01 in 3D-GS) and the opacity's
  * Adam moments set to zero.  In place, asynchronous. */
@@ -541,6 +555,16 @@ typedef struct {
 gs_status gs_iso_extract(gs_ctx* ctx, gs_volume volume, float iso, float keep_prob,
                          uint64_t seed, float* xyz, int64_t capacity, int64_t* n_points,
                          void* stream);
+
+/* gs_iso_extract in one call, with the points' array allocated by the caller between the
+ * count and the writing (a call to count and another to write reads the volume twice):
+ * `alloc` is called once, on the calling thread, with n = *n_points > 0 and returns a
+ * device float32 [3][n] array, or NULL to end the call with GS_ERR_NOMEM.  It must not
+ * make another extraction on the same context. */
+typedef float* (*gs_points_fn)(void* user, int64_t n);
+gs_status gs_iso_extract_alloc(gs_ctx* ctx, gs_volume volume, float iso, float keep_prob,
+                               uint64_t seed, gs_points_fn alloc, void* user, int64_t* n_points,
+                               void* stream);
 
 /* Ray-cast target views of the isosurface: per pixel the ray from the camera
  * centre through the pixel centre, clipped to the box, sampled every `step`

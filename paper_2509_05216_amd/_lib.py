@@ -109,6 +109,12 @@ class GsDensityInfo(C.Structure):
                 ("pruned", C.c_int64)]
 
 
+# callbacks that allocate a call's outputs once their sizes are known
+PointsFn = C.CFUNCTYPE(C.c_void_p, C.c_void_p, C.c_int64)
+DensifySetsFn = C.CFUNCTYPE(C.c_int32, C.c_void_p, C.POINTER(GsDensityInfo),
+                            C.POINTER(GsParams), C.POINTER(C.c_void_p))
+
+
 class GsVolume(C.Structure):
     _fields_ = [("values", C.c_void_p), ("nx", C.c_int64), ("ny", C.c_int64), ("nz", C.c_int64),
                 ("lo", C.c_float * 3), ("hi", C.c_float * 3)]
@@ -150,6 +156,11 @@ SIGNATURES = [
     ("gs_opacity_reset", C.c_int, [_P, GsParams, GsParams, GsParams, C.c_double, _P]),
     ("gs_iso_extract", C.c_int, [_P, GsVolume, C.c_float, C.c_float, C.c_uint64, _P, C.c_int64,
                                  C.POINTER(C.c_int64), _P]),
+    ("gs_iso_extract_alloc", C.c_int, [_P, GsVolume, C.c_float, C.c_float, C.c_uint64, PointsFn,
+                                       _P, C.POINTER(C.c_int64), _P]),
+    ("gs_densify_alloc", C.c_int, [_P, GsParams, GsParams, GsParams, GsDensityStats,
+                                   C.POINTER(GsDensityOpts), DensifySetsFn, _P,
+                                   C.POINTER(GsDensityInfo), _P]),
     ("gs_raycast", C.c_int, [_P, GsVolume, C.c_float, C.POINTER(GsCamera), C.c_int32,
                              C.c_float, _PP, _P]),
     ("gs_adam_step", C.c_int, [_P, GsParams, GsParams, GsParams, GsParams,

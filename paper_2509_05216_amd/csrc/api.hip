@@ -1256,13 +1256,15 @@ static bool overlaps(const gs_params& a, const gs_params& b) {
   return false;
 }
 
-gs_status gs_densify(gs_ctx* ctx, gs_params p, gs_params m, gs_params v, gs_density_stats stats,
-                     const gs_density_opts* opts, gs_params p_out, gs_params m_out,
-                     gs_params v_out, int32_t* src_index, gs_density_info* info, void* stream) {
+// Arguments shared by the two densification calls.
+static gs_status densify_args(gs_ctx* ctx, const gs_params& p, const gs_params& m,
+                              const gs_params& v, const gs_density_stats& stats,
+                              const gs_density_opts* opts, const gs_density_info* info) {
   if (ctx == nullptr || opts == nullptr || info == nullptr) {
     set_error("gs_densify: null argument");
     return GS_ERR_INVALID;
   }
+  const gs_density_opts& o = *opts;
   if (!valid_params(p, "gs_densify (p)") || !valid_params(m, "gs_densify (m)") ||
       !valid_params(v, "gs_densify (v)"))
     return GS_ERR_INVALID;
@@ -1280,7 +1282,6 @@ gs_status gs_densify(gs_ctx* ctx, gs_params p, gs_params m, gs_params v, gs_dens
               (long long)p.n);
     return GS_ERR_INVALID;
   }
-  const gs_density_opts& o = *opts;
   if (o.n_split < 1 || o.n_split > 8 || !(o.split_div > 0.0) || !(o.extent > 0.0) ||
       !(o.grad_threshold >= 0.0) || !(o.percent_dense >= 0.0) || !(o.max_world >= 0.0) ||
       !(o.min_opacity >= 0.0) || o.max_screen != o.max_screen) {
@@ -1288,29 +1289,74 @@ gs_status gs_densify(gs_ctx* ctx, gs_params p, gs_params m, gs_params v, gs_dens
               "thresholds >= 0)");
     return GS_ERR_INVALID;
   }
-  const bool write = p_out.means != nullptr;
-  if (write) {
-    if (!valid_params(p_out, "gs_densify (p_out)") || !valid_params(m_out, "gs_densify (m_out)") ||
-        !valid_params(v_out, "gs_densify (v_out)"))
-      return GS_ERR_INVALID;
-    if (p_out.sh_degree != p.sh_degree || m_out.sh_degree != p.sh_degree ||
-        v_out.sh_degree != p.sh_degree) {
-      set_error("gs_densify: output SH degree differs from the input's");
-      return GS_ERR_INVALID;
-    }
-    const gs_params ins[3] = {p, m, v}, outs[3] = {p_out, m_out, v_out};
-    for (const gs_params& a : outs)
-      for (const gs_params& b : ins)
-        if (overlaps(a, b)) {
-          set_error("gs_densify: an output array overlaps an input array");
-          return GS_ERR_INVALID;
-        }
+  return GS_OK;
+}
+
+// Whether three sets can take the densified one (their sizes are checked with the counts).
+static bool densify_outs(const gs_params& p, const gs_params& m, const gs_params& v,
+                         const gs_params& p_out, const gs_params& m_out, const gs_params& v_out) {
+  if (!valid_params(p_out, "gs_densify (p_out)") || !valid_params(m_out, "gs_densify (m_out)") ||
+      !valid_params(v_out, "gs_densify (v_out)"))
+    return false;
+  if (p_out.sh_degree != p.sh_degree || m_out.sh_degree != p.sh_degree ||
+      v_out.sh_degree != p.sh_degree) {
+    set_error("gs_densify: output SH degree differs from the input's");
+    return false;
   }
-  gs_status st = set_device(ctx);
+  const gs_params ins[3] = {p, m, v}, outs[3] = {p_out, m_out, v_out};
+  for (const gs_params& a : outs)
+    for (const gs_params& b : ins)
+      if (overlaps(a, b)) {
+        set_error("gs_densify: an output array overlaps an input array");
+        return false;
+      }
+  return true;
+}
+
+gs_status gs_densify(gs_ctx* ctx, gs_params p, gs_params m, gs_params v, gs_density_stats stats,
+                     const gs_density_opts* opts, gs_params p_out, gs_params m_out,
+                     gs_params v_out, int32_t* src_index, gs_density_info* info, void* stream) {
+  gs_status st = densify_args(ctx, p, m, v, stats, opts, info);
   if (st != GS_OK) return st;
-  StageTimer tm(ctx, ST_DENSIFY, (hipStream_t)stream);
-  return densify_run(ctx, p, m, v, stats, o, write ? &p_out : nullptr, write ? &m_out : nullptr,
-                     write ? &v_out : nullptr, src_index, info, (hipStream_t)stream);
+  const bool write = p_out.means != nullptr;
+  if (write && !densify_outs(p, m, v, p_out, m_out, v_out)) return GS_ERR_INVALID;
+  st = set_device(ctx);
+  if (st != GS_OK) return st;
+  const hipStream_t s = (hipStream_t)stream;
+  StageTimer tm(ctx, ST_DENSIFY, s);
+  st = densify_count(ctx, p, stats, *opts, info, s);
+  if (st != GS_OK || !write) return st;
+  return densify_apply(ctx, p, m, v, stats, *opts, p_out, m_out, v_out, src_index, info, s);
+}
+
+gs_status gs_densify_alloc(gs_ctx* ctx, gs_params p, gs_params m, gs_params v,
+                           gs_density_stats stats, const gs_density_opts* opts,
+                           gs_densify_sets_fn alloc, void* user, gs_density_info* info,
+                           void* stream) {
+  gs_status st = densify_args(ctx, p, m, v, stats, opts, info);
+  if (st != GS_OK) return st;
+  if (alloc == nullptr) {
+    set_error("gs_densify_alloc: null argument");
+    return GS_ERR_INVALID;
+  }
+  st = set_device(ctx);
+  if (st != GS_OK) return st;
+  const hipStream_t s = (hipStream_t)stream;
+  StageTimer tm(ctx, ST_DENSIFY, s);
+  st = densify_count(ctx, p, stats, *opts, info, s);
+  if (st != GS_OK) return st;
+  gs_params out[3];
+  std::memset(out, 0, sizeof(out));
+  int32_t* src = nullptr;
+  if (alloc(user, info, out, &src) != 0) {
+    set_error("gs_densify_alloc: no memory for %lld Gaussians", (long long)info->n_out);
+    return GS_ERR_NOMEM;
+  }
+  if (info->n_out == 0) return GS_OK;  // everything pruned: nothing to write
+  if (!densify_outs(p, m, v, out[0], out[1], out[2])) return GS_ERR_INVALID;
+  st = set_device(ctx);  // the caller's code may have changed it
+  if (st != GS_OK) return st;
+  return densify_apply(ctx, p, m, v, stats, *opts, out[0], out[1], out[2], src, info, s);
 }
 
 static bool valid_volume(const gs_volume& v, const char* what) {
@@ -1332,8 +1378,8 @@ static bool valid_volume(const gs_volume& v, const char* what) {
   return true;
 }
 
-gs_status gs_iso_extract(gs_ctx* ctx, gs_volume vol, float iso, float keep_prob, uint64_t seed,
-                         float* xyz, int64_t capacity, int64_t* n_points, void* stream) {
+static gs_status iso_args(gs_ctx* ctx, const gs_volume& vol, float iso, float keep_prob,
+                          const int64_t* n_points) {
   if (ctx == nullptr || n_points == nullptr) {
     set_error("gs_iso_extract: null argument");
     return GS_ERR_INVALID;
@@ -1343,14 +1389,47 @@ gs_status gs_iso_extract(gs_ctx* ctx, gs_volume vol, float iso, float keep_prob,
     set_error("gs_iso_extract: keep_prob %g not in [0, 1] or iso is NaN", (double)keep_prob);
     return GS_ERR_INVALID;
   }
+  return GS_OK;
+}
+
+gs_status gs_iso_extract(gs_ctx* ctx, gs_volume vol, float iso, float keep_prob, uint64_t seed,
+                         float* xyz, int64_t capacity, int64_t* n_points, void* stream) {
+  gs_status st = iso_args(ctx, vol, iso, keep_prob, n_points);
+  if (st != GS_OK) return st;
   if (xyz != nullptr && capacity < 1) {
     set_error("gs_iso_extract: capacity %lld < 1", (long long)capacity);
     return GS_ERR_INVALID;
   }
-  gs_status st = set_device(ctx);
+  st = set_device(ctx);
   if (st != GS_OK) return st;
-  return iso_extract_run(ctx, vol, iso, keep_prob, seed, xyz, capacity, n_points,
-                         (hipStream_t)stream);
+  const hipStream_t s = (hipStream_t)stream;
+  st = iso_count(ctx, vol, iso, keep_prob, seed, n_points, s);
+  if (st != GS_OK || xyz == nullptr) return st;
+  return iso_emit(ctx, vol, iso, keep_prob, seed, xyz, capacity, *n_points, s);
+}
+
+gs_status gs_iso_extract_alloc(gs_ctx* ctx, gs_volume vol, float iso, float keep_prob,
+                               uint64_t seed, gs_points_fn alloc, void* user, int64_t* n_points,
+                               void* stream) {
+  gs_status st = iso_args(ctx, vol, iso, keep_prob, n_points);
+  if (st != GS_OK) return st;
+  if (alloc == nullptr) {
+    set_error("gs_iso_extract_alloc: null argument");
+    return GS_ERR_INVALID;
+  }
+  st = set_device(ctx);
+  if (st != GS_OK) return st;
+  const hipStream_t s = (hipStream_t)stream;
+  st = iso_count(ctx, vol, iso, keep_prob, seed, n_points, s);
+  if (st != GS_OK || *n_points == 0) return st;
+  float* xyz = alloc(user, *n_points);
+  if (xyz == nullptr) {
+    set_error("gs_iso_extract_alloc: no memory for %lld points", (long long)*n_points);
+    return GS_ERR_NOMEM;
+  }
+  st = set_device(ctx);  // the caller's code may have changed it
+  if (st != GS_OK) return st;
+  return iso_emit(ctx, vol, iso, keep_prob, seed, xyz, *n_points, *n_points, s);
 }
 
 gs_status gs_raycast(gs_ctx* ctx, gs_volume vol, float iso, const gs_camera* cams,

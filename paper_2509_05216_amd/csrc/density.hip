@@ -373,19 +373,16 @@ gs_status launch_density_accumulate(const Frame& f, const gs_density_stats& st, 
   return GS_OK;
 }
 
-gs_status densify_run(Ctx* ctx, const gs_params& p, const gs_params& m, const gs_params& v,
-                      const gs_density_stats& st, const gs_density_opts& o, const gs_params* p_out,
-                      const gs_params* m_out, const gs_params* v_out, int32_t* src_index,
-                      gs_density_info* info, hipStream_t s) {
-  const long long n = p.n;
-  const int nb = (int)((n + kDG - 1) / kDG);
+// What decides each Gaussian's fate.
+static DensityCfg density_cfg(const gs_params& p, const gs_density_stats& st,
+                              const gs_density_opts& o) {
   DensityCfg c;
   c.grad = st.grad;
   c.count = st.count;
   c.maxr = st.max_radius;
   c.ls = p.log_scales;
   c.logit = p.opacity_logits;
-  c.n = n;
+  c.n = p.n;
   c.tau = o.grad_threshold;
   c.clone_lim = o.percent_dense * o.extent;
   c.min_op = o.min_opacity;
@@ -393,6 +390,14 @@ gs_status densify_run(Ctx* ctx, const gs_params& p, const gs_params& m, const gs
   c.world_lim = o.max_world * o.extent;
   c.log_div = std::log(o.split_div);
   c.size_on = o.max_screen > 0.0 ? 1 : 0;
+  return c;
+}
+
+gs_status densify_count(Ctx* ctx, const gs_params& p, const gs_density_stats& st,
+                        const gs_density_opts& o, gs_density_info* info, hipStream_t s) {
+  const long long n = p.n;
+  const int nb = (int)((n + kDG - 1) / kDG);
+  const DensityCfg c = density_cfg(p, st, o);
   // block totals [nb], offsets [nb + 1]
   const size_t bytes = sizeof(uint4) * (2 * (size_t)nb + 1);
   gs_status stt = buf_ensure(ctx, ctx->dens_blk, bytes, s);
@@ -417,15 +422,24 @@ gs_status densify_run(Ctx* ctx, const gs_params& p, const gs_params& m, const gs
   info->children = (int64_t)t.z * o.n_split;
   info->n_out = (int64_t)t.x + t.y + info->children;
   info->pruned = n - (int64_t)t.x - t.w;
-  if (p_out == nullptr) return GS_OK;
-  if (p_out->n < info->n_out || m_out->n < info->n_out || v_out->n < info->n_out) {
+  return GS_OK;
+}
+
+gs_status densify_apply(Ctx* ctx, const gs_params& p, const gs_params& m, const gs_params& v,
+                        const gs_density_stats& st, const gs_density_opts& o, const gs_params& p_out,
+                        const gs_params& m_out, const gs_params& v_out, int32_t* src_index,
+                        const gs_density_info* info, hipStream_t s) {
+  const int nb = (int)((p.n + kDG - 1) / kDG);
+  const DensityCfg c = density_cfg(p, st, o);
+  const uint4* off = (const uint4*)ctx->dens_blk.p + nb;
+  if (p_out.n < info->n_out || m_out.n < info->n_out || v_out.n < info->n_out) {
     set_error("gs_densify: output sets hold %lld entries; the densified set has %lld",
-              (long long)p_out->n, (long long)info->n_out);
+              (long long)p_out.n, (long long)info->n_out);
     return GS_ERR_CAPACITY;
   }
-  if (p_out->n != info->n_out || m_out->n != info->n_out || v_out->n != info->n_out) {
+  if (p_out.n != info->n_out || m_out.n != info->n_out || v_out.n != info->n_out) {
     set_error("gs_densify: output sets must hold exactly %lld entries (p_out.n = %lld)",
-              (long long)info->n_out, (long long)p_out->n);
+              (long long)info->n_out, (long long)p_out.n);
     return GS_ERR_INVALID;
   }
   if (nb == 0) return GS_OK;
@@ -433,9 +447,9 @@ gs_status densify_run(Ctx* ctx, const gs_params& p, const gs_params& m, const gs
   a.in[0] = p;
   a.in[1] = m;
   a.in[2] = v;
-  a.out[0] = *p_out;
-  a.out[1] = *m_out;
-  a.out[2] = *v_out;
+  a.out[0] = p_out;
+  a.out[1] = m_out;
+  a.out[2] = v_out;
   a.src = src_index;
   a.off = off;
   a.nb = nb;

@@ -378,18 +378,25 @@ gs_status launch_loss(const LossScratch& ls, const float* const* x, const float*
                       const int* W, const int* H, int nv, float lambda, float* loss_out,
                       float* const* dl, hipStream_t s);
 // iso.hip
-gs_status iso_extract_run(Ctx* ctx, const gs_volume& vol, float iso, float keep_prob,
-                          uint64_t seed, float* xyz, int64_t cap, int64_t* n_kept,
-                          hipStream_t s);
+// The number of points (one synchronisation), then the points, from the offsets that the
+// count left in the context's scratch: the two belong to one call.
+gs_status iso_count(Ctx* ctx, const gs_volume& vol, float iso, float keep_prob, uint64_t seed,
+                    int64_t* n_kept, hipStream_t s);
+gs_status iso_emit(Ctx* ctx, const gs_volume& vol, float iso, float keep_prob, uint64_t seed,
+                   float* xyz, int64_t cap, int64_t n_kept, hipStream_t s);
 gs_status launch_raycast(Ctx* ctx, const gs_volume& vol, float iso, const gs_camera* cams, int nv,
                          float* const* images, double step, hipStream_t s);
 // density.hip
 gs_status launch_density_accumulate(const Frame& f, const gs_density_stats& st, float scale,
                                     hipStream_t s);
-gs_status densify_run(Ctx* ctx, const gs_params& p, const gs_params& m, const gs_params& v,
-                      const gs_density_stats& st, const gs_density_opts& o, const gs_params* p_out,
-                      const gs_params* m_out, const gs_params* v_out, int32_t* src_index,
-                      gs_density_info* info, hipStream_t s);
+// The counts (one synchronisation), then the new set, from the offsets that the count left
+// in the context's scratch: the two belong to one call.
+gs_status densify_count(Ctx* ctx, const gs_params& p, const gs_density_stats& st,
+                        const gs_density_opts& o, gs_density_info* info, hipStream_t s);
+gs_status densify_apply(Ctx* ctx, const gs_params& p, const gs_params& m, const gs_params& v,
+                        const gs_density_stats& st, const gs_density_opts& o, const gs_params& p_out,
+                        const gs_params& m_out, const gs_params& v_out, int32_t* src_index,
+                        const gs_density_info* info, hipStream_t s);
 gs_status launch_opacity_reset(const gs_params& p, const gs_params& m, const gs_params& v,
                                double max_opacity, hipStream_t s);
 // Per-view MSE, PSNR, L1 and SSIM into out[nv][4] (workspace as for launch_loss).

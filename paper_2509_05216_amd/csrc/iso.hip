@@ -803,44 +803,66 @@ bool build_grid(Ctx* ctx, const VolDev& V, CellGrid& G, hipStream_t s) {
 
 }  // namespace
 
-gs_status iso_extract_run(Ctx* ctx, const gs_volume& vol, float iso, float keep_prob,
-                          uint64_t seed, float* xyz, int64_t cap, int64_t* n_kept,
-                          hipStream_t s) {
+// The extraction's scratch: tile offsets and the grand total (64-bit), block offsets, tile
+// totals.
+struct IsoScratch {
+  long long nvert, nb, tiles;
+  size_t bytes;
+  unsigned long long* tile_off;
+  uint32_t *off, *tile_tot;
+  IsoScratch(Ctx* ctx, const gs_volume& vol) {
+    nvert = (long long)vol.nx * vol.ny * vol.nz;
+    nb = (nvert + kIG - 1) / kIG;
+    tiles = (nb + kTile - 1) / kTile;
+    bytes = sizeof(unsigned long long) * (size_t)(tiles + 1) +
+            sizeof(uint32_t) * (size_t)(nb + tiles);
+    place(ctx);
+  }
+  void place(Ctx* ctx) {
+    tile_off = (unsigned long long*)ctx->iso_blk.p;
+    off = (uint32_t*)(tile_off + tiles + 1);
+    tile_tot = off + nb;
+  }
+};
+
+gs_status iso_count(Ctx* ctx, const gs_volume& vol, float iso, float keep_prob, uint64_t seed,
+                    int64_t* n_kept, hipStream_t s) {
   const VolDev V = vol_dev(vol, iso);
-  const long long nvert = (long long)vol.nx * vol.ny * vol.nz;
-  const long long nb = (nvert + kIG - 1) / kIG;
-  KeepRule r{(uint32_t)seed, (uint32_t)(seed >> 32), keep_prob};
-  // tile offsets and the grand total (64-bit), block offsets, tile totals
-  const long long tiles = (nb + kTile - 1) / kTile;
-  const size_t bytes = sizeof(unsigned long long) * (size_t)(tiles + 1) +
-                       sizeof(uint32_t) * (size_t)(nb + tiles);
-  gs_status st = buf_ensure(ctx, ctx->iso_blk, bytes, s);
+  const KeepRule r{(uint32_t)seed, (uint32_t)(seed >> 32), keep_prob};
+  IsoScratch w(ctx, vol);
+  gs_status st = buf_ensure(ctx, ctx->iso_blk, w.bytes, s);
   if (st != GS_OK) return st;
+  w.place(ctx);
   if (ctx->iso_host == nullptr)
     GS_HIP(hipHostMalloc((void**)&ctx->iso_host, sizeof(unsigned long long),
                          hipHostMallocDefault));
-  auto* tile_off = (unsigned long long*)ctx->iso_blk.p;
-  auto* off = (uint32_t*)(tile_off + tiles + 1);
-  auto* tile_tot = off + nb;
-  hipLaunchKernelGGL(k_iso_count, dim3((unsigned)nb), dim3(kIB), 0, s, V, r, nvert, off);
+  hipLaunchKernelGGL(k_iso_count, dim3((unsigned)w.nb), dim3(kIB), 0, s, V, r, w.nvert, w.off);
   GS_LAUNCHED("iso_count");
-  hipLaunchKernelGGL(k_iso_scan_tile, dim3((unsigned)tiles), dim3(1024), 0, s, off, nb, tile_tot);
+  hipLaunchKernelGGL(k_iso_scan_tile, dim3((unsigned)w.tiles), dim3(1024), 0, s, w.off, w.nb,
+                     w.tile_tot);
   GS_LAUNCHED("iso_scan_tile");
-  hipLaunchKernelGGL(k_iso_scan_top, dim3(1), dim3(1024), 0, s, (const uint32_t*)tile_tot,
-                     (int)tiles, tile_off);
+  hipLaunchKernelGGL(k_iso_scan_top, dim3(1), dim3(1024), 0, s, (const uint32_t*)w.tile_tot,
+                     (int)w.tiles, w.tile_off);
   GS_LAUNCHED("iso_scan_top");
-  GS_HIP(hipMemcpyAsync(ctx->iso_host, tile_off + tiles, sizeof(unsigned long long),
+  GS_HIP(hipMemcpyAsync(ctx->iso_host, w.tile_off + w.tiles, sizeof(unsigned long long),
                         hipMemcpyDeviceToHost, s));
   GS_HIP(hipStreamSynchronize(s));
   *n_kept = (int64_t)*ctx->iso_host;
-  if (xyz == nullptr) return GS_OK;
-  if (*n_kept > cap) {
-    set_error("gs_iso_extract: %lld points do not fit the capacity of %lld",
-              (long long)*n_kept, (long long)cap);
+  return GS_OK;
+}
+
+gs_status iso_emit(Ctx* ctx, const gs_volume& vol, float iso, float keep_prob, uint64_t seed,
+                   float* xyz, int64_t cap, int64_t n_kept, hipStream_t s) {
+  if (n_kept > cap) {
+    set_error("gs_iso_extract: %lld points do not fit the capacity of %lld", (long long)n_kept,
+              (long long)cap);
     return GS_ERR_CAPACITY;
   }
-  hipLaunchKernelGGL(k_iso_emit, dim3((unsigned)nb), dim3(kIB), 0, s, V, r, nvert,
-                     (const uint32_t*)off, (const unsigned long long*)tile_off, xyz,
+  const VolDev V = vol_dev(vol, iso);
+  const KeepRule r{(uint32_t)seed, (uint32_t)(seed >> 32), keep_prob};
+  const IsoScratch w(ctx, vol);
+  hipLaunchKernelGGL(k_iso_emit, dim3((unsigned)w.nb), dim3(kIB), 0, s, V, r, w.nvert,
+                     (const uint32_t*)w.off, (const unsigned long long*)w.tile_off, xyz,
                      (long long)cap);
   GS_LAUNCHED("iso_emit");
   return GS_OK;

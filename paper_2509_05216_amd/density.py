@@ -91,22 +91,32 @@ def count(ctx, params, m, v, stats, extent, *, seed=0, stream=None, **opts):
 
 def densify(ctx, params, m, v, stats, extent, *, seed=0, want_src=False, stream=None, **opts):
     """(params, m, v, info[, src_index]) of the densified set."""
-    info = count(ctx, params, m, v, stats, extent, seed=seed, stream=stream, **opts)
-    n_out = info["n_out"]
-    dev = params.means.device
-    po, mo, vo = (_empty(n_out, params.sh_degree, dev) for _ in range(3))
-    src = torch.empty(n_out, dtype=torch.int32, device=dev) if want_src else None
-    if n_out == 0:                      # everything pruned: nothing to write
-        res = (po, mo, vo, info)
-        return res + (src,) if want_src else res
     o = _opts(extent, seed, **opts)
     out = L.GsDensityInfo()
-    L.check(L.lib().gs_densify(ctx.handle, params.abi(), m.abi(), v.abi(), stats.abi(),
-                               C.byref(o), po.abi(), mo.abi(), vo.abi(),
-                               C.c_void_p(src.data_ptr()) if src is not None else None,
-                               C.byref(out), _stream(stream)))
-    res = (po, mo, vo, _info(out))
-    return res + (src,) if want_src else res
+    dev = params.means.device
+    made, failed = [], []
+
+    @L.DensifySetsFn
+    def alloc(_, info, sets, src_index):
+        try:
+            n_out = info[0].n_out
+            made.extend(_empty(n_out, params.sh_degree, dev) for _ in range(3))
+            for k in range(3):
+                sets[k] = made[k].abi()
+            made.append(torch.empty(n_out, dtype=torch.int32, device=dev) if want_src else None)
+            src_index[0] = made[3].data_ptr() if want_src else None
+            return 0
+        except BaseException as e:      # handed on below: it cannot cross the C call
+            failed.append(e)
+            return 1
+
+    st = L.lib().gs_densify_alloc(ctx.handle, params.abi(), m.abi(), v.abi(), stats.abi(),
+                                  C.byref(o), alloc, None, C.byref(out), _stream(stream))
+    if failed:
+        raise failed[0]
+    L.check(st)
+    res = (made[0], made[1], made[2], _info(out))
+    return res + (made[3],) if want_src else res
 
 
 def opacity_reset(ctx, params, m, v, max_opacity=0.01, stream=None):

@@ -33,18 +33,26 @@ class Volume:
 
 def extract(ctx, vol, iso=0.5, keep_prob=1.0, seed=0, stream=None):
     """(3, n) float32 device tensor of the kept crossing points."""
+    made, failed = [], []
+
+    @L.PointsFn
+    def alloc(_, n):
+        try:
+            made.append(torch.empty((3, n), dtype=torch.float32, device=vol.values.device))
+            return made[0].data_ptr()
+        except BaseException as e:      # handed on below: it cannot cross the C call
+            failed.append(e)
+            return None
+
     n = C.c_int64()
-    va = vol.abi()
-    L.check(L.lib().gs_iso_extract(ctx.handle, va, float(iso), float(keep_prob),
-                                   C.c_uint64(seed & 0xFFFFFFFFFFFFFFFF), None, 0, C.byref(n),
-                                   _stream(stream)))
-    cap = max(n.value, 1)
-    out = torch.empty((3, cap), dtype=torch.float32, device=vol.values.device)
-    L.check(L.lib().gs_iso_extract(ctx.handle, va, float(iso), float(keep_prob),
-                                   C.c_uint64(seed & 0xFFFFFFFFFFFFFFFF),
-                                   C.c_void_p(out.data_ptr()), cap, C.byref(n),
-                                   _stream(stream)))
-    return out[:, :n.value]
+    st = L.lib().gs_iso_extract_alloc(ctx.handle, vol.abi(), float(iso), float(keep_prob),
+                                      C.c_uint64(seed & 0xFFFFFFFFFFFFFFFF), alloc, None,
+                                      C.byref(n), _stream(stream))
+    if failed:
+        raise failed[0]
+    L.check(st)
+    return made[0] if made else torch.empty((3, 0), dtype=torch.float32,
+                                            device=vol.values.device)
 
 
 def count(ctx, vol, iso=0.5, keep_prob=1.0, seed=0, stream=None):

@@ -167,3 +167,51 @@ def test_binning_at_sort_sizes(P, ctx, n):
     want = torch.stack([end - count, end], 1) * (count > 0)[:, None]
     assert torch.equal(frame.export("ranges").view(-1, 2).long(), want)
     frame.release()
+
+
+# ---------------------------------------------------------------- outputs sized inside a call
+def test_outputs_allocated_between_count_and_write(P, ctx, monkeypatch):
+    """extract() and densify(), which allocate inside the library's call, against counting
+    and then writing in two calls (equal); an allocation that fails ends the call."""
+    import ctypes as C
+    from paper_2509_05216_amd import _lib as L
+    from paper_2509_05216_amd import density as D
+    from paper_2509_05216_amd import iso
+    null = None
+    V = iso.Volume(torch.tensor(_volume("noise", (17, 12, 9)), device="cuda"))
+    pts = iso.extract(ctx, V, 0.5, 0.6, 9)
+    n = C.c_int64()
+    two = torch.empty((3, iso.count(ctx, V, 0.5, 0.6, 9)), device="cuda")
+    L.check(L.lib().gs_iso_extract(ctx.handle, V.abi(), 0.5, 0.6, 9, C.c_void_p(two.data_ptr()),
+                                   two.shape[1], C.byref(n), null))
+    assert n.value == pts.shape[1] and torch.equal(pts, two)
+    assert iso.extract(ctx, V, 7.0).shape == (3, 0)
+    assert L.lib().gs_iso_extract_alloc(ctx.handle, V.abi(), 0.5, 1.0, 0,
+                                        L.PointsFn(lambda _, k: None), null, C.byref(n),
+                                        null) == -2
+
+    g = torch.Generator("cuda").manual_seed(3)
+    r = lambda *s: torch.rand(s, device="cuda", generator=g)  # noqa: E731
+    p, m, v = (P.Params(r(3, 700), r(3, 700) * 2 - 5, r(4, 700) - 0.5, r(700) * 6 - 4,
+                        r(12, 700), 1) for _ in range(3))
+    st = D.DensityStats(r(700) ** 3 * 2e-3, torch.ones(700, dtype=torch.int32, device="cuda"),
+                        torch.zeros(700, dtype=torch.int32, device="cuda"))
+    po, mo, vo, info, src = D.densify(ctx, p, m, v, st, 2.5, seed=5, want_src=True)
+    k = info["n_out"]
+    assert info["split"] > 0 and info["cloned"] > 0
+    outs = [D._empty(k, 1, "cuda") for _ in range(3)]
+    src2 = torch.empty(k, dtype=torch.int32, device="cuda")
+    out = L.GsDensityInfo()
+    L.check(L.lib().gs_densify(ctx.handle, p.abi(), m.abi(), v.abi(), st.abi(),
+                               C.byref(D._opts(2.5, 5)), *(o.abi() for o in outs),
+                               C.c_void_p(src2.data_ptr()), C.byref(out), null))
+    assert D._info(out) == info and torch.equal(src, src2)
+    for a, b in zip((po, mo, vo), outs):
+        for x, y in zip(a.tensors(), b.tensors()):
+            assert torch.equal(x, y)
+
+    def full(*a, **kw):
+        raise MemoryError("no room")
+    monkeypatch.setattr(D, "_empty", full)
+    with pytest.raises(MemoryError):
+        D.densify(ctx, p, m, v, st, 2.5)
