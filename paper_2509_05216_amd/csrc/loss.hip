@@ -17,6 +17,7 @@
 // produces four consecutive rows of one column from 14 LDS rows.  Loss sums are reduced per block into
 // float64 partials and summed by a final single-block kernel, so the loss
 // value is deterministic.
+#include <algorithm>
 #include <atomic>
 
 #include "internal.h"
@@ -108,22 +109,39 @@ __device__ inline void row14(const float (*tile)[kH], int r, int c0, float (&v)[
   }
 }
 
-// Tile (bx, by) and channel bz of this block.  Workgroups are dispatched to
-// the eight XCDs (each with its own L2) in turn, so consecutive block indices
-// go to different XCDs; the permutation below gives each XCD a contiguous run
-// of tiles instead, so that the halos neighbouring tiles share are read into
-// the same L2.  A bijection (the last total % 8 blocks keep their place), so
+// Views of one launch: blocks [first[k], first[k + 1]) are the tiles of view k, channel by
+// channel.  The views share a launch, so that only its last round of blocks is partly
+// filled (a 1003 x 771 view has 2400 blocks for 768 resident ones), as far as the
+// workspace holds their partials together.
+struct LossViews {
+  int n;
+  uint32_t first[kMaxViews + 1];
+  const float* x[kMaxViews];
+  const float* y[kMaxViews];
+  float* dl[kMaxViews];       // gradient, or null: none
+  float* gmap[kMaxViews];     // partials of the view
+  float scale[kMaxViews];
+  int W[kMaxViews], H[kMaxViews];
+};
+
+// View, tile (bx, by) and channel of this block, and its place in the list of all blocks
+// of the launch.  Workgroups are dispatched to the eight XCDs (each with its own L2) in
+// turn, so consecutive block indices go to different XCDs; the permutation below gives
+// each XCD a contiguous run of tiles instead, so that the halos neighbouring tiles share
+// are read into the same L2.  A bijection (the last total % 8 blocks keep their place), so
 // every tile is done once whatever the dispatch order.
-__device__ inline void xcd_tile(int& bx, int& by, int& bz) {
-  const uint32_t gx = gridDim.x, gxy = gridDim.x * gridDim.y;
-  const uint32_t total = gxy * gridDim.z;
-  const uint32_t L = blockIdx.x + gx * (blockIdx.y + gridDim.y * blockIdx.z);
-  const uint32_t n8 = total / 8;
+__device__ inline uint32_t xcd_tile(const LossViews& lv, int& v, int& bx, int& by, int& ch) {
+  const uint32_t total = gridDim.x, L = blockIdx.x, n8 = total / 8;
   const uint32_t T = L < 8 * n8 ? (L % 8) * n8 + L / 8 : L;
-  bz = (int)(T / gxy);
-  const uint32_t r = T % gxy;
+  v = 0;
+  for (int k = 1; k < lv.n; ++k)
+    if (T >= lv.first[k]) v = k;
+  const uint32_t gx = (uint32_t)(lv.W[v] + kT - 1) / kT, gy = (uint32_t)(lv.H[v] + kT - 1) / kT;
+  const uint32_t t = T - lv.first[v], r = t % (gx * gy);
+  ch = (int)(t / (gx * gy));
   by = (int)(r / gx);
   bx = (int)(r % gx);
+  return T;
 }
 
 // Thread layout of the vertical pass: column c, rows r0 .. r0 + 3.
@@ -154,15 +172,18 @@ __device__ inline void vert_filter(const float (*hq)[kH][kQ], const Win& win, in
 }
 
 // One block per 32 x 32 tile and channel.
-__global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ x,
-                                                  const float* __restrict__ y, int W, int H,
-                                                  Win win, float* __restrict__ gmap,
+// GRAD: also write the partials (the metrics need none).
+template <bool GRAD>
+__global__ __launch_bounds__(256) void k_ssim_fwd(LossViews lv, Win win,
                                                   double* __restrict__ part) {
   __shared__ alignas(16) float sx[kH][kH];
   __shared__ alignas(16) float sy[kH][kH];
   __shared__ alignas(16) float hq[5][kH][kQ];
-  int bx, by, ch;
-  xcd_tile(bx, by, ch);
+  int vw, bx, by, ch;
+  const size_t b = xcd_tile(lv, vw, bx, by, ch);
+  const int W = lv.W[vw], H = lv.H[vw];
+  const float *__restrict__ x = lv.x[vw], *__restrict__ y = lv.y[vw];
+  float* __restrict__ gmap = lv.gmap[vw];
   const size_t plane = (size_t)W * H;
   const int ox = bx * kT - kR, oy = by * kT - kR;
   {
@@ -233,13 +254,12 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ x,
       const float iB1 = __builtin_amdgcn_rcpf(B1), iB2 = __builtin_amdgcn_rcpf(B2);
       const float Pb = iB1 * iB2;
       const float S = (A1 * A2) * Pb;
-      const float g1 = 2.f * (my * (A2 - A1) * Pb + S * mx * (iB2 - iB1));
-      const float g2 = -S * iB2;
-      const float g3 = 2.f * A1 * Pb;
-      const size_t pix = (size_t)gy * W + gx;
-      gmap[(0 * 3 + ch) * plane + pix] = g1;
-      gmap[(1 * 3 + ch) * plane + pix] = g2;
-      gmap[(2 * 3 + ch) * plane + pix] = g3;
+      if constexpr (GRAD) {
+        const size_t pix = (size_t)gy * W + gx;
+        gmap[(0 * 3 + ch) * plane + pix] = 2.f * (my * (A2 - A1) * Pb + S * mx * (iB2 - iB1));
+        gmap[(1 * 3 + ch) * plane + pix] = -S * iB2;
+        gmap[(2 * 3 + ch) * plane + pix] = 2.f * A1 * Pb;
+      }
       l1 += fabs((double)sx[r0 + o + kR][c + kR] - (double)sy[r0 + o + kR][c + kR]);
       ss += (double)S;
     }
@@ -258,21 +278,22 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ x,
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const size_t b = ((size_t)ch * gridDim.y + by) * gridDim.x + bx;
     part[2 * b + 0] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
     part[2 * b + 1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
   }
 }
 
-__global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ x,
-                                                  const float* __restrict__ y, int W, int H,
-                                                  Win win, const float* __restrict__ gmap,
-                                                  float lambda, float scale,
-                                                  float* __restrict__ dl) {
+__global__ __launch_bounds__(256) void k_ssim_bwd(LossViews lv, Win win, float lambda) {
   __shared__ alignas(16) float sg[3][kH][kH];
   __shared__ alignas(16) float hq[3][kH][kQ];
-  int bx, by, ch;
-  xcd_tile(bx, by, ch);
+  int vw, bx, by, ch;
+  xcd_tile(lv, vw, bx, by, ch);
+  float* __restrict__ dl = lv.dl[vw];
+  if (dl == nullptr) return;  // no gradient of this view (the whole block)
+  const int W = lv.W[vw], H = lv.H[vw];
+  const float *__restrict__ x = lv.x[vw], *__restrict__ y = lv.y[vw];
+  const float* __restrict__ gmap = lv.gmap[vw];
+  const float scale = lv.scale[vw];
   const size_t plane = (size_t)W * H;
   const int ox = bx * kT - kR, oy = by * kT - kR;
   {
@@ -431,7 +452,7 @@ void loss_scratch_bytes(const int* W, const int* H, int nv, size_t* gmap_bytes,
     if (plane > max_plane) max_plane = plane;
     total_blocks += (size_t)((W[v] + kT - 1) / kT) * ((H[v] + kT - 1) / kT) * 3;
   }
-  *gmap_bytes = sizeof(float) * 9 * max_plane;
+  *gmap_bytes = sizeof(float) * 9 * max_plane;  // the least: one view at a time
   // block partials (2 each), per-view stage-1 sums (2 each), metric sums (1 each)
   *part_bytes = sizeof(double) * (2 * (total_blocks + kRedBlocks * kMaxViews) +
                                   (size_t)kRedBlocks * kMaxViews);
@@ -443,9 +464,54 @@ gs_status loss_reserve(Ctx* ctx, LossScratch& ls, const int* W, const int* H, in
     GS_HIP(hipEventCreateWithFlags(&ls.last_use, hipEventDisableTiming));
   size_t gb = 0, pb = 0;
   loss_scratch_bytes(W, H, nv, &gb, &pb);
-  gs_status st = buf_ensure(ctx, ls.gmap, gb, s, ls.last_use);
+  // room for several small views at once (up to 2^22 pixels together), if there is any
+  size_t pix = 0;
+  for (int v = 0; v < nv; ++v) pix += (size_t)W[v] * H[v];
+  const size_t want = sizeof(float) * 9 * std::min(pix, (size_t)1 << 22);
+  gs_status st = buf_ensure(ctx, ls.gmap, std::max(gb, want), s, ls.last_use);
+  if (st != GS_OK && want > gb) st = buf_ensure(ctx, ls.gmap, gb, s, ls.last_use);
   if (st != GS_OK) return st;
   return buf_ensure(ctx, ls.part, pb, s, ls.last_use);
+}
+
+// Launches `go` on runs of consecutive views that fit the workspace together (grad: their
+// partials; without gradients all views at once).  Views that share an output, or read
+// what another writes, go one after the other.
+template <class F>
+static gs_status loss_groups(const LossScratch& ls, const float* const* x, const float* const* y,
+                             const int* W, const int* H, int nv, float* const* dl, bool grad,
+                             F go) {
+  const size_t cap = ls.gmap.cap / (sizeof(float) * 9);
+  for (int v0 = 0, v1; v0 < nv; v0 = v1) {
+    LossViews lv;
+    lv.n = 0;
+    lv.first[0] = 0;
+    size_t used = 0;
+    for (v1 = v0; v1 < nv; ++v1) {
+      const size_t plane = (size_t)W[v1] * H[v1];
+      if (v1 > v0 && grad && used + plane > cap) break;
+      float* d = grad && dl != nullptr ? dl[v1] : nullptr;
+      bool apart = false;
+      for (int k = 0; k < lv.n; ++k)
+        apart |= (d != nullptr && (d == lv.dl[k] || d == lv.x[k] || d == lv.y[k])) ||
+                 (lv.dl[k] != nullptr && (lv.dl[k] == x[v1] || lv.dl[k] == y[v1]));
+      if (apart) break;
+      const int k = lv.n++;
+      lv.x[k] = x[v1];
+      lv.y[k] = y[v1];
+      lv.dl[k] = d;
+      lv.gmap[k] = (float*)ls.gmap.p + 9 * used;
+      lv.scale[k] = (float)(1.0 / (3.0 * (double)W[v1] * H[v1] * nv));
+      lv.W[k] = W[v1];
+      lv.H[k] = H[v1];
+      lv.first[k + 1] =
+          lv.first[k] + (uint32_t)((W[v1] + kT - 1) / kT) * (uint32_t)((H[v1] + kT - 1) / kT) * 3u;
+      used += plane;
+    }
+    const gs_status st = go(lv, v0);
+    if (st != GS_OK) return st;
+  }
+  return GS_OK;
 }
 
 gs_status launch_loss(const LossScratch& ls, const float* const* x, const float* const* y,
@@ -482,18 +548,24 @@ gs_status launch_loss(const LossScratch& ls, const float* const* x, const float*
     }
   }
   double* part2 = (double*)ls.part.p + 2 * total_blocks;
-  for (int v = 0; v < nv; ++v) {
-    const dim3 grid((W[v] + kT - 1) / kT, (H[v] + kT - 1) / kT, 3);
-    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, s, x[v], y[v], W[v], H[v], win,
-                       (float*)ls.gmap.p, (double*)ls.part.p + 2 * lr.off[v]);
-    GS_LAUNCHED("ssim_fwd");
-    if (dl != nullptr && dl[v] != nullptr) {
-      const float scale = (float)(1.0 / (3.0 * (double)W[v] * H[v] * nv));
-      hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(256), 0, s, x[v], y[v], W[v], H[v], win,
-                         (const float*)ls.gmap.p, lambda, scale, dl[v]);
-      GS_LAUNCHED("ssim_bwd");
-    }
-  }
+  bool grad = false;
+  for (int v = 0; dl != nullptr && v < nv; ++v) grad |= dl[v] != nullptr;
+  const gs_status st =
+      loss_groups(ls, x, y, W, H, nv, dl, grad, [&](const LossViews& lv, int v0) -> gs_status {
+        const dim3 grid(lv.first[lv.n]);
+        double* part = (double*)ls.part.p + 2 * lr.off[v0];
+        if (!grad) {
+          hipLaunchKernelGGL(k_ssim_fwd<false>, grid, dim3(256), 0, s, lv, win, part);
+          GS_LAUNCHED("ssim_fwd");
+          return GS_OK;
+        }
+        hipLaunchKernelGGL(k_ssim_fwd<true>, grid, dim3(256), 0, s, lv, win, part);
+        GS_LAUNCHED("ssim_fwd");
+        hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(256), 0, s, lv, win, lambda);
+        GS_LAUNCHED("ssim_bwd");
+        return GS_OK;
+      });
+  if (st != GS_OK) return st;
   if (loss_out != nullptr) {
     hipLaunchKernelGGL(k_loss_partial, dim3(kRedBlocks, nv), dim3(256), 0, s,
                        (const double*)ls.part.p, lr, part2);
@@ -608,12 +680,14 @@ gs_status launch_metrics(const LossScratch& ls, const float* const* x, const flo
   double* part = (double*)ls.part.p;
   double* part2 = part + 2 * total_blocks;
   double* part3 = part2 + 2 * (size_t)kRedBlocks * kMaxViews;
-  for (int v = 0; v < nv; ++v) {
-    const dim3 grid((W[v] + kT - 1) / kT, (H[v] + kT - 1) / kT, 3);
-    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, s, x[v], y[v], W[v], H[v], win,
-                       (float*)ls.gmap.p, part + 2 * lr.off[v]);
-    GS_LAUNCHED("ssim_fwd");
-  }
+  const gs_status st = loss_groups(
+      ls, x, y, W, H, nv, nullptr, false, [&](const LossViews& lv, int v0) -> gs_status {
+        hipLaunchKernelGGL(k_ssim_fwd<false>, dim3(lv.first[lv.n]), dim3(256), 0, s, lv, win,
+                           part + 2 * lr.off[v0]);
+        GS_LAUNCHED("ssim_fwd");
+        return GS_OK;
+      });
+  if (st != GS_OK) return st;
   hipLaunchKernelGGL(k_loss_partial, dim3(kRedBlocks, nv), dim3(256), 0, s, (const double*)part,
                      lr, part2);
   GS_LAUNCHED("loss_partial");
