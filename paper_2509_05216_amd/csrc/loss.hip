@@ -4,8 +4,7 @@
 // SSIM uses an 11 x 11 Gaussian window (sigma 1.5, separable, weights summing
 // to one), C1 = 0.01^2, C2 = 0.03^2, zero padding, averaged over pixels and
 // channels.  Two LDS-tiled passes per view and channel (32 x 32 output pixels
-// per 256-thread block, a 42 x 42 halo tile): the first forms the five local
-// moments by separable filtering and writes, per pixel, the partials
+// at a time, in 42 x 42 windows): the first forms the five local moments by separable filtering and writes, per pixel, the partials
 // g1 = dS/dmu_x, g2 = dS/dE[x^2] and g3 = dS/dE[xy]; the second filters those
 // maps (the window is symmetric, so the zero-padded correlation is its own
 // adjoint) and combines them with the L1 term:
@@ -29,10 +28,10 @@ constexpr int kT = 32;           // output tile side
 constexpr int kR = 5;            // window radius
 constexpr int kN = 2 * kR + 1;   // taps
 constexpr int kH = kT + 2 * kR;  // 42: halo tile side (LDS rows of 168 bytes, 8-byte aligned)
-constexpr int kQ = kT + 4;       // 36: LDS row of the horizontal pass (16-byte aligned)
+constexpr int kC = 2 * kR;       // 10: filtered rows that a tile shares with the one below
 constexpr int kRows = 4;         // output rows per thread in the vertical pass
 constexpr int kGroups = kT / 4;  // four-wide output groups per row in the horizontal pass
-constexpr int kHTasks = kH * kGroups;  // 336 horizontal tasks (halo row, group)
+static_assert(kT * kGroups == 256, "one horizontal task per thread and tile");
 constexpr float kC1 = 0.01f * 0.01f;
 constexpr float kC2 = 0.03f * 0.03f;
 
@@ -40,11 +39,9 @@ struct Win {
   float w[kN];
 };
 
-// Halo tiles are loaded by rows: wave w takes rows w, w + 4, ..., lane l
-// column l (lanes 42-63 load a valid clamped address and store nothing), so
-// the column clamp is a per-lane constant and the row clamp a scalar.
-constexpr int kHaloRows = (kH + 3) / 4;  // 11 rows per wave
-
+// Rows are loaded by waves: wave w takes rows w, w + 4, ..., lane l column l (lanes 42-63
+// load a valid clamped address and store nothing), so the column clamp is a per-lane
+// constant and the row clamp a scalar.
 struct HaloCols {
   uint32_t gxc;  // clamped image column of this lane
   bool inx;      // lane < 42 and its column inside the image
@@ -56,15 +53,15 @@ __device__ inline HaloCols halo_cols(int ox, int W) {
   return {(uint32_t)min(max(gx, 0), W - 1), lane < kH && gx >= 0 && gx < W};
 }
 
-// This thread's share of a halo tile of NI image planes (top-left halo pixel
-// row oy), into registers; the loads are issued together.
-template <int NI>
-__device__ inline void halo_load(const float* const (&img)[NI], HaloCols hc, int oy, int W, int H,
-                                 float (&v)[NI][kHaloRows]) {
+// This thread's share of 4 K rows of NI image planes from row oy on, into registers; the
+// loads are issued together, and waited for where rows_store uses them.
+template <int NI, int K>
+__device__ inline void rows_load(const float* const (&img)[NI], HaloCols hc, int oy, int W, int H,
+                                 float (&v)[NI][K]) {
   // wave-uniform (scalar) row arithmetic; per lane only the column offset
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
 #pragma unroll
-  for (int k = 0; k < kHaloRows; ++k) {
+  for (int k = 0; k < K; ++k) {
     const int gy = min(max(oy + wave + 4 * k, 0), H - 1);
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -72,27 +69,22 @@ __device__ inline void halo_load(const float* const (&img)[NI], HaloCols hc, int
       v[i][k] = rp[hc.gxc];
     }
   }
-  // keep every load here, ahead of the (predicated) stores, so that their
-  // latencies overlap instead of each store waiting for its own load
-#pragma unroll
-  for (int k = 0; k < kHaloRows; ++k)
-#pragma unroll
-    for (int i = 0; i < NI; ++i) asm volatile("" : "+v"(v[i][k]));
 }
 
-// ... and from registers into LDS tiles, zero outside the image.
-template <int NI>
-__device__ inline void halo_store(float (*const (&tile)[NI])[kH], const float (&v)[NI][kHaloRows],
-                                  HaloCols hc, int oy, int H) {
+// ... and from registers into rows of LDS tiles, zero outside the image (of the rows only
+// the first R).
+template <int NI, int K, int R>
+__device__ inline void rows_store(float (*const (&tile)[NI])[kH], int row,
+                                  const float (&v)[NI][K], HaloCols hc, int oy, int H) {
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
   const int lane = (int)(threadIdx.x % 64);
 #pragma unroll
-  for (int k = 0; k < kHaloRows; ++k) {
+  for (int k = 0; k < K; ++k) {
     const int r = wave + 4 * k;
     const bool in = hc.inx && oy + r >= 0 && oy + r < H;
-    if (lane < kH && r < kH) {
+    if (lane < kH && r < R) {
 #pragma unroll
-      for (int i = 0; i < NI; ++i) tile[i][r][lane] = in ? v[i][k] : 0.f;
+      for (int i = 0; i < NI; ++i) tile[i][row + r][lane] = in ? v[i][k] : 0.f;
     }
   }
 }
@@ -109,13 +101,13 @@ __device__ inline void row14(const float (*tile)[kH], int r, int c0, float (&v)[
   }
 }
 
-// Views of one launch: blocks [first[k], first[k + 1]) are the tiles of view k, channel by
-// channel.  The views share a launch, so that only its last round of blocks is partly
-// filled (a 1003 x 771 view has 2400 blocks for 768 resident ones), as far as the
-// workspace holds their partials together.
+// Views of one launch: blocks [first[k], first[k + 1]) are the strips of view k, channel by
+// channel: a block takes `len` tiles below each other.  The views share a launch as far as
+// the workspace holds their partials together.
 struct LossViews {
-  int n;
+  int n, len;
   uint32_t first[kMaxViews + 1];
+  uint32_t tile0[kMaxViews];  // place of the view's first tile in the list of all tiles
   const float* x[kMaxViews];
   const float* y[kMaxViews];
   float* dl[kMaxViews];       // gradient, or null: none
@@ -124,24 +116,35 @@ struct LossViews {
   int W[kMaxViews], H[kMaxViews];
 };
 
-// View, tile (bx, by) and channel of this block, and its place in the list of all blocks
-// of the launch.  Workgroups are dispatched to the eight XCDs (each with its own L2) in
-// turn, so consecutive block indices go to different XCDs; the permutation below gives
-// each XCD a contiguous run of tiles instead, so that the halos neighbouring tiles share
-// are read into the same L2.  A bijection (the last total % 8 blocks keep their place), so
-// every tile is done once whatever the dispatch order.
-__device__ inline uint32_t xcd_tile(const LossViews& lv, int& v, int& bx, int& by, int& ch) {
+// The strip of this block: view, channel, tile column bx and tile rows [by0, by1).
+// Workgroups are dispatched to the eight XCDs (each with its own L2) in turn, so
+// consecutive block indices go to different XCDs; the permutation below gives each XCD a
+// contiguous run of strips instead, so that the columns neighbouring strips share are read
+// into the same L2.  A bijection (the last total % 8 blocks keep their place), so every
+// strip is done once whatever the dispatch order.
+struct Strip {
+  int v, ch, bx, by0, by1;
+  uint32_t tile;     // list place of tile (bx, by0) of the channel; the next row is gx on
+  uint32_t gx;
+};
+
+__device__ inline Strip strip_of(const LossViews& lv) {
   const uint32_t total = gridDim.x, L = blockIdx.x, n8 = total / 8;
   const uint32_t T = L < 8 * n8 ? (L % 8) * n8 + L / 8 : L;
-  v = 0;
+  Strip st;
+  st.v = 0;
   for (int k = 1; k < lv.n; ++k)
-    if (T >= lv.first[k]) v = k;
-  const uint32_t gx = (uint32_t)(lv.W[v] + kT - 1) / kT, gy = (uint32_t)(lv.H[v] + kT - 1) / kT;
-  const uint32_t t = T - lv.first[v], r = t % (gx * gy);
-  ch = (int)(t / (gx * gy));
-  by = (int)(r / gx);
-  bx = (int)(r % gx);
-  return T;
+    if (T >= lv.first[k]) st.v = k;
+  const uint32_t gx = (uint32_t)(lv.W[st.v] + kT - 1) / kT, gy = (uint32_t)(lv.H[st.v] + kT - 1) / kT;
+  const uint32_t segs = (gy + lv.len - 1) / lv.len;
+  const uint32_t t = T - lv.first[st.v], r = t % (gx * segs);
+  st.ch = (int)(t / (gx * segs));
+  st.by0 = (int)(r / gx) * lv.len;
+  st.by1 = min(st.by0 + lv.len, (int)gy);
+  st.bx = (int)(r % gx);
+  st.gx = gx;
+  st.tile = lv.tile0[st.v] + ((uint32_t)st.ch * gy + st.by0) * gx + st.bx;
+  return st;
 }
 
 // Thread layout of the vertical pass: column c, rows r0 .. r0 + 3.
@@ -153,7 +156,7 @@ __device__ inline void vert_slot(int& c, int& r0) {
 // Vertical filtering of NM moment maps held in LDS (hq[m][row][col]) for the
 // four rows of this thread: out[o][m] = sum_i w[i] hq[m][r0 + o + i][c].
 template <int NM>
-__device__ inline void vert_filter(const float (*hq)[kH][kQ], const Win& win, int c, int r0,
+__device__ inline void vert_filter(const float (*hq)[kH][kT], const Win& win, int c, int r0,
                                    float (*out)[NM]) {
 #pragma unroll
   for (int o = 0; o < kRows; ++o)
@@ -171,75 +174,77 @@ __device__ inline void vert_filter(const float (*hq)[kH][kQ], const Win& win, in
   }
 }
 
-// One block per 32 x 32 tile and channel.
-// GRAD: also write the partials (the metrics need none).
+// Four horizontally filtered outputs (columns c0 ..) of 14 inputs, into a row of hq.
+__device__ inline void filter_row(const float (&in)[14], const Win& win, float* out) {
+  float a[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < kN; ++i)
+#pragma unroll
+    for (int o = 0; o < 4; ++o) a[o] = fmaf(win.w[i], in[o + i], a[o]);
+  *reinterpret_cast<float4*>(out) = make_float4(a[0], a[1], a[2], a[3]);
+}
+
+// The five moments of row r of the tiles, filtered, into row q of hq: map by map, with the
+// products x^2, y^2, x y formed once per input (five maps at once hold 90 registers).
+__device__ inline void moments_row(const float (*sx)[kH], const float (*sy)[kH], int r, int c0,
+                                   const Win& win, float (*hq)[kH][kT], int q) {
+  float xv[14], yv[14], p[14];
+  row14(sx, r, c0, xv);
+  row14(sy, r, c0, yv);
+  filter_row(xv, win, &hq[0][q][c0]);
+  __builtin_amdgcn_sched_barrier(0);
+  filter_row(yv, win, &hq[1][q][c0]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < 14; ++k) p[k] = xv[k] * xv[k];
+  filter_row(p, win, &hq[2][q][c0]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < 14; ++k) p[k] = yv[k] * yv[k];
+  filter_row(p, win, &hq[3][q][c0]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < 14; ++k) p[k] = xv[k] * yv[k];
+  filter_row(p, win, &hq[4][q][c0]);
+}
+
+// The last kC rows of NM filtered maps are carried to the top of the next tile's: quad j of
+// this thread's share (threads past the end repeat the last quad), read into registers and,
+// after a barrier, written.
+constexpr int kCarryQuads = kC * kT / 4;  // per map
+
+template <int NM>
+__device__ inline int carry_quad(int j) {
+  return min((int)threadIdx.x + 256 * j, NM * kCarryQuads - 1);
+}
+
+template <int NM>
+__device__ inline float4 carry_read(const float (*hq)[kH][kT], int j) {
+  const int e = carry_quad<NM>(j);
+  return reinterpret_cast<const float4*>(&hq[e / kCarryQuads][kT][0])[e % kCarryQuads];
+}
+
+template <int NM>
+__device__ inline void carry_write(float (*hq)[kH][kT], int j, float4 q) {
+  const int e = carry_quad<NM>(j);
+  reinterpret_cast<float4*>(&hq[e / kCarryQuads][0][0])[e % kCarryQuads] = q;
+}
+
+// SSIM and its partials of the four outputs of this thread (rows by kT + r0 .., column gx)
+// from the five filtered maps; sx, sy at row 0: the tile's first row of centres.  Leaves the
+// wave's sums of |x - y| and of SSIM in red.
 template <bool GRAD>
-__global__ __launch_bounds__(256) void k_ssim_fwd(LossViews lv, Win win,
-                                                  double* __restrict__ part) {
-  __shared__ alignas(16) float sx[kH][kH];
-  __shared__ alignas(16) float sy[kH][kH];
-  __shared__ alignas(16) float hq[5][kH][kQ];
-  int vw, bx, by, ch;
-  const size_t b = xcd_tile(lv, vw, bx, by, ch);
-  const int W = lv.W[vw], H = lv.H[vw];
-  const float *__restrict__ x = lv.x[vw], *__restrict__ y = lv.y[vw];
-  float* __restrict__ gmap = lv.gmap[vw];
-  const size_t plane = (size_t)W * H;
-  const int ox = bx * kT - kR, oy = by * kT - kR;
-  {
-    // every halo load is issued before the first LDS store (clamped addresses,
-    // zero outside the image), so their latencies overlap
-    const HaloCols hc = halo_cols(ox, W);
-    const float* const src[2] = {x + ch * plane, y + ch * plane};
-    float (*const dst[2])[kH] = {sx, sy};
-    float v[2][kHaloRows];
-    halo_load<2>(src, hc, oy, W, H, v);
-    halo_store<2>(dst, v, hc, oy, H);
-  }
-  __syncthreads();
-  // horizontal pass: four outputs of one halo row per task; the products x^2,
-  // y^2, x y are formed once per input, so each tap is five fused multiply-adds
-  for (int t = threadIdx.x; t < kHTasks; t += 256) {
-    const int r = t / kGroups, c0 = (t % kGroups) * 4;
-    float xv[14], yv[14];
-    row14(sx, r, c0, xv);
-    row14(sy, r, c0, yv);
-    float xx[14], yy[14], xy[14];
-#pragma unroll
-    for (int k = 0; k < 14; ++k) {
-      xx[k] = xv[k] * xv[k];
-      yy[k] = yv[k] * yv[k];
-      xy[k] = xv[k] * yv[k];
-    }
-    float a0[4], a1[4], a2[4], a3[4], a4[4];
-#pragma unroll
-    for (int o = 0; o < 4; ++o) a0[o] = a1[o] = a2[o] = a3[o] = a4[o] = 0.f;
-#pragma unroll
-    for (int i = 0; i < kN; ++i)
-#pragma unroll
-      for (int o = 0; o < 4; ++o) {
-        const float w = win.w[i];
-        a0[o] = fmaf(w, xv[o + i], a0[o]);
-        a1[o] = fmaf(w, yv[o + i], a1[o]);
-        a2[o] = fmaf(w, xx[o + i], a2[o]);
-        a3[o] = fmaf(w, yy[o + i], a3[o]);
-        a4[o] = fmaf(w, xy[o + i], a4[o]);
-      }
-    *reinterpret_cast<float4*>(&hq[0][r][c0]) = make_float4(a0[0], a0[1], a0[2], a0[3]);
-    *reinterpret_cast<float4*>(&hq[1][r][c0]) = make_float4(a1[0], a1[1], a1[2], a1[3]);
-    *reinterpret_cast<float4*>(&hq[2][r][c0]) = make_float4(a2[0], a2[1], a2[2], a2[3]);
-    *reinterpret_cast<float4*>(&hq[3][r][c0]) = make_float4(a3[0], a3[1], a3[2], a3[3]);
-    *reinterpret_cast<float4*>(&hq[4][r][c0]) = make_float4(a4[0], a4[1], a4[2], a4[3]);
-  }
-  __syncthreads();
-  int c, r0;
-  vert_slot(c, r0);
+__device__ inline void ssim_tile(const float (*hq)[kH][kT], const float (*sx)[kH],
+                                 const float (*sy)[kH], const Win& win, int by, int c, int r0,
+                                 int gx, int W, int H, float* __restrict__ g1,
+                                 float* __restrict__ g2, float* __restrict__ g3,
+                                 double (&red)[2][4]) {
   float mom[kRows][5];
   vert_filter<5>(hq, win, c, r0, mom);
   double l1 = 0.0, ss = 0.0;
-  const int gx = bx * kT + c;
+  uint32_t pix = (uint32_t)(by * kT + r0) * (uint32_t)W + (uint32_t)gx;
 #pragma unroll
-  for (int o = 0; o < kRows; ++o) {
+  for (int o = 0; o < kRows; ++o, pix += (uint32_t)W) {
     const int gy = by * kT + r0 + o;
     if (gx < W && gy < H) {
       const float mx = mom[o][0], my = mom[o][1];
@@ -255,88 +260,269 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(LossViews lv, Win win,
       const float Pb = iB1 * iB2;
       const float S = (A1 * A2) * Pb;
       if constexpr (GRAD) {
-        const size_t pix = (size_t)gy * W + gx;
-        gmap[(0 * 3 + ch) * plane + pix] = 2.f * (my * (A2 - A1) * Pb + S * mx * (iB2 - iB1));
-        gmap[(1 * 3 + ch) * plane + pix] = -S * iB2;
-        gmap[(2 * 3 + ch) * plane + pix] = 2.f * A1 * Pb;
+        g1[pix] = 2.f * (my * (A2 - A1) * Pb + S * mx * (iB2 - iB1));
+        g2[pix] = -S * iB2;
+        g3[pix] = 2.f * A1 * Pb;
       }
-      l1 += fabs((double)sx[r0 + o + kR][c + kR] - (double)sy[r0 + o + kR][c + kR]);
+      l1 += fabs((double)sx[r0 + o][c + kR] - (double)sy[r0 + o][c + kR]);
       ss += (double)S;
     }
   }
-  // block reduction of the two sums
-  __shared__ double red[2][4];
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) {
     l1 += __shfl_xor(l1, d, 64);
     ss += __shfl_xor(ss, d, 64);
   }
-  const int lane = __lane_id(), wave = threadIdx.x / 64;
-  if (lane == 0) {
-    red[0][wave] = l1;
-    red[1][wave] = ss;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    part[2 * b + 0] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-    part[2 * b + 1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+  if (__lane_id() == 0) {
+    red[0][threadIdx.x / 64] = l1;
+    red[1][threadIdx.x / 64] = ss;
   }
 }
 
-__global__ __launch_bounds__(256) void k_ssim_bwd(LossViews lv, Win win, float lambda) {
-  __shared__ alignas(16) float sg[3][kH][kH];
-  __shared__ alignas(16) float hq[3][kH][kQ];
-  int vw, bx, by, ch;
-  xcd_tile(lv, vw, bx, by, ch);
-  float* __restrict__ dl = lv.dl[vw];
-  if (dl == nullptr) return;  // no gradient of this view (the whole block)
-  const int W = lv.W[vw], H = lv.H[vw];
-  const float *__restrict__ x = lv.x[vw], *__restrict__ y = lv.y[vw];
-  const float* __restrict__ gmap = lv.gmap[vw];
-  const float scale = lv.scale[vw];
+// The block's sums of a tile, by one thread after a barrier.
+__device__ inline void write_part(double* part, uint32_t tile, const double (&red)[2][4]) {
+  part[2 * (size_t)tile + 0] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+  part[2 * (size_t)tile + 1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+}
+
+// STRIP: one block per strip of 32 x 32 tiles below each other and channel.  The ten
+// filtered rows that a tile shares with the one below are carried, so each tile filters its
+// 32 new rows only (one task per thread, where 42 rows take one and a third), and the next
+// tile's rows are loaded while this one's are filtered.  Bound by VALU issue (about 200
+// lane operations per output).  2048^2, three channels: 99 us, with a 42-row window per
+// block 119.  Otherwise one tile per block: few blocks are bound by a block's chain of
+// steps, which the strip's start lengthens.  GRAD: also write the partials (the metrics
+// need none).
+constexpr int kFwdBlocks = 4;  // strips resident per CU, by LDS (39.4 KB)
+template <bool GRAD, bool STRIP>
+__global__ __launch_bounds__(256, STRIP ? kFwdBlocks : 1) void k_ssim_fwd(
+    LossViews lv, Win win, double* __restrict__ part) {
+  // image rows of a tile's window; of a strip's tiles from the sixth on (centres and below)
+  constexpr int kTop = STRIP ? kR : 0, kS = kH - kTop;
+  __shared__ alignas(16) float sx[kS][kH];
+  __shared__ alignas(16) float sy[kS][kH];
+  __shared__ alignas(16) float hq[5][kH][kT];
+  __shared__ double red[2][2][4];
+  const Strip st = strip_of(lv);
+  const int W = lv.W[st.v], H = lv.H[st.v], ch = st.ch;
   const size_t plane = (size_t)W * H;
-  const int ox = bx * kT - kR, oy = by * kT - kR;
+  // partials of this channel (32-bit pixel offsets: a view has at most 2^28 pixels)
+  float* __restrict__ const g1 = lv.gmap[st.v] + (size_t)ch * plane;
+  float* __restrict__ const g2 = g1 + 3 * plane;
+  float* __restrict__ const g3 = g2 + 3 * plane;
+  const float* const src[2] = {lv.x[st.v] + ch * plane, lv.y[st.v] + ch * plane};
+  float (*const dst[2])[kH] = {sx, sy};
+  const HaloCols hc = halo_cols(st.bx * kT - kR, W);
+  const int t = threadIdx.x, hr = t / kGroups, hc0 = (t % kGroups) * 4;
+  const int oy = st.by0 * kT - kR;
+  int c, r0;
+  vert_slot(c, r0);
+  const int gx = st.bx * kT + c;
+  if constexpr (!STRIP) {
+    float u[2][11];
+    rows_load<2, 11>(src, hc, oy, W, H, u);
+    rows_store<2, 11, kH>(dst, 0, u, hc, oy, H);
+    __syncthreads();
+    moments_row(sx, sy, hr, hc0, win, hq, hr);
+    if (t < kC * kGroups) moments_row(sx, sy, kT + hr, hc0, win, hq, kT + hr);
+    __syncthreads();
+    ssim_tile<GRAD>(hq, sx + kR, sy + kR, win, st.by0, c, r0, gx, W, H, g1, g2, g3, red[0]);
+    __syncthreads();
+    if (t == 0) write_part(part, st.tile, red[0]);
+    return;
+  }
+  float v[2][8];
   {
-    const HaloCols hc = halo_cols(ox, W);
-    const float* const src[3] = {gmap + (size_t)(0 * 3 + ch) * plane,
-                                 gmap + (size_t)(1 * 3 + ch) * plane,
-                                 gmap + (size_t)(2 * 3 + ch) * plane};
-    float (*const dst[3])[kH] = {sg[0], sg[1], sg[2]};
-    float v[3][kHaloRows];
-    halo_load<3>(src, hc, oy, W, H, v);
-    halo_store<3>(dst, v, hc, oy, H);
+    // the rows above: the last ten of a tile before the first
+    float u[2][3];
+    rows_load<2, 3>(src, hc, oy, W, H, u);
+    rows_load<2, 8>(src, hc, oy + kC, W, H, v);
+    rows_store<2, 3, kC>(dst, kS - kC, u, hc, oy, H);
+    __syncthreads();
+    if (t < kC * kGroups) moments_row(sx, sy, kS - kC + hr, hc0, win, hq, kT + hr);
+    __syncthreads();
+  }
+  uint32_t b = st.tile;
+  for (int by = st.by0; by < st.by1; ++by, b += st.gx) {
+    const float4 q0 = carry_read<5>(hq, 0), q1 = carry_read<5>(hq, 1);
+    constexpr int kPairs = kR * kH / 2;  // and the last five image rows
+    float2 cs = make_float2(0.f, 0.f);
+    if (t < 2 * kPairs)
+      cs = reinterpret_cast<const float2*>(t < kPairs ? &sx[kS - kR][0] : &sy[kS - kR][0])[t % kPairs];
+    __syncthreads();
+    if (by > st.by0 && t == 0) write_part(part, b - st.gx, red[(by - 1) & 1]);
+    carry_write<5>(hq, 0, q0);
+    carry_write<5>(hq, 1, q1);
+    if (t < 2 * kPairs)
+      reinterpret_cast<float2*>(t < kPairs ? &sx[0][0] : &sy[0][0])[t % kPairs] = cs;
+    rows_store<2, 8, kT>(dst, kR, v, hc, by * kT + kR, H);
+    __syncthreads();
+    if (by + 1 < st.by1) rows_load<2, 8>(src, hc, (by + 1) * kT + kR, W, H, v);
+    moments_row(sx, sy, kR + hr, hc0, win, hq, kC + hr);
+    __syncthreads();
+    ssim_tile<GRAD>(hq, sx, sy, win, by, c, r0, gx, W, H, g1, g2, g3, red[by & 1]);
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < kHTasks; t += 256) {
-    const int r = t / kGroups, c0 = (t % kGroups) * 4;
+  if (t == 0) write_part(part, b - st.gx, red[(st.by1 - 1) & 1]);
+}
+
+// Blocks as in the forward; bound by VALU issue and by the bytes of the partials.
+// 2048^2, three channels: 71 us in strips, with a 42-row window per block 96.
+constexpr int kBwdBlocks = 5;  // strips resident per CU, by LDS (32.3 KB)
+template <bool STRIP>
+__global__ __launch_bounds__(256, STRIP ? kBwdBlocks : 1) void k_ssim_bwd(LossViews lv, Win win,
+                                                                          float lambda) {
+  __shared__ alignas(16) float sg[3][STRIP ? kT : kH][kH];
+  __shared__ alignas(16) float hq[3][kH][kT];
+  const Strip st = strip_of(lv);
+  float* __restrict__ dl = lv.dl[st.v];
+  if (dl == nullptr) return;  // no gradient of this view (the whole block)
+  const int W = lv.W[st.v], H = lv.H[st.v], ch = st.ch;
+  const float* __restrict__ gmap = lv.gmap[st.v];
+  const float scale = lv.scale[st.v];
+  const size_t plane = (size_t)W * H;
+  // this channel's planes (32-bit pixel offsets)
+  const float* __restrict__ const x = lv.x[st.v] + ch * plane;
+  const float* __restrict__ const y = lv.y[st.v] + ch * plane;
+  float* __restrict__ const out = dl + ch * plane;
+  const float* const src[3] = {gmap + (size_t)(0 * 3 + ch) * plane,
+                               gmap + (size_t)(1 * 3 + ch) * plane,
+                               gmap + (size_t)(2 * 3 + ch) * plane};
+  float (*const dst[3])[kH] = {sg[0], sg[1], sg[2]};
+  const HaloCols hc = halo_cols(st.bx * kT - kR, W);
+  const int t = threadIdx.x, hr = t / kGroups, hc0 = (t % kGroups) * 4;
+  const int oy = st.by0 * kT - kR;
+  int c, r0;
+  vert_slot(c, r0);
+  const int gx = st.bx * kT + c;
+  const uint32_t gxc = (uint32_t)min(gx, W - 1);
+  auto maps_row = [&](int r, int q) {
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
       float gv[14];
-      row14(sg[m], r, c0, gv);
-      float a[4] = {0.f, 0.f, 0.f, 0.f};
+      row14(sg[m], r, hc0, gv);
+      filter_row(gv, win, &hq[m][q][hc0]);
+    }
+  };
+  float xv[kRows], yv[kRows];
+  auto load_images = [&](int by) {
 #pragma unroll
-      for (int i = 0; i < kN; ++i)
+    for (int o = 0; o < kRows; ++o) {
+      const uint32_t pix = (uint32_t)min(by * kT + r0 + o, H - 1) * (uint32_t)W + gxc;
+      xv[o] = x[pix];
+      yv[o] = y[pix];
+    }
+  };
+  auto tile = [&](int by) {
+    float f[kRows][3];
+    vert_filter<3>(hq, win, c, r0, f);
 #pragma unroll
-        for (int o = 0; o < 4; ++o) a[o] = fmaf(win.w[i], gv[o + i], a[o]);
-      *reinterpret_cast<float4*>(&hq[m][r][c0]) = make_float4(a[0], a[1], a[2], a[3]);
+    for (int o = 0; o < kRows; ++o) {
+      const int gy = by * kT + r0 + o;
+      if (gx >= W || gy >= H) break;
+      const uint32_t pix = (uint32_t)gy * (uint32_t)W + (uint32_t)gx;
+      const float sgn = (xv[o] > yv[o]) ? 1.f : ((xv[o] < yv[o]) ? -1.f : 0.f);
+      out[pix] = scale *
+                 ((1.f - lambda) * sgn - lambda * (f[o][0] + 2.f * xv[o] * f[o][1] + yv[o] * f[o][2]));
+    }
+  };
+  if constexpr (!STRIP) {
+    float u[3][11];
+    rows_load<3, 11>(src, hc, oy, W, H, u);
+    load_images(st.by0);
+    rows_store<3, 11, kH>(dst, 0, u, hc, oy, H);
+    __syncthreads();
+    maps_row(hr, hr);
+    if (t < kC * kGroups) maps_row(kT + hr, kT + hr);
+    __syncthreads();
+    tile(st.by0);
+    return;
+  }
+  float v[3][8];
+  {
+    float u[3][3];
+    rows_load<3, 3>(src, hc, oy, W, H, u);
+    rows_load<3, 8>(src, hc, oy + kC, W, H, v);
+    rows_store<3, 3, kC>(dst, 0, u, hc, oy, H);
+    __syncthreads();
+    if (t < kC * kGroups) maps_row(hr, kT + hr);
+    __syncthreads();
+  }
+  for (int by = st.by0; by < st.by1; ++by) {
+    const float4 q0 = carry_read<3>(hq, 0);
+    __syncthreads();
+    carry_write<3>(hq, 0, q0);
+    rows_store<3, 8, kT>(dst, 0, v, hc, by * kT + kR, H);
+    __syncthreads();
+    load_images(by);
+    if (by + 1 < st.by1) rows_load<3, 8>(src, hc, (by + 1) * kT + kR, W, H, v);
+    maps_row(hr, kC + hr);
+    __syncthreads();
+    tile(by);
+  }
+}
+
+// Tiles per strip for kernels of which `per_cu` blocks run at once on each of the 256 CUs:
+// the length that costs a CU least, a strip's start taken as 0.7 tiles and k < per_cu
+// blocks as 1 - (1 - k / per_cu)^2 of a full CU's rate (1024^2, three channels, forward:
+// strips of 4 tiles 33 us, of 1 tile 41).
+static int strip_len(const int* W, const int* H, int n, int per_cu) {
+  int longest = 1, best = 1;
+  double least = 1e30;
+  for (int k = 0; k < n; ++k) longest = std::max(longest, (H[k] + kT - 1) / kT);
+  for (int len = 1; len <= std::min(longest, 64); ++len) {
+    size_t blocks = 0;
+    for (int k = 0; k < n; ++k)
+      blocks += (size_t)((W[k] + kT - 1) / kT) * 3 * (((H[k] + kT - 1) / kT + len - 1) / len);
+    const size_t per = (blocks + 255) / 256, rest = per % per_cu;
+    const double idle = 1.0 - (double)rest / per_cu;
+    const double cost =
+        (len + 0.7) * ((double)(per - rest) + (rest != 0 ? rest / (1.0 - idle * idle) : 0.0));
+    if (cost < least) {
+      least = cost;
+      best = len;
     }
   }
-  __syncthreads();
-  int c, r0;
-  vert_slot(c, r0);
-  float f[kRows][3];
-  vert_filter<3>(hq, win, c, r0, f);
-  const int gx = bx * kT + c;
-  if (gx >= W) return;
-#pragma unroll
-  for (int o = 0; o < kRows; ++o) {
-    const int gy = by * kT + r0 + o;
-    if (gy >= H) break;
-    const size_t pix = ch * plane + (size_t)gy * W + gx;
-    const float xv = x[pix], yv = y[pix];
-    const float sgn = (xv > yv) ? 1.f : ((xv < yv) ? -1.f : 0.f);
-    dl[pix] = scale * ((1.f - lambda) * sgn - lambda * (f[o][0] + 2.f * xv * f[o][1] + yv * f[o][2]));
+  return best;
+}
+
+// Up to this many tiles (four blocks per CU) a launch takes them one per block (loss and
+// gradient of 64^2 and of 640 x 480: 20 and 33 us, in strips 27 and 35; of 1024^2, 3072
+// tiles: 62 and 61).
+constexpr uint32_t kSingleTiles = 1024;
+
+inline uint32_t tiles_of(int W, int H) {
+  return (uint32_t)((W + kT - 1) / kT) * (uint32_t)((H + kT - 1) / kT) * 3u;
+}
+
+// Sets the strips of a launch (len: tiles per strip); returns its grid.
+static dim3 set_strips(LossViews& lv, int len) {
+  lv.len = len;
+  lv.first[0] = 0;
+  for (int k = 0; k < lv.n; ++k)
+    lv.first[k + 1] = lv.first[k] + (uint32_t)((lv.W[k] + kT - 1) / kT) * 3u *
+                                        (uint32_t)(((lv.H[k] + kT - 1) / kT + len - 1) / len);
+  return dim3(lv.first[lv.n]);
+}
+
+// The passes over the views of lv: moments (and partials), then, with gradients, theirs.
+template <bool GRAD>
+static gs_status launch_views(LossViews& lv, const Win& win, double* part, float lambda,
+                              hipStream_t s) {
+  uint32_t tiles = 0;
+  for (int k = 0; k < lv.n; ++k) tiles += tiles_of(lv.W[k], lv.H[k]);
+  const bool single = tiles <= kSingleTiles;
+  dim3 grid = set_strips(lv, single ? 1 : strip_len(lv.W, lv.H, lv.n, kFwdBlocks));
+  auto fwd = single ? k_ssim_fwd<GRAD, false> : k_ssim_fwd<GRAD, true>;
+  hipLaunchKernelGGL(fwd, grid, dim3(256), 0, s, lv, win, part);
+  GS_LAUNCHED("ssim_fwd");
+  if constexpr (GRAD) {
+    grid = set_strips(lv, single ? 1 : strip_len(lv.W, lv.H, lv.n, kBwdBlocks));
+    auto bwd = single ? k_ssim_bwd<false> : k_ssim_bwd<true>;
+    hipLaunchKernelGGL(bwd, grid, dim3(256), 0, s, lv, win, lambda);
+    GS_LAUNCHED("ssim_bwd");
   }
+  return GS_OK;
 }
 
 struct LossRed {
@@ -485,7 +671,7 @@ static gs_status loss_groups(const LossScratch& ls, const float* const* x, const
   for (int v0 = 0, v1; v0 < nv; v0 = v1) {
     LossViews lv;
     lv.n = 0;
-    lv.first[0] = 0;
+    uint32_t tiles = 0;
     size_t used = 0;
     for (v1 = v0; v1 < nv; ++v1) {
       const size_t plane = (size_t)W[v1] * H[v1];
@@ -504,8 +690,8 @@ static gs_status loss_groups(const LossScratch& ls, const float* const* x, const
       lv.scale[k] = (float)(1.0 / (3.0 * (double)W[v1] * H[v1] * nv));
       lv.W[k] = W[v1];
       lv.H[k] = H[v1];
-      lv.first[k + 1] =
-          lv.first[k] + (uint32_t)((W[v1] + kT - 1) / kT) * (uint32_t)((H[v1] + kT - 1) / kT) * 3u;
+      lv.tile0[k] = tiles;
+      tiles += tiles_of(W[v1], H[v1]);
       used += plane;
     }
     const gs_status st = go(lv, v0);
@@ -551,19 +737,10 @@ gs_status launch_loss(const LossScratch& ls, const float* const* x, const float*
   bool grad = false;
   for (int v = 0; dl != nullptr && v < nv; ++v) grad |= dl[v] != nullptr;
   const gs_status st =
-      loss_groups(ls, x, y, W, H, nv, dl, grad, [&](const LossViews& lv, int v0) -> gs_status {
-        const dim3 grid(lv.first[lv.n]);
+      loss_groups(ls, x, y, W, H, nv, dl, grad, [&](LossViews& lv, int v0) -> gs_status {
         double* part = (double*)ls.part.p + 2 * lr.off[v0];
-        if (!grad) {
-          hipLaunchKernelGGL(k_ssim_fwd<false>, grid, dim3(256), 0, s, lv, win, part);
-          GS_LAUNCHED("ssim_fwd");
-          return GS_OK;
-        }
-        hipLaunchKernelGGL(k_ssim_fwd<true>, grid, dim3(256), 0, s, lv, win, part);
-        GS_LAUNCHED("ssim_fwd");
-        hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(256), 0, s, lv, win, lambda);
-        GS_LAUNCHED("ssim_bwd");
-        return GS_OK;
+        return grad ? launch_views<true>(lv, win, part, lambda, s)
+                    : launch_views<false>(lv, win, part, lambda, s);
       });
   if (st != GS_OK) return st;
   if (loss_out != nullptr) {
@@ -681,11 +858,8 @@ gs_status launch_metrics(const LossScratch& ls, const float* const* x, const flo
   double* part2 = part + 2 * total_blocks;
   double* part3 = part2 + 2 * (size_t)kRedBlocks * kMaxViews;
   const gs_status st = loss_groups(
-      ls, x, y, W, H, nv, nullptr, false, [&](const LossViews& lv, int v0) -> gs_status {
-        hipLaunchKernelGGL(k_ssim_fwd<false>, dim3(lv.first[lv.n]), dim3(256), 0, s, lv, win,
-                           part + 2 * lr.off[v0]);
-        GS_LAUNCHED("ssim_fwd");
-        return GS_OK;
+      ls, x, y, W, H, nv, nullptr, false, [&](LossViews& lv, int v0) -> gs_status {
+        return launch_views<false>(lv, win, part + 2 * lr.off[v0], 0.f, s);
       });
   if (st != GS_OK) return st;
   hipLaunchKernelGGL(k_loss_partial, dim3(kRedBlocks, nv), dim3(256), 0, s, (const double*)part,

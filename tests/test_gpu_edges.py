@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from tests._parity import rel_l2
 from tests.test_gpu_density import _check_densify
 
 pytestmark = pytest.mark.gpu
@@ -215,3 +216,34 @@ def test_outputs_allocated_between_count_and_write(P, ctx, monkeypatch):
     monkeypatch.setattr(D, "_empty", full)
     with pytest.raises(MemoryError):
         D.densify(ctx, p, m, v, st, 2.5)
+
+
+# ---------------------------------------------------------------- loss
+@pytest.mark.parametrize("sizes", [
+    [(32, 33)],                                  # one tile a block
+    [(1003, 771)],                               # strips, ragged both ways
+    [(33, 11000), (95, 31)],                     # long strips, two views in a launch
+    [(700, 640), (5, 9), (640, 700)],            # views of one and of many strips together
+    [(2200, 2000), (40, 50)]])                   # more than the shared workspace: one by one
+def test_loss_strips_and_groups(P, ctx, sizes):
+    """Loss, gradients and metrics against the float64 oracle (the tolerances of the
+    small-image test)."""
+    from oracle import loss as OL
+    rng = np.random.default_rng(11)
+    ys = [rng.random((3, h, w)).astype(np.float32) for w, h in sizes]
+    xs = [np.clip(y + 0.2 * rng.standard_normal(y.shape), 0, 1).astype(np.float32) for y in ys]
+    cams = [P.camera(np.eye(3), np.zeros(3), 200.0, 200.0, w / 2, h / 2, w, h) for w, h in sizes]
+    gx, gy = ([torch.tensor(t, device="cuda") for t in ts] for ts in (xs, ys))
+    loss, grads = P.loss_grad(ctx, gx, gy, cams)
+    loss2, none = P.loss_grad(ctx, gx, gy, cams, want_grad=False)
+    m = P.core.image_metrics(ctx, gx, gy, cams)
+    torch.cuda.synchronize()
+    assert none is None and torch.equal(loss, loss2)
+    want, dl = OL.batch_loss([x.astype(np.float64) for x in xs],
+                             [y.astype(np.float64) for y in ys], 0.2)
+    assert abs(loss.item() - want) < 1e-5 * max(1, abs(want))
+    for k, (x, y) in enumerate(zip(xs, ys)):
+        assert rel_l2(grads[k].cpu().numpy(), dl[k]) < 1e-4
+        l1 = np.abs(x.astype(np.float64) - y).mean()
+        ssim = OL.ssim(x.astype(np.float64), y.astype(np.float64))
+        assert abs(m[k, 2].item() - l1) < 1e-5 and abs(m[k, 3].item() - np.mean(ssim)) < 1e-5
