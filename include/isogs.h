@@ -88,10 +88,10 @@ typedef struct {
 /* Render options.  tile in {8, 16, 32} (pixels per tile side); lds_depth in
  * {32, 64, 128, 256} (Gaussians staged in LDS per batch; 0 = default 256,
  * clipped to the tile's pixel count for tile 8); bg = background colour;
- * flags: GS_RENDER_PERSISTENT blends all views' tiles with one persistent
- * launch (a resident grid draining a work queue), GS_RENDER_LONGEST_FIRST
- * orders that queue by descending tile list length (to within 1/16 of an
- * octave).  Results do not depend on the flags.  GS_RENDER_RADII also keeps
+ * flags: GS_RENDER_PERSISTENT and GS_RENDER_LONGEST_FIRST ask for schedules of
+ * the tiles that no longer differ (many tiles are always blended in
+ * descending list length, to within 1/16 of an octave); results never
+ * depended on them, and they stay accepted.  GS_RENDER_RADII also keeps
  * every (view, Gaussian)'s integer pixel radius in the frame (0 where the
  * Gaussian touches no tile), which gs_density_accumulate reads. */
 enum { GS_RENDER_PERSISTENT = 1, GS_RENDER_LONGEST_FIRST = 2, GS_RENDER_RADII = 4 };
@@ -579,8 +579,7 @@ gs_status gs_raycast(gs_ctx* ctx, gs_volume volume, float iso, const gs_camera* 
 
 /* -------------------------------------------------------------- autotuner
  * Times forward + backward of the given views for tile sizes {8, 16, 32},
- * LDS depths {32, 64, 128, 256} and the grid or persistent longest-first
- * forms, `reps` timed repetitions each after a warm-up, and returns the
+ * LDS depths {32, 64, 128, 256} and values of the schedule flags, `reps` timed repetitions each after a warm-up, and returns the
  * fastest options in *best.  table (optional, host) receives up to table_cap
  * entries; *table_n their number.  Synchronous. */
 typedef struct {

@@ -154,8 +154,7 @@ size_t Frame::bytes() const {
   size_t s = splat.cap + rect.cap + dkey.cap + dkw[0].cap + dkw[1].cap + sidx[0].cap +
              sidx[1].cap + clampm.cap + offs.cap + tkey[0].cap + tkey[1].cap + tval[0].cap +
              tval[1].cap + ranges.cap + finalT.cap + ncon.cap + acc.cap + ss.hist.cap +
-             ss.partial.cap + ss.total.cap + words.cap + okey[0].cap + okey[1].cap +
-             oval[0].cap + oval[1].cap + radii.cap + gmu.cap;
+             ss.partial.cap + ss.total.cap + words.cap + order.cap + radii.cap + gmu.cap;
   return s;
 }
 
@@ -165,8 +164,7 @@ static void frame_free(Frame* f) {
                    &f->sidx[0], &f->sidx[1], &f->clampm,  &f->offs,       &f->tkey[0],
                    &f->tkey[1], &f->tval[0], &f->tval[1], &f->ranges,     &f->finalT,
                    &f->ncon,    &f->acc,     &f->ss.hist, &f->ss.partial, &f->ss.total,
-                   &f->words,   &f->okey[0], &f->okey[1], &f->oval[0],    &f->oval[1],
-                   &f->radii,   &f->gmu};
+                   &f->words,   &f->order,   &f->radii,   &f->gmu};
   for (DevBuf* b : all) buf_free(c, *b);
   if (f->pinned != nullptr) (void)hipHostFree(f->pinned);
   f->pinned = nullptr;
@@ -281,6 +279,21 @@ static gs_status build_views(Frame& f, const gs_camera* cams, int nv, float* con
   return GS_OK;
 }
 
+// Whether the tiles are blended longest list first: whenever there are more tiles than run
+// at once.  A tile's time follows its list, and a few lists are tens of times the mean:
+// started late, they leave the chip idle behind them.  Forward + backward in us, by tile id
+// and longest first (the order itself takes 6 to 12): one 2048^2 view of 4M Gaussians 2245
+// and 1414, one 1024^2 of 1M 1725 and 1383, six 397 x 301 of 100k (2850 tiles) 695 and 618;
+// 1900 tiles of 800 x 600 531 either way; the 18M step (524k tiles of 8) 21.0 and 20.1 ms
+// in all.  A resident grid that drains a queue in the same order takes longer (the 4M step
+// of four views 7.88 against 7.46 ms): the hardware hands out the workgroups.
+constexpr int kOrderTiles = 2048;
+
+static void choose_order(Frame& f) {
+  f.ordered = f.vt.total_tiles >= kOrderTiles;
+  f.tile_order = nullptr;
+}
+
 // Sizes the frame's buffers for its views; s: the stream of the calling pass.
 static gs_status frame_buffers(Frame& f, hipStream_t s) {
   Ctx* c = f.ctx;
@@ -305,6 +318,7 @@ static gs_status frame_buffers(Frame& f, hipStream_t s) {
   ENS(f.clampm, vn);
   ENS(f.offs, vn * 4);
   ENS(f.ranges, (size_t)f.vt.total_tiles * 8);
+  ENS(f.order, (size_t)(f.vt.total_tiles + kOrderWords) * 4);
   ENS(f.finalT, (size_t)f.total_pix * 4);
   ENS(f.ncon, (size_t)f.total_pix * 4);
   if (f.keep_radii) ENS(f.radii, vn * 4);
@@ -737,14 +751,12 @@ gs_status gs_render_fwd(gs_ctx* ctx, gs_params params, const gs_camera* cams, in
   f.views = n_views;
   f.tile = tile;
   f.depth = depth;
-  f.persistent = (flags & GS_RENDER_PERSISTENT) != 0;
-  f.lpt = f.persistent && (flags & GS_RENDER_LONGEST_FIRST) != 0;
-  f.tile_order = nullptr;
   f.sh_degree = params.sh_degree;
   f.K = 0;
   f.keep_radii = (flags & GS_RENDER_RADII) != 0;
   f.screen_kept = false;
   st = build_views(f, cams, n_views, images, bg);
+  if (st == GS_OK) choose_order(f);
   if (st == GS_OK) st = frame_buffers(f, s);
   if (st != GS_OK) {
     if (fresh) frame_delete(fr);
@@ -858,15 +870,13 @@ gs_status gs_render_fwd_multi(gs_ctx* ctx, const gs_params* params, const gs_cam
   f.views = n_views;
   f.tile = tile;
   f.depth = depth;
-  f.persistent = (flags & GS_RENDER_PERSISTENT) != 0;
-  f.lpt = f.persistent && (flags & GS_RENDER_LONGEST_FIRST) != 0;
-  f.tile_order = nullptr;
   f.sh_degree = -1;
   f.K = 0;
   f.keep_radii = false;
   f.screen_kept = false;
   st = build_views(f, oc, n_views, oi, bg);
   if (st == GS_OK) {
+    choose_order(f);
     uint32_t base = 0;
     int v = 0;
     f.n_groups = ng;
@@ -998,9 +1008,7 @@ gs_status forward_stages(Ctx* ctx, Frame& f, const ParamsDev& pd, hipStream_t s,
   {
     StageTimer tm(ctx, ST_RANGES, s);
     st = launch_ranges(f, n_rec, d_K, s);
-    if (st == GS_OK && f.lpt) st = launch_tile_order(f, s);
-    // persistent work queues start empty
-    if (st == GS_OK && f.persistent) st = launch_fill_u32(f.words.p, 0u, 2, s);
+    if (st == GS_OK && f.ordered) st = launch_tile_order(f, s);
   }
   if (st != GS_OK) return st;
   StageTimer tm(ctx, ST_BLEND_FWD, s);
@@ -1012,10 +1020,6 @@ gs_status backward_stages(Ctx* ctx, Frame& f, const ParamsDev& pd, const GradsDe
                           hipStream_t s) {
   gs_status st = GS_OK;
   if (f.K > 0) {
-    if (f.persistent) {
-      st = launch_fill_u32((uint32_t*)f.words.p + kWordBwdCounter, 0u, 1, s);
-      if (st != GS_OK) return st;
-    }
     StageTimer tm(ctx, ST_BLEND_BWD, s);
     st = launch_blend_bwd(f.vt, f, s);
   }

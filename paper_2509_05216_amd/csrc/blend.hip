@@ -346,44 +346,18 @@ __device__ inline void fwd_tile(Stage<TILE * TILE, DEPTH>& st, const ViewTable& 
 template <int TILE>
 constexpr int kFwdWaves = TILE <= 16 ? 8 : 1;
 
-// One workgroup per tile.
+// One workgroup per tile, the tiles in the given order (null: by id).
 template <int TILE, int DEPTH>
 __global__ __launch_bounds__(TILE* TILE) __attribute__((amdgpu_waves_per_eu(kFwdWaves<TILE>))) void k_blend_fwd(ViewTable vt,
                                                           const uint2* __restrict__ ranges,
                                                           const uint32_t* __restrict__ tval,
                                                           const float4* __restrict__ splat,
                                                           float* __restrict__ finalT,
-                                                          uint32_t* __restrict__ ncon) {
+                                                          uint32_t* __restrict__ ncon,
+                                                          const uint32_t* __restrict__ order) {
   __shared__ Stage<TILE * TILE, DEPTH> st;
-  fwd_tile<TILE, DEPTH>(st, vt, blockIdx.x, ranges, tval, splat, finalT, ncon);
-}
-
-// Next work item of a persistent workgroup: a tile index from the shared
-// counter, mapped through the tile order when one is given; -1 when drained.
-__device__ inline int next_tile(uint32_t* counter, const uint32_t* order, int total,
-                                uint32_t* slot) {
-  __syncthreads();  // the previous item (and its LDS use) is finished
-  if (threadIdx.x == 0) *slot = atomicAdd(counter, 1u);
-  __syncthreads();
-  const uint32_t it = *slot;
-  if (it >= (uint32_t)total) return -1;
-  return order != nullptr ? (int)order[it] : (int)it;
-}
-
-// Persistent form: a grid sized to the device's resident capacity drains the
-// (view, tile) work queue of all views, in the given tile order.
-template <int TILE, int DEPTH>
-__global__ __launch_bounds__(TILE* TILE) __attribute__((amdgpu_waves_per_eu(kFwdWaves<TILE>))) void k_blend_fwd_persistent(
-    ViewTable vt, const uint2* __restrict__ ranges, const uint32_t* __restrict__ tval,
-    const float4* __restrict__ splat, float* __restrict__ finalT, uint32_t* __restrict__ ncon,
-    const uint32_t* __restrict__ order, uint32_t* counter) {
-  __shared__ Stage<TILE * TILE, DEPTH> st;
-  __shared__ uint32_t slot;
-  for (;;) {
-    const int gt = next_tile(counter, order, vt.total_tiles, &slot);
-    if (gt < 0) break;
-    fwd_tile<TILE, DEPTH>(st, vt, gt, ranges, tval, splat, finalT, ncon);
-  }
+  const int gt = order != nullptr ? (int)order[blockIdx.x] : (int)blockIdx.x;
+  fwd_tile<TILE, DEPTH>(st, vt, gt, ranges, tval, splat, finalT, ncon);
 }
 
 // ---------------------------------------------------------------- reduction
@@ -667,51 +641,19 @@ __global__ __launch_bounds__(TILE* TILE) __attribute__((amdgpu_waves_per_eu(6)))
                                                           const float* __restrict__ finalT,
                                                           const uint32_t* __restrict__ ncon,
                                                           float* __restrict__ accG,
-                                                          float* __restrict__ accC) {
+                                                          float* __restrict__ accC,
+                                                          const uint32_t* __restrict__ order) {
   __shared__ BwdSmem<TILE, DEPTH> sm;
-  bwd_tile<TILE, DEPTH>(sm, vt, blockIdx.x, ranges, tval, splat, finalT, ncon, accG, accC);
-}
-
-template <int TILE, int DEPTH>
-__global__ __launch_bounds__(TILE* TILE) __attribute__((amdgpu_waves_per_eu(6))) void k_blend_bwd_persistent(
-    ViewTable vt, const uint2* __restrict__ ranges, const uint32_t* __restrict__ tval,
-    const float4* __restrict__ splat, const float* __restrict__ finalT,
-    const uint32_t* __restrict__ ncon, float* __restrict__ accG, float* __restrict__ accC,
-    const uint32_t* __restrict__ order, uint32_t* counter) {
-  __shared__ BwdSmem<TILE, DEPTH> sm;
-  __shared__ uint32_t slot;
-  for (;;) {
-    const int gt = next_tile(counter, order, vt.total_tiles, &slot);
-    if (gt < 0) break;
-    bwd_tile<TILE, DEPTH>(sm, vt, gt, ranges, tval, splat, finalT, ncon, accG, accC);
-  }
-}
-
-// Workgroups of a persistent kernel that are resident at once on the device.
-template <class K>
-int resident_grid(K kernel, int threads, const Ctx* ctx) {
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess ||
-      per_cu < 1)
-    per_cu = 1;
-  return per_cu * ctx->cu_count;
+  const int gt = order != nullptr ? (int)order[blockIdx.x] : (int)blockIdx.x;
+  bwd_tile<TILE, DEPTH>(sm, vt, gt, ranges, tval, splat, finalT, ncon, accG, accC);
 }
 
 template <int TILE, int DEPTH>
 gs_status fwd_t(const ViewTable& vt, Frame& f, hipStream_t s) {
-  if (f.persistent) {
-    auto kern = k_blend_fwd_persistent<TILE, DEPTH>;
-    const int grid = std::min(resident_grid(kern, TILE * TILE, f.ctx), vt.total_tiles);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(TILE * TILE), 0, s, vt, (const uint2*)f.ranges.p,
-                       (const uint32_t*)f.tval[f.tkey_sel].p, (const float4*)f.splat.p,
-                       (float*)f.finalT.p, (uint32_t*)f.ncon.p, f.tile_order,
-                       (uint32_t*)f.words.p + kWordFwdCounter);
-    GS_LAUNCHED("blend_fwd_persistent");
-    return GS_OK;
-  }
   hipLaunchKernelGGL((k_blend_fwd<TILE, DEPTH>), dim3(vt.total_tiles), dim3(TILE * TILE), 0, s,
                      vt, (const uint2*)f.ranges.p, (const uint32_t*)f.tval[f.tkey_sel].p,
-                     (const float4*)f.splat.p, (float*)f.finalT.p, (uint32_t*)f.ncon.p);
+                     (const float4*)f.splat.p, (float*)f.finalT.p, (uint32_t*)f.ncon.p,
+                     f.tile_order);
   GS_LAUNCHED("blend_fwd");
   return GS_OK;
 }
@@ -720,20 +662,10 @@ template <int TILE, int DEPTH>
 gs_status bwd_t(const ViewTable& vt, Frame& f, hipStream_t s) {
   float* accG = (float*)f.acc.p;
   float* accC = accG + (size_t)f.views * (size_t)f.n * kAccG;
-  if (f.persistent) {
-    auto kern = k_blend_bwd_persistent<TILE, DEPTH>;
-    const int grid = std::min(resident_grid(kern, TILE * TILE, f.ctx), vt.total_tiles);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(TILE * TILE), 0, s, vt, (const uint2*)f.ranges.p,
-                       (const uint32_t*)f.tval[f.tkey_sel].p, (const float4*)f.splat.p,
-                       (const float*)f.finalT.p, (const uint32_t*)f.ncon.p, accG, accC,
-                       f.tile_order, (uint32_t*)f.words.p + kWordBwdCounter);
-    GS_LAUNCHED("blend_bwd_persistent");
-    return GS_OK;
-  }
   hipLaunchKernelGGL((k_blend_bwd<TILE, DEPTH>), dim3(vt.total_tiles), dim3(TILE * TILE), 0, s,
                      vt, (const uint2*)f.ranges.p, (const uint32_t*)f.tval[f.tkey_sel].p,
                      (const float4*)f.splat.p, (const float*)f.finalT.p,
-                     (const uint32_t*)f.ncon.p, accG, accC);
+                     (const uint32_t*)f.ncon.p, accG, accC, f.tile_order);
   GS_LAUNCHED("blend_bwd");
   return GS_OK;
 }

@@ -28,6 +28,7 @@
 namespace isogs {
 
 constexpr int kMaxViews = 16;
+constexpr int kOrderWords = 512;  // tile order: 256 class counts, 256 cursors
 // Screen-gradient accumulators, one record per (view, Gaussian) in each of two
 // arrays held in one allocation: the geometric sums dL/d(mx, my, A, B, C,
 // opacity) + 2 pad floats, then (after all geometric records) the colour sums
@@ -44,8 +45,6 @@ constexpr int kAccStride = kAccG + kAccC;  // floats per (view, Gaussian) in tot
 
 // Frame-owned device words (u32 slots; 64-bit values at even slots).
 enum Word {
-  kWordFwdCounter = 0,  // work counter of the persistent forward blend
-  kWordBwdCounter = 1,  // work counter of the persistent backward blend
   kWordK = 2,           // record count clamped to the capacity (device-count pipelines)
   kWordOverflow = 3,    // set when the records exceed the capacity
   kWordBC = 4,          // two floats: Adam 1/(1 - b1^t), 1/sqrt(1 - b2^t)
@@ -276,11 +275,10 @@ struct Frame {
   bool acc_zeroed = false;
   size_t acc_zero_bytes = 0;  // how much of acc the last fill cleared (acc_zeroed)
   bool settled = false;       // the last call on the frame recorded last_use after its work
-  bool persistent = false;            // blend with persistent work-queue kernels
-  bool lpt = false;                   // persistent queue in longest-list-first tile order
-  const uint32_t* tile_order = nullptr;
+  bool ordered = false;               // tiles are blended longest list first
+  const uint32_t* tile_order = nullptr;  // blending order of the tiles (null: by id)
   DevBuf words;                       // kWordCount device words
-  DevBuf okey[2], oval[2];            // tile-order sort buffers
+  DevBuf order;                       // tile order [tiles], class counts and cursors
   SortScratch ss;
   uint64_t* pinned = nullptr;  // host-pinned readback words (K, visible count)
   // recorded on the call's stream after each call that enqueues work on the
@@ -352,7 +350,7 @@ gs_status launch_emit(const ViewTable& vt, Frame& f, const uint32_t* sidx, const
                       const uint32_t* sry, uint32_t count, uint32_t* overflow, hipStream_t s);
 // Per-tile ranges of n_rec records (d_K: device count bounding n_rec, optional).
 gs_status launch_ranges(Frame& f, uint32_t n_rec, const uint32_t* d_K, hipStream_t s);
-// Tiles in descending list length (ties by tile id) for the persistent queue.
+// Tiles in descending length class of their lists: the order in which they are blended.
 gs_status launch_tile_order(Frame& f, hipStream_t s);
 gs_status launch_fill_u32(void* p, uint32_t value, size_t count, hipStream_t s);
 // After a depth sort of n keys (untouched entries keyed 0xffffffff): the count of

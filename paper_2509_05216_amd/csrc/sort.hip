@@ -461,11 +461,13 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
                                               uint32_t cap, uint32_t* __restrict__ tkey,
                                               uint32_t* __restrict__ tval,
                                               uint32_t* overflow, uint2* __restrict__ ranges,
-                                              uint32_t tiles) {
+                                              uint32_t tiles, uint32_t* __restrict__ order) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = __lane_id();
   // the tiles' ranges start empty (k_ranges, after the sort, writes those with records)
   for (uint32_t t = i; t < tiles; t += gridDim.x * blockDim.x) ranges[t] = make_uint2(0u, 0u);
+  // ... and so do the counts of the tile order
+  for (uint32_t t = i; t < (uint32_t)kOrderWords; t += gridDim.x * blockDim.x) order[tiles + t] = 0u;
   uint32_t need = 0, o = 0, idx = 0, key0 = 0, w = 1, tx = 0;
   if (i < count) {
     idx = sidx[i];
@@ -574,20 +576,62 @@ __global__ void k_clamp_count(const uint64_t* __restrict__ total, uint32_t cap,
   if (t > cap) *overflow = 1u;
 }
 
-// Sort key of a tile for the longest-first work queue: 255 minus a log-scale
-// length class (16 classes per octave of length + 1, lengths up to 2^16 - 1
-// distinguished), so one 8-bit pass orders the tiles by length to within 1/16
-// of an octave, which is all the schedule needs.
-__global__ __launch_bounds__(256) void k_tile_len_keys(const uint2* __restrict__ ranges,
-                                                       uint32_t tiles, uint32_t* __restrict__ key) {
-  const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= tiles) return;
-  const uint2 r = ranges[t];
+// Length class of a tile in the longest-first order: 255 minus a log-scale class of its
+// list's length (16 classes per octave of length + 1, lengths up to 2^16 - 1
+// distinguished): tiles ordered to within 1/16 of an octave are all the schedule needs.
+__device__ inline uint32_t length_class(uint2 r) {
   const uint32_t x = r.y - r.x + 1u;                      // >= 1
   const uint32_t e = 31u - (uint32_t)__clz((int)x);       // floor(log2 x)
   const uint32_t m = ((x << (31u - e)) >> 27) & 15u;      // next four bits after the leading one
   const uint32_t cls = e * 16u + m;
-  key[t] = 255u - (cls < 255u ? cls : 255u);
+  return 255u - (cls < 255u ? cls : 255u);
+}
+
+constexpr int kOrderItems = 4;  // tiles per thread
+
+// Tiles per class (counts, cleared before).
+__global__ __launch_bounds__(256) void k_order_count(const uint2* __restrict__ ranges,
+                                                     uint32_t tiles, uint32_t* __restrict__ counts) {
+  __shared__ uint32_t h[256];
+  h[threadIdx.x] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kOrderItems; ++j) {
+    const uint32_t t = (blockIdx.x * kOrderItems + j) * 256 + threadIdx.x;
+    if (t < tiles) atomicAdd(&h[length_class(ranges[t])], 1u);
+  }
+  __syncthreads();
+  if (h[threadIdx.x] != 0u) atomicAdd(&counts[threadIdx.x], h[threadIdx.x]);
+}
+
+// Tile ids by class; the order within a class is that of the blocks' arrival (no result
+// depends on it).
+__global__ __launch_bounds__(256) void k_order_place(const uint2* __restrict__ ranges,
+                                                     uint32_t tiles,
+                                                     const uint32_t* __restrict__ counts,
+                                                     uint32_t* __restrict__ cursors,
+                                                     uint32_t* __restrict__ order) {
+  __shared__ uint32_t h[256], first[256];
+  __shared__ uint64_t sw[kWaves];
+  h[threadIdx.x] = 0u;
+  __syncthreads();
+  uint32_t cls[kOrderItems], rank[kOrderItems];
+#pragma unroll
+  for (int j = 0; j < kOrderItems; ++j) {
+    const uint32_t t = (blockIdx.x * kOrderItems + j) * 256 + threadIdx.x;
+    cls[j] = t < tiles ? length_class(ranges[t]) : 0u;
+    rank[j] = t < tiles ? atomicAdd(&h[cls[j]], 1u) : 0u;
+  }
+  uint64_t total;
+  const uint32_t before = (uint32_t)block_exclusive_scan(counts[threadIdx.x], sw, total);
+  const uint32_t mine = h[threadIdx.x];  // (the scan's barriers come after the counting)
+  first[threadIdx.x] = before + (mine != 0u ? atomicAdd(&cursors[threadIdx.x], mine) : 0u);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kOrderItems; ++j) {
+    const uint32_t t = (blockIdx.x * kOrderItems + j) * 256 + threadIdx.x;
+    if (t < tiles) order[first[cls[j]] + rank[j]] = t;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_export_keys(const uint32_t* __restrict__ tkey,
@@ -737,7 +781,7 @@ gs_status launch_emit(const ViewTable& vt, Frame& f, const uint32_t* sidx, const
   hipLaunchKernelGGL(k_emit, dim3((count + 255) / 256), dim3(256), 0, s, vt, sidx, srx,
                      sry, (const uint32_t*)f.offs.p, count, cap, (uint32_t*)f.tkey[0].p,
                      (uint32_t*)f.tval[0].p, overflow, (uint2*)f.ranges.p,
-                     (uint32_t)f.vt.total_tiles);
+                     (uint32_t)f.vt.total_tiles, (uint32_t*)f.order.p);
   GS_LAUNCHED("emit");
   return GS_OK;
 }
@@ -776,22 +820,15 @@ gs_status launch_visible_count(const SortScratch& ss, uint32_t n, uint32_t* dst,
 
 gs_status launch_tile_order(Frame& f, hipStream_t s) {
   const uint32_t tiles = (uint32_t)f.vt.total_tiles;
-  for (int k = 0; k < 2; ++k) {
-    gs_status st = buf_ensure(f.ctx, f.okey[k], (size_t)tiles * 4, s, f.last_use);
-    if (st == GS_OK) st = buf_ensure(f.ctx, f.oval[k], (size_t)tiles * 4, s, f.last_use);
-    if (st != GS_OK) return st;
-  }
-  // keys into okey[1]; the sort reads them and ping-pongs okey[0] <-> okey[1]
-  hipLaunchKernelGGL(k_tile_len_keys, dim3((tiles + 255) / 256), dim3(256), 0, s,
-                     (const uint2*)f.ranges.p, tiles, (uint32_t*)f.okey[1].p);
-  GS_LAUNCHED("tile_len_keys");
-  int in_b = 0;
-  gs_status st = sort_pairs_u32(f.ctx, f.ss, (const uint32_t*)f.okey[1].p, nullptr,
-                                (uint32_t*)f.okey[0].p, (uint32_t*)f.oval[0].p,
-                                (uint32_t*)f.okey[1].p, (uint32_t*)f.oval[1].p, tiles, nullptr,
-                                8, &in_b, s);
-  if (st != GS_OK) return st;
-  f.tile_order = (const uint32_t*)f.oval[in_b].p;
+  const uint32_t blocks = (tiles + 256 * kOrderItems - 1) / (256 * kOrderItems);
+  auto* order = (uint32_t*)f.order.p;
+  auto* ranges = (const uint2*)f.ranges.p;
+  hipLaunchKernelGGL(k_order_count, dim3(blocks), dim3(256), 0, s, ranges, tiles, order + tiles);
+  GS_LAUNCHED("order_count");
+  hipLaunchKernelGGL(k_order_place, dim3(blocks), dim3(256), 0, s, ranges, tiles,
+                     (const uint32_t*)(order + tiles), order + tiles + 256, order);
+  GS_LAUNCHED("order_place");
+  f.tile_order = order;
   return GS_OK;
 }
 

@@ -247,3 +247,29 @@ def test_loss_strips_and_groups(P, ctx, sizes):
         l1 = np.abs(x.astype(np.float64) - y).mean()
         ssim = OL.ssim(x.astype(np.float64), y.astype(np.float64))
         assert abs(m[k, 2].item() - l1) < 1e-5 and abs(m[k, 3].item() - np.mean(ssim)) < 1e-5
+
+
+# ---------------------------------------------------------------- tile order
+@pytest.mark.parametrize("views,size,tile", [(9, (256, 240), 16), (3, (250, 179), 8),
+                                             (16, (410, 310), 32)])
+def test_tiles_in_length_order(P, ctx, views, size, tile):
+    """Views rendered together, with at least 2048 tiles blended longest list first, against
+    each view alone, blended in tile order: the same images and gradient sums."""
+    import gsscenes
+    p = P.Params.from_numpy(gsscenes.make_scene("iso1m", n=4000, G=96).params)
+    cams = P.orbit_cameras(views, 2.5, 60.0, *size)
+    assert views * -(-size[0] // tile) * -(-size[1] // tile) >= 2048
+    assert -(-size[0] // tile) * -(-size[1] // tile) < 2048
+    imgs, frame = P.render_fwd(ctx, p, cams, tile=tile, lds_depth=64)
+    g = torch.Generator("cuda").manual_seed(1)
+    dl = [torch.rand(i.shape, device="cuda", generator=g) for i in imgs]
+    got = P.render_bwd(ctx, frame, p, dl)
+    want = p.zeros_like()
+    one = P.Frame()
+    for k, c in enumerate(cams):
+        img, _ = P.render_fwd(ctx, p, [c], tile=tile, lds_depth=64, frame=one)
+        P.render_bwd(ctx, one, p, [dl[k]], want, accumulate=True)
+        assert torch.equal(img[0], imgs[k]), k
+    for a, b in zip(got.tensors(), want.tensors()):
+        assert rel_l2(a.cpu().numpy(), b.cpu().numpy()) < 1e-5
+    frame.release()
