@@ -72,11 +72,19 @@ struct IsoBlock {
   const float* p[3];
   long long base;
   uint32_t left[3];
+  uint32_t i, j, k;  // position of the first vertex
+  float rnx, rny;
 };
 
 __device__ inline IsoBlock iso_block(const VolDev& V, long long nvert, long long chunk) {
   IsoBlock b;
   b.base = chunk * kIG;
+  const long long row = b.base / V.nx;
+  b.i = (uint32_t)(b.base - row * V.nx);
+  b.k = (uint32_t)(row / V.ny);
+  b.j = (uint32_t)(row - (long long)b.k * V.ny);
+  b.rnx = 1.0f / (float)V.nx;
+  b.rny = 1.0f / (float)V.ny;
   const long long st[3] = {0, V.nx, V.nx * V.ny};
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -87,47 +95,69 @@ __device__ inline IsoBlock iso_block(const VolDev& V, long long nvert, long long
   return b;
 }
 
-// Position of vertex vid on the grid (sides up to 2^20).
-__device__ inline void vertex_ijk(const VolDev& V, long long vid, uint32_t& i, uint32_t& j,
-                                  uint32_t& k) {
-  const uint32_t nx = (uint32_t)V.nx, ny = (uint32_t)V.ny;
-  if (V.nx * V.ny * V.nz <= 0xffffffffll) {
-    const uint32_t u = (uint32_t)vid, jk = u / nx;
-    i = u - jk * nx;
-    k = jk / ny;
-    j = jk - k * ny;
-  } else {
-    const long long jk = vid / V.nx;
-    i = (uint32_t)(vid - jk * V.nx);
-    k = (uint32_t)(jk / V.ny);
-    j = (uint32_t)(jk - (long long)k * V.ny);
+// n / d and its remainder for n < 2^22, d < 2^21, from d's float reciprocal: the estimate is
+// off by at most one.
+__device__ inline uint32_t div_small(uint32_t n, uint32_t d, float rd, uint32_t& rem) {
+  uint32_t q = (uint32_t)((float)n * rd);
+  int32_t r = (int32_t)(n - q * d);
+  q = r < 0 ? q - 1 : (r >= (int32_t)d ? q + 1 : q);
+  rem = n - q * d;
+  return q;
+}
+
+// Position of vertex o of the block on the grid (sides up to 2^20, o < 2 kIG).
+__device__ inline void vertex_ijk(const VolDev& V, const IsoBlock& B, uint32_t o, uint32_t& i,
+                                  uint32_t& j, uint32_t& k) {
+  const uint32_t dj = div_small(B.i + o, (uint32_t)V.nx, B.rnx, i);
+  k = B.k + div_small(B.j + dj, (uint32_t)V.ny, B.rny, j);
+}
+
+// The values that the edges of this lane's four consecutive vertices o .. o + 3 of the
+// block need: a (and in a[4] the vertex after the last), b (+y) and c (+z).
+struct EdgeValues {
+  float a[5], b[4], c[4];
+};
+
+__device__ inline void edge_load(const IsoBlock& B, uint32_t o, EdgeValues& v) {
+  if (B.left[2] >= kIG) {  // the whole block and its neighbours are in the volume
+    load4(B.p[0], o, v.a);
+    v.a[4] = B.p[0][o + 4];
+    load4(B.p[1], o, v.b);
+    load4(B.p[2], o, v.c);
+  } else {  // clamped addresses; what lies past the end is masked in edge_flags
+#pragma unroll
+    for (int s = 0; s < 5; ++s) v.a[s] = B.p[0][min(o + s, B.left[0] - 1)];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      v.b[s] = B.p[1][min(o + s, max(B.left[1], 1u) - 1)];
+      v.c[s] = B.p[2][min(o + s, max(B.left[2], 1u) - 1)];
+    }
   }
 }
 
-// The kept crossings among the edges of this lane's four consecutive vertices o .. o + 3
-// of the block: bit 3 s + x for the edge of vertex o + s along axis x (the canonical
-// order); the values they need in a (vertex), b (+y) and c (+z), a[4] the vertex after
-// the last.  Returns 0 for the whole wave, without looking at positions, when no edge of
-// its 256 vertices crosses (nearly all waves: a surface meets few of them).  The sign
-// tests compare the float32 values with iso directly, strictly (exact; NaN never
+// Of the crossings f (see edge_flags), those that the subsample keeps.
+__device__ inline uint32_t kept_flags(const KeepRule& r, const IsoBlock& B, uint32_t o, uint32_t f) {
+  if (r.prob < 1.0f) {
+    const unsigned long long e0 = 3ull * (unsigned long long)(B.base + o);
+    for (uint32_t left = f; left != 0; left &= left - 1) {
+      const int e = __builtin_ctz(left);
+      if (!kept(r, e0 + e)) f &= ~(1u << e);
+    }
+  }
+  return f;
+}
+
+// The kept crossings among those edges: bit 3 s + x for the edge of vertex o + s along axis
+// x (the canonical order).  Returns 0 for the whole wave, without looking at positions,
+// when no edge of its 256 vertices crosses (most waves: a surface meets few of them).  The
+// sign tests compare the float32 values with iso directly, strictly (exact; NaN never
 // crosses); every test is one comparison whose result is a wave mask, and the rest is
 // scalar mask arithmetic.
 __device__ inline uint32_t edge_flags(const VolDev& V, const KeepRule& r, const IsoBlock& B,
-                                      uint32_t o, float (&a)[5], float (&b)[4], float (&c)[4]) {
-  if (B.left[2] >= kIG) {  // the whole block and its neighbours are in the volume
-    load4(B.p[0], o, a);
-    a[4] = B.p[0][o + 4];
-    load4(B.p[1], o, b);
-    load4(B.p[2], o, c);
-  } else {  // clamped addresses; what lies past the end is masked below
-#pragma unroll
-    for (int s = 0; s < 5; ++s) a[s] = B.p[0][min(o + s, B.left[0] - 1)];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      b[s] = B.p[1][min(o + s, max(B.left[1], 1u) - 1)];
-      c[s] = B.p[2][min(o + s, max(B.left[2], 1u) - 1)];
-    }
-  }
+                                      uint32_t o, const EdgeValues& v) {
+  const float(&a)[5] = v.a;
+  const float(&b)[4] = v.b;
+  const float(&c)[4] = v.c;
   unsigned long long lt[5], gt[5], m[4][3], any = 0;
 #pragma unroll
   for (int s = 0; s < 5; ++s) {
@@ -150,10 +180,21 @@ __device__ inline uint32_t edge_flags(const VolDev& V, const KeepRule& r, const 
 #pragma unroll
     for (int x = 0; x < 3; ++x)
       f |= __builtin_amdgcn_inverse_ballot_w64(m[s][x]) ? 1u << (3 * s + x) : 0u;
-  // edges of the grid only: not past the last vertex of a row, column or the volume
+  // edges of the grid only: not past the last vertex of a row, column or the volume; a wave
+  // inside one row knows its position as a whole
+  const uint32_t o0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)o);
+  uint32_t i0, j0, k0;
+  vertex_ijk(V, B, o0, i0, j0, k0);
+  i0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)i0);
+  j0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)j0);
+  if (i0 + 256 <= (uint32_t)V.nx && B.left[2] >= kIG) {
+    if (j0 + 1 == (uint32_t)V.ny) f &= ~0x492u;                          // the y edges
+    if (i0 + 256 == (uint32_t)V.nx && __lane_id() == 63) f &= ~0x200u;  // the last x edge
+    return kept_flags(r, B, o, f);
+  }
   const uint32_t nx = (uint32_t)V.nx, ny = (uint32_t)V.ny;
   uint32_t i, j, k;
-  vertex_ijk(V, B.base + o, i, j, k);
+  vertex_ijk(V, B, o, i, j, k);
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     uint32_t out = i + 1 == nx ? 1u : 0u;
@@ -165,41 +206,47 @@ __device__ inline uint32_t edge_flags(const VolDev& V, const KeepRule& r, const 
     j = wrap ? (j + 1 == ny ? 0u : j + 1) : j;
     i = wrap ? 0u : i + 1;
   }
-  if (r.prob < 1.0f) {
-    const unsigned long long e0 = 3ull * (unsigned long long)(B.base + o);
-    for (uint32_t left = f; left != 0; left &= left - 1) {
-      const int e = __builtin_ctz(left);
-      if (!kept(r, e0 + e)) f &= ~(1u << e);
-    }
-  }
-  return f;
+  return kept_flags(r, B, o, f);
 }
 
 constexpr int kIS = kIV / 4;  // steps of four vertices per thread
 
 // Bound by the read of the volume (4 B per vertex; the neighbours come from L1 and L2):
-// 144 us for 512^3 vertices (3.7 TB/s), where one vertex per lane with 64-bit positions
-// for every vertex and blocks in dispatch order took 435 us.
+// 118 us for 512^3 vertices (4.6 TB/s; with every lane dividing for its position 139, with
+// the loads step by step as well 144, with one vertex per lane, 64-bit positions and blocks
+// in dispatch order 435).  Also writes which of the block's sixteen 256-vertex waves hold crossings (bit 4 q + w).
 __global__ __launch_bounds__(kIB) void k_iso_count(VolDev V, KeepRule r, long long nvert,
-                                                    uint32_t* __restrict__ tot) {
-  __shared__ uint32_t sh[kIW];
+                                                    uint32_t* __restrict__ tot,
+                                                    uint16_t* __restrict__ held) {
+  __shared__ uint32_t sh[kIW], sm[kIW];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const long long chunk = iso_chunk();
   const IsoBlock B = iso_block(V, nvert, chunk);
-  uint32_t n = 0;
+  EdgeValues v[kIS];
+#pragma unroll
+  for (int q = 0; q < kIS; ++q) edge_load(B, 4u * (q * kIB + threadIdx.x), v[q]);
+  uint32_t n = 0, mine = 0;
 #pragma unroll
   for (int q = 0; q < kIS; ++q) {
-    float a[5], b[4], c[4];
-    n += (uint32_t)__popc(edge_flags(V, r, B, 4u * (q * kIB + threadIdx.x), a, b, c));
+    const uint32_t f = edge_flags(V, r, B, 4u * (q * kIB + threadIdx.x), v[q]);
+    n += (uint32_t)__popc(f);
+    mine |= __builtin_amdgcn_ballot_w64(f != 0) != 0 ? 1u << (4 * q + w) : 0u;
   }
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) n += (uint32_t)__shfl_xor((int)n, d, 64);
-  if (lane == 0) sh[w] = n;
+  if (lane == 0) {
+    sh[w] = n;
+    sm[w] = mine;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    uint32_t t = 0;
-    for (int q = 0; q < kIW; ++q) t += sh[q];
+    uint32_t t = 0, m = 0;
+    for (int q = 0; q < kIW; ++q) {
+      t += sh[q];
+      m |= sm[q];
+    }
     tot[chunk] = t;
+    held[chunk] = (uint16_t)m;
   }
 }
 
@@ -268,82 +315,89 @@ __global__ __launch_bounds__(1024) void k_iso_scan_top(const uint32_t* __restric
   if (threadIdx.x == 0) tile_off[tiles] = carry;
 }
 
-// Blocks without a crossing leave at once.  The others form the same flags again; every
-// wave lists its crossings (vertex and axis) in LDS in order and then takes them 64 at a
-// time, so that the float64 divisions run with full waves and the points are stored
-// coalesced: 195 us on a 512^3 volume with 1M crossings (each lane writing the points of
-// its own vertices, axis by axis: 312 us; walking every block as well: 765 us).
+// Inclusive sums over the wave: shifts inside the 16-lane rows, then the rows' last lanes
+// broadcast to the rows after them.
+__device__ inline uint32_t wave_scan(uint32_t x) {
+  auto add = [&](uint32_t y) { x += y; };
+  add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true));   // row_shr:1
+  add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true));   // row_shr:2
+  add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true));   // row_shr:4
+  add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true));   // row_shr:8
+  add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));  // row_bcast:15
+  add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));  // row_bcast:31
+  return x;
+}
+
+// Blocks without a crossing leave at once; of the others only the waves' steps that hold
+// crossings are loaded.  The block lists its crossings (vertex and axis) in LDS in the
+// canonical order and takes them 256 at a time, so that the float64 divisions run with full
+// waves and the points are stored coalesced: 135 us on a 512^3 volume with 1M crossings (a
+// list per wave, every step loaded: 195 us; each lane writing the points of its own
+// vertices, axis by axis: 312; walking every block as well: 765).
 __global__ __launch_bounds__(kIB) void k_iso_emit(VolDev V, KeepRule r, long long nvert,
                                                    const uint32_t* __restrict__ off,
                                                    const unsigned long long* __restrict__ tile_off,
+                                                   const uint16_t* __restrict__ held,
                                                    float* __restrict__ xyz, long long cap) {
   __shared__ uint32_t sh[kIS][kIW];
-  __shared__ uint16_t list[kIW][kIS * 64 * 12];  // 4 x vertex in the block + axis
+  __shared__ uint16_t list[kIG * 3];  // 4 x vertex in the block + axis
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const long long chunk = iso_chunk(), next = chunk + 1;
+  const long long chunk = iso_chunk();
+  const uint32_t steps = held[chunk];
+  if (steps == 0) return;
   const unsigned long long base = tile_off[chunk / kTile] + off[chunk];
-  const unsigned long long end =
-      next < (long long)gridDim.x && next % kTile != 0 ? tile_off[chunk / kTile] + off[next]
-                                                       : tile_off[chunk / kTile + 1];
-  if (base == end) return;
   const IsoBlock B = iso_block(V, nvert, chunk);
-  uint32_t first[kIS + 1];  // this wave's list: start of every step's crossings
-  first[0] = 0;
+  const uint32_t mine = (uint32_t)__builtin_amdgcn_readfirstlane((int)(steps >> w));
+  EdgeValues v[kIS];
+#pragma unroll
+  for (int q = 0; q < kIS; ++q)
+    if ((mine >> (4 * q)) & 1u) edge_load(B, 4u * (q * kIB + threadIdx.x), v[q]);
+  uint32_t f[kIS], at[kIS];  // this lane's crossings, and the wave's before them
 #pragma unroll
   for (int q = 0; q < kIS; ++q) {
-    const uint32_t ov = 4u * (q * kIB + threadIdx.x);
-    float a[5], b[4], c[4];
-    const uint32_t f = edge_flags(V, r, B, ov, a, b, c);
+    f[q] = at[q] = 0;
     uint32_t n = 0;
-    if (__builtin_amdgcn_ballot_w64(f != 0) != 0) {
-      const uint32_t own = (uint32_t)__popc(f);
-      uint32_t inc = own;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = (uint32_t)__shfl_up((int)inc, d, 64);
-        if (lane >= d) inc += y;
-      }
+    if ((mine >> (4 * q)) & 1u) {
+      f[q] = edge_flags(V, r, B, 4u * (q * kIB + threadIdx.x), v[q]);
+      const uint32_t own = (uint32_t)__popc(f[q]);
+      const uint32_t inc = wave_scan(own);
       n = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-      uint32_t at = first[q] + inc - own;
-      for (uint32_t left = f; left != 0; left &= left - 1) {
-        const uint32_t e = (uint32_t)__builtin_ctz(left), s = e / 3;
-        list[w][at++] = (uint16_t)(4 * (ov + s) + (e - 3 * s));
-      }
+      at[q] = inc - own;
     }
-    first[q + 1] = first[q] + n;
     if (lane == 0) sh[q][w] = n;
   }
   __syncthreads();
-  // points of step q precede those of step q + 1; inside a step the waves are in order:
-  // shift[q] takes a position in this wave's list to its place among the block's points
-  uint32_t shift[kIS], before = 0;
+  // crossings of step q precede those of step q + 1; inside a step the waves are in order
+  uint32_t total = 0;
 #pragma unroll
   for (int q = 0; q < kIS; ++q) {
-    uint32_t pre = 0, all = 0;
+    uint32_t to = total + at[q];
 #pragma unroll
     for (int x = 0; x < kIW; ++x) {
-      if (x < w) pre += sh[q][x];
-      all += sh[q][x];
+      const uint32_t n = sh[q][x];
+      to += x < w ? n : 0u;
+      total += n;
     }
-    shift[q] = before + pre - first[q];
-    before += all;
+    const uint32_t ov = 4u * (q * kIB + threadIdx.x);
+    for (uint32_t left = f[q]; left != 0; left &= left - 1) {
+      const uint32_t e = (uint32_t)__builtin_ctz(left), s = e / 3;
+      list[to++] = (uint16_t)(4 * (ov + s) + (e - 3 * s));
+    }
   }
-  for (uint32_t t = lane; t < first[kIS]; t += 64) {
-    const uint32_t code = list[w][t];
+  __syncthreads();
+  for (uint32_t t = threadIdx.x; t < total; t += kIB) {
+    const uint32_t code = list[t];
     const int x = (int)(code & 3u);
     const long long vid = B.base + (code >> 2);
     const float v0 = V.v[vid];
     const float v1 = V.v[vid + (x == 0 ? 1 : (x == 1 ? V.nx : V.nx * V.ny))];
-    uint32_t place = shift[0];
-#pragma unroll
-    for (int q = 1; q < kIS; ++q) place = t >= first[q] ? shift[q] : place;
     uint32_t i, j, k;
-    vertex_ijk(V, vid, i, j, k);
+    vertex_ijk(V, B, code >> 2, i, j, k);
     // t = a / (a - b), a = v0 - iso, b = v1 - iso (both exact in float64)
     const double u = ((double)v0 - (double)V.iso) / ((double)v0 - (double)v1);
     const double px = V.lo[0] + (double)i * V.h[0], py = V.lo[1] + (double)j * V.h[1],
                  pz = V.lo[2] + (double)k * V.h[2];
-    const long long o = (long long)(base + (uint32_t)(place + t));
+    const long long o = (long long)(base + t);
     if (o < cap) {
       xyz[o] = (float)(x == 0 ? px + u * V.h[0] : px);
       xyz[cap + o] = (float)(x == 1 ? py + u * V.h[1] : py);
@@ -804,24 +858,26 @@ bool build_grid(Ctx* ctx, const VolDev& V, CellGrid& G, hipStream_t s) {
 }  // namespace
 
 // The extraction's scratch: tile offsets and the grand total (64-bit), block offsets, tile
-// totals.
+// totals, the waves that hold crossings.
 struct IsoScratch {
   long long nvert, nb, tiles;
   size_t bytes;
   unsigned long long* tile_off;
   uint32_t *off, *tile_tot;
+  uint16_t* held;
   IsoScratch(Ctx* ctx, const gs_volume& vol) {
     nvert = (long long)vol.nx * vol.ny * vol.nz;
     nb = (nvert + kIG - 1) / kIG;
     tiles = (nb + kTile - 1) / kTile;
     bytes = sizeof(unsigned long long) * (size_t)(tiles + 1) +
-            sizeof(uint32_t) * (size_t)(nb + tiles);
+            sizeof(uint32_t) * (size_t)(nb + tiles) + sizeof(uint16_t) * (size_t)nb;
     place(ctx);
   }
   void place(Ctx* ctx) {
     tile_off = (unsigned long long*)ctx->iso_blk.p;
     off = (uint32_t*)(tile_off + tiles + 1);
     tile_tot = off + nb;
+    held = (uint16_t*)(tile_tot + tiles);
   }
 };
 
@@ -836,7 +892,8 @@ gs_status iso_count(Ctx* ctx, const gs_volume& vol, float iso, float keep_prob, 
   if (ctx->iso_host == nullptr)
     GS_HIP(hipHostMalloc((void**)&ctx->iso_host, sizeof(unsigned long long),
                          hipHostMallocDefault));
-  hipLaunchKernelGGL(k_iso_count, dim3((unsigned)w.nb), dim3(kIB), 0, s, V, r, w.nvert, w.off);
+  hipLaunchKernelGGL(k_iso_count, dim3((unsigned)w.nb), dim3(kIB), 0, s, V, r, w.nvert, w.off,
+                     w.held);
   GS_LAUNCHED("iso_count");
   hipLaunchKernelGGL(k_iso_scan_tile, dim3((unsigned)w.tiles), dim3(1024), 0, s, w.off, w.nb,
                      w.tile_tot);
@@ -862,7 +919,8 @@ gs_status iso_emit(Ctx* ctx, const gs_volume& vol, float iso, float keep_prob, u
   const KeepRule r{(uint32_t)seed, (uint32_t)(seed >> 32), keep_prob};
   const IsoScratch w(ctx, vol);
   hipLaunchKernelGGL(k_iso_emit, dim3((unsigned)w.nb), dim3(kIB), 0, s, V, r, w.nvert,
-                     (const uint32_t*)w.off, (const unsigned long long*)w.tile_off, xyz,
+                     (const uint32_t*)w.off, (const unsigned long long*)w.tile_off,
+                     (const uint16_t*)w.held, xyz,
                      (long long)cap);
   GS_LAUNCHED("iso_emit");
   return GS_OK;
