@@ -411,6 +411,7 @@ struct RayView {
   double R[9], o[3];
   double fx, fy, cx, cy;
   int W, H;
+  int side;  // blocks per side of a chunk (see ray_block)
   float* img;
 };
 
@@ -616,6 +617,18 @@ __device__ inline int quick_side(const VolDev& V, const CellGrid& G, double m, c
   return fabsf(f) > 1e-5f * (big + fabsf(V.iso)) ? (f < 0.f ? kBelow : kAbove) : kMixed;
 }
 
+// Place (in blocks of 16 x 16 pixels) of block L of a view.  Workgroups go to the eight XCDs
+// in turn; each XCD takes whole chunks of side x side blocks, so that neighbouring rays'
+// values meet in one L2, and chunks go round the XCDs, so that each has a share of the
+// expensive parts of the image.
+__device__ inline void ray_block(const RayView& c, uint32_t L, int& bx, int& by) {
+  const uint32_t per = (uint32_t)(c.side * c.side), s = L / 8;
+  const uint32_t chunk = (s / per) * 8 + L % 8, in = s % per;
+  const uint32_t cx = (uint32_t)((c.W + 16 * c.side - 1) / (16 * c.side));
+  bx = (int)(chunk % cx) * c.side + (int)(in % c.side);
+  by = (int)(chunk / cx) * c.side + (int)(in / c.side);
+}
+
 // One thread per pixel, a wave an 8 x 8 block of them: neighbouring rays read the same
 // cells and leave the march together (64 x 1 pixels: 4258 us for two 1024^2 views of a
 // 512^3 volume at one sample a cell, 8 x 8: 2640).  QUICK: samples are decided by
@@ -627,11 +640,11 @@ template <bool QUICK>
 __global__ __launch_bounds__(256) void k_raycast(VolDev V, RayViews rv, CellGrid G, double step,
                                                  double hi0, double hi1, double hi2) {
   const RayView& c = rv.v[blockIdx.y];
-  const int tiles_x = (c.W + 15) / 16;
-  if ((int)blockIdx.x >= tiles_x * ((c.H + 15) / 16)) return;
+  int bx, by;
+  ray_block(c, blockIdx.x, bx, by);
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int x = (blockIdx.x % tiles_x) * 16 + (wave % 2) * 8 + lane % 8;
-  const int y = (blockIdx.x / tiles_x) * 16 + (wave / 2) * 8 + lane / 8;
+  const int x = bx * 16 + (wave % 2) * 8 + lane % 8;
+  const int y = by * 16 + (wave / 2) * 8 + lane / 8;
   if (x >= c.W || y >= c.H) return;
   const double dc[3] = {((double)x + 0.5 - c.cx) / c.fx, ((double)y + 0.5 - c.cy) / c.fy, 1.0};
   double d[3];
@@ -948,7 +961,16 @@ gs_status launch_raycast(Ctx* ctx, const gs_volume& vol, float iso, const gs_cam
     r.W = c.width;
     r.H = c.height;
     r.img = images[k];
-    blocks = std::max(blocks, ((c.width + 15) / 16) * ((c.height + 15) / 16));
+    // chunks of up to 8 x 8 blocks, at least 1024 of them (or single blocks): fewer leave the
+    // XCDs unequal (two 1024^2 views: 2 x 2 blocks 508 us, 4 x 4 526, 8 x 8 625, single
+    // blocks 578)
+    r.side = 8;
+    auto chunks = [&] {
+      return ((c.width + 16 * r.side - 1) / (16 * r.side)) *
+             ((c.height + 16 * r.side - 1) / (16 * r.side));
+    };
+    while (r.side > 1 && chunks() < 1024) r.side /= 2;
+    blocks = std::max(blocks, (chunks() + 7) / 8 * 8 * r.side * r.side);
     pix += (long long)c.width * c.height;
   }
   const dim3 grid((unsigned)blocks, (unsigned)nv);
