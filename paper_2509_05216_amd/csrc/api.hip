@@ -1000,7 +1000,8 @@ gs_status forward_stages(Ctx* ctx, Frame& f, const ParamsDev& pd, hipStream_t s,
     StageTimer tm(ctx, ST_TILE_SORT, s);
     st = sort_pairs_u32(ctx, f.ss, (const uint32_t*)f.tkey[0].p, (const uint32_t*)f.tval[0].p,
                         (uint32_t*)f.tkey[1].p, (uint32_t*)f.tval[1].p, (uint32_t*)f.tkey[0].p,
-                        (uint32_t*)f.tval[0].p, n_rec, d_K, f.key_bits, &in_b, s);
+                        (uint32_t*)f.tval[0].p, n_rec, d_K, f.key_bits, &in_b, s, srx,
+                        f.dkw[0].cap / sizeof(uint32_t));  // emitted: the rectangles are free
   }
   if (st != GS_OK) return st;
   f.tkey_sel = (n_rec == 0) ? 0 : (in_b ? 0 : 1);

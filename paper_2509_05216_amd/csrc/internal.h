@@ -230,7 +230,7 @@ gs_status timing_collect(Ctx* c);
 
 // Radix-sort / scan scratch.
 struct SortScratch {
-  DevBuf hist;      // u32[256 * blocks]
+  DevBuf hist;      // u32[256 * (blocks + 1)], 8-bit digits
   DevBuf partial;   // u64[blocks]
   DevBuf total;     // u64[1]
   hipEvent_t prior = nullptr;  // last use of the owning frame (see buf_ensure)
@@ -330,9 +330,11 @@ gs_status launch_init_points(const float* xyz, int64_t n, const gs_init_opts& o,
 // Stable LSD sort of n (key, value) pairs on key bits [0, bits): the first pass
 // reads kin/vin (vin == nullptr: values are the indices 0..n-1) and passes
 // alternate between buffer pairs A and B; *result_in_b tells where the result is.
+// `spare`: memory that is free during the sort, for larger digit tables.
 gs_status sort_pairs_u32(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const uint32_t* vin,
                          uint32_t* kA, uint32_t* vA, uint32_t* kB, uint32_t* vB, uint32_t n,
-                         const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s);
+                         const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s,
+                         uint32_t* spare = nullptr, size_t spare_words = 0);
 // Tile counts of the depth-ordered entries, scanned into record offsets; the
 // entries' rectangles are also written in that order (srx, sry: the two halves)
 // so the emission reads them coalesced.

@@ -10,10 +10,11 @@
 // records gives, at a fraction of the traffic.
 //
 // Radix passes use 8-bit digits, 256 threads (4 waves of 64) and 16 keys per
-// thread per block (4 in small sorts).  Stable ranking inside a block uses wave ballots: for each
-// item slot the lanes holding the same digit are found with 8 ballots, the
-// group's leader bumps a per-wave LDS counter, and lanes take their rank from
-// the popcount of lower peer lanes.
+// thread per block (4 in small sorts); 9 or 10 bits and 512 threads where that saves a
+// pass.  Stable ranking inside a block uses wave ballots: for each item slot the lanes
+// holding the same digit are found with a ballot per bit, all of them read the wave's LDS
+// counter of the digit, the last adds their number, and lanes take their rank from the
+// count of lower peer lanes.
 #include <algorithm>
 
 #include "internal.h"
@@ -39,7 +40,8 @@ __device__ inline uint64_t lanemask_lt() {
 }
 
 // ---------------------------------------------------------------- block scan
-// Exclusive scan of one u64 value per thread over a 256-thread block.
+// Exclusive scan of one u64 value per thread over a block of WAVES waves.
+template <int WAVES = kWaves>
 __device__ inline uint64_t block_exclusive_scan(uint64_t x, uint64_t* sh_waves, uint64_t& total) {
   const int lane = __lane_id();
   const int wave = threadIdx.x / 64;
@@ -53,7 +55,7 @@ __device__ inline uint64_t block_exclusive_scan(uint64_t x, uint64_t* sh_waves, 
   __syncthreads();
   uint64_t before = 0;
   total = 0;
-  for (int w = 0; w < kWaves; ++w) {
+  for (int w = 0; w < WAVES; ++w) {
     const uint64_t s = sh_waves[w];
     if (w < wave) before += s;
     total += s;
@@ -187,33 +189,59 @@ __global__ __launch_bounds__(256) void k_counts(const uint32_t* __restrict__ sid
 }
 
 // ---------------------------------------------------------------- radix sort
-// Chunk of this block (grid of nblocks blocks).  Workgroups go to the eight
-// XCDs in turn, so consecutive block indices land in different L2s; this
-// bijection gives each XCD a contiguous run of chunks instead (the last
-// nblocks % 8 keep their place).
-__device__ inline uint32_t xcd_chunk(uint32_t nblocks) {
-  const uint32_t n8 = nblocks / 8;
+// Chunk of this block, of nchunks that hold keys (blocks from nchunks on have none).
+// Workgroups go to the eight XCDs in turn, so consecutive block indices land in
+// different L2s; this bijection gives each XCD a contiguous run of chunks instead (the
+// last nchunks % 8 keep their place).  nchunks follows the number of keys there are, which
+// may be on the device, and not the capacity that the grid is launched for: with runs cut
+// from the capacity, 108M records in a capacity of 270M were sorted by 3.2 of the XCDs.
+__device__ inline uint32_t xcd_chunk(uint32_t nchunks) {
+  const uint32_t n8 = nchunks / 8;
   return blockIdx.x < 8 * n8 ? (blockIdx.x % 8) * n8 + blockIdx.x / 8 : blockIdx.x;
 }
 
-template <int ITEMS>
-__global__ __launch_bounds__(kThreads) void k_radix_hist(const uint32_t* __restrict__ keys,
-                                                         uint32_t n_max, const uint32_t* d_n,
-                                                         int shift, uint32_t nblocks,
-                                                         uint32_t stride,
-                                                         uint32_t* __restrict__ hist) {
-  __shared__ uint32_t h[kWaves][kRadix];
+// Shape of a pass: BITS per digit, blocks of THREADS threads with ITEMS keys each.
+template <int BITS_, int THREADS_, int ITEMS_>
+struct Pass {
+  static constexpr int BITS = BITS_, THREADS = THREADS_, ITEMS = ITEMS_;
+  static constexpr int RADIX = 1 << BITS, WAVES = THREADS / 64, CHUNK = THREADS * ITEMS;
+  static constexpr int PER = RADIX / THREADS;  // digits of a thread in the offset scan
+  static_assert(RADIX % THREADS == 0, "whole digits per thread");
+  static_assert(CHUNK < 65536, "local places fit 16 bits");
+  __host__ __device__ static uint32_t chunks(uint32_t n) {
+    return n / CHUNK + (n % CHUNK != 0 ? 1u : 0u);
+  }
+};
+using PassSmall = Pass<8, kThreads, 4>;
+using PassLarge = Pass<8, kThreads, kItems>;
+using PassWide9 = Pass<9, 512, kItems>;
+using PassWide10 = Pass<10, 512, kItems>;
+
+// Uint4 words of a digit's row that hold nchunks counts (zeros follow the last count).
+__host__ __device__ inline uint32_t row_quads(uint32_t nchunks) { return (nchunks + 3) / 4; }
+
+template <class P>
+__global__ __launch_bounds__(P::THREADS) void k_radix_hist(const uint32_t* __restrict__ keys,
+                                                           uint32_t n_max, const uint32_t* d_n,
+                                                           int shift, uint32_t stride,
+                                                           uint32_t* __restrict__ hist) {
+  constexpr int ITEMS = P::ITEMS;
+  constexpr int COPIES = P::BITS == 8 ? P::WAVES : 2;  // of the counts, against collisions
+  __shared__ uint32_t h[COPIES][P::RADIX];
   const int wave = threadIdx.x / 64, lane = __lane_id();
-  for (int d = threadIdx.x; d < kWaves * kRadix; d += kThreads) (&h[0][0])[d] = 0;
+  uint32_t* const hw = h[wave % COPIES];
+  for (int d = threadIdx.x; d < COPIES * P::RADIX; d += P::THREADS) (&h[0][0])[d] = 0;
   __syncthreads();
   const uint32_t n = load_n(n_max, d_n);
   // chunk of this block: XCD-contiguous as in k_radix_scatter, so that the
   // counts of neighbouring chunks, adjacent in every digit's row of the table,
   // are written through the same L2
-  const uint32_t chunk = xcd_chunk(nblocks);
+  const uint32_t nchunks = P::chunks(n);
+  const uint32_t chunk = xcd_chunk(nchunks);
+  if (chunk >= nchunks) return;  // no keys (uniform)
   // the wave's keys as 16-byte reads, all issued before the
   // counting (the order of counting does not matter)
-  const uint32_t base = chunk * (uint32_t)(kThreads * ITEMS) + wave * 64 * ITEMS;
+  const uint32_t base = chunk * (uint32_t)P::CHUNK + wave * 64 * ITEMS;
   uint4 q[ITEMS / 4];
 #pragma unroll
   for (int j = 0; j < ITEMS / 4; ++j) {
@@ -238,44 +266,47 @@ __global__ __launch_bounds__(kThreads) void k_radix_hist(const uint32_t* __restr
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const bool ok = i + u < n;
-      const uint32_t d = (kk[u] >> shift) & 0xffu;
+      const uint32_t d = __builtin_amdgcn_ubfe(kk[u], shift, P::BITS);
       const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
       const uint64_t m0 = __builtin_amdgcn_ballot_w64(ok && d == d0);
       const uint64_t r0 = __builtin_amdgcn_ballot_w64(ok && d != d0);
-      uint32_t d1 = 0x100u;  // no digit
+      uint32_t d1 = P::RADIX;  // no digit
       uint64_t m1 = 0;
       if (r0 != 0) {
         d1 = (uint32_t)__builtin_amdgcn_readlane((int)d, __builtin_ctzll(r0));
         m1 = __builtin_amdgcn_ballot_w64(ok && d == d1);
       }
       if (lane == 0) {
-        if (m0 != 0) atomicAdd(&h[wave][d0], (uint32_t)__popcll(m0));
-        if (m1 != 0) atomicAdd(&h[wave][d1], (uint32_t)__popcll(m1));
+        if (m0 != 0) atomicAdd(&hw[d0], (uint32_t)__popcll(m0));
+        if (m1 != 0) atomicAdd(&hw[d1], (uint32_t)__popcll(m1));
       }
-      if (ok && d != d0 && d != d1) atomicAdd(&h[wave][d], 1u);
+      if (ok && d != d0 && d != d1) atomicAdd(&hw[d], 1u);
     }
   }
   __syncthreads();
-  for (int d = threadIdx.x; d < kRadix; d += kThreads) {
+  for (int d = threadIdx.x; d < P::RADIX; d += P::THREADS) {
     uint32_t s = 0;
-    for (int w = 0; w < kWaves; ++w) s += h[w][d];
+#pragma unroll
+    for (int w = 0; w < COPIES; ++w) s += h[w][d];
     uint32_t* row = hist + (size_t)d * stride;
     row[chunk] = s;
-    if (chunk == nblocks - 1)
-      for (uint32_t c = nblocks; c < stride; ++c) row[c] = 0u;
+    if (chunk == nchunks - 1)
+      for (uint32_t c = nchunks; c < row_quads(nchunks) * 4; ++c) row[c] = 0u;
   }
 }
 
 // Rows of the digit table: row d (stride words, a multiple of four) holds digit d's count
-// in every chunk, and the totals of the rows follow the table.  One block per digit turns
+// in every chunk that has keys, and the totals of the rows follow the table.  One block per digit turns
 // its row into the exclusive prefix over the chunks and writes the total; the scatter
 // itself scans the 256 totals.  One launch instead of the two of a scan over the whole
 // table (passes over 16M and 42M keys: 7 us on average instead of 18).
+template <class P>
 __global__ __launch_bounds__(kThreads) void k_digit_rows(uint32_t* __restrict__ hist,
-                                                         uint32_t stride) {
+                                                         uint32_t stride, uint32_t n_max,
+                                                         const uint32_t* d_n) {
   __shared__ uint32_t sw[2][kWaves];
   uint4* row = reinterpret_cast<uint4*>(hist + (size_t)blockIdx.x * stride);
-  const uint32_t quads = stride / 4;
+  const uint32_t quads = row_quads(P::chunks(load_n(n_max, d_n)));
   const int lane = __lane_id(), wave = threadIdx.x / 64;
   uint32_t carry = 0;
   int buf = 0;
@@ -316,22 +347,22 @@ __global__ __launch_bounds__(kThreads) void k_digit_rows(uint32_t* __restrict__ 
       if (q < quads) row[q] = o;
     }
   }
-  if (threadIdx.x == 0) hist[(size_t)kRadix * stride + blockIdx.x] = carry;
+  if (threadIdx.x == 0) hist[(size_t)P::RADIX * stride + blockIdx.x] = carry;
 }
 
 // This chunk's prefix in row d, and the row's total: from the scanned table and its
 // totals, or (RAW, small tables) summed here from the counts.
-template <bool RAW>
+template <bool RAW, int RADIX>
 __device__ inline void digit_row(const uint32_t* __restrict__ hist, uint32_t stride,
-                                 uint32_t chunk, int d, uint32_t& before, uint32_t& total) {
+                                 uint32_t nchunks, uint32_t chunk, int d, uint32_t& before, uint32_t& total) {
   if constexpr (!RAW) {
     before = hist[(size_t)d * stride + chunk];
-    total = hist[(size_t)kRadix * stride + d];
+    total = hist[(size_t)RADIX * stride + d];
     return;
   }
   const uint4* row = reinterpret_cast<const uint4*>(hist + (size_t)d * stride);
   before = total = 0;
-  for (uint32_t q = 0; q < stride / 4; ++q) {
+  for (uint32_t q = 0; q < row_quads(nchunks); ++q) {
     const uint4 v = row[q];
     const uint32_t c = 4 * q;
     total += v.x + v.y + v.z + v.w;
@@ -340,108 +371,149 @@ __device__ inline void digit_row(const uint32_t* __restrict__ hist, uint32_t str
   }
 }
 
-// One pass of the stable LSD sort.  Each block ranks its 4096 elements by
+// One pass of the stable LSD sort.  Each block ranks its elements by
 // digit (wave ballots, stable), places them in LDS in block-local digit order,
 // and writes them out so that consecutive threads store consecutive addresses
-// of one digit's run: the global writes are coalesced.
-static_assert(kThreads == kRadix, "one thread per digit in the offset scan");
+// of one digit's run: the global writes are coalesced.  Large passes are bound by memory
+// (16 bytes a pair): 216M records of two 4096^2 views move at 4.5 TB/s (8 bits) and 4.0
+// (10 bits).  Ranking took more issue slots than that before it was cut from about 150 to
+// 75 instructions a key (one three-operand instruction per bit and half, no leader
+// election or shuffle, no test whether a key is there): 8-bit passes over 4M to 22M
+// pairs 29.3 -> 23.4 us on average, over 16M to 42M 112 -> 92.
+constexpr uint32_t kAndXnor = 0xF0 & ~(0xCC ^ 0xAA);  // bitop3 table of a & ~(b ^ c)
 
-template <bool RAW, int ITEMS>
-__global__ __launch_bounds__(kThreads) void k_radix_scatter(
+template <bool RAW, class P>
+__global__ __launch_bounds__(P::THREADS) void k_radix_scatter(
     const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
-    uint32_t* __restrict__ vout, uint32_t n_max, const uint32_t* d_n, int shift, uint32_t nblocks,
-    uint32_t stride, const uint32_t* __restrict__ hist) {
-  constexpr int CHUNK = kThreads * ITEMS;
-  __shared__ uint32_t cnt[kWaves][kRadix];
-  __shared__ uint32_t gofs[kRadix];    // global position of local index 0 of digit d's run
-  __shared__ uint32_t lstart[kRadix];  // block-local start of digit d
-  __shared__ uint64_t scan_tmp[kWaves];
-  __shared__ uint32_t sk[CHUNK], sv[CHUNK];
+    uint32_t* __restrict__ vout, uint32_t n_max, const uint32_t* d_n, int shift, uint32_t stride,
+    const uint32_t* __restrict__ hist) {
+  constexpr int ITEMS = P::ITEMS, CHUNK = P::CHUNK;
+  __shared__ uint16_t cnt[P::WAVES][P::RADIX];
+  __shared__ uint32_t gofs[P::RADIX];  // global position of local index 0 of digit d's run
+  __shared__ uint64_t scan_tmp[P::WAVES];
+  __shared__ uint32_t stage[CHUNK];
   const int wave = threadIdx.x / 64, lane = __lane_id();
-  for (int d = threadIdx.x; d < kWaves * kRadix; d += kThreads) (&cnt[0][0])[d] = 0;
+  for (int d = threadIdx.x; d < P::WAVES * P::RADIX; d += P::THREADS) (&cnt[0][0])[d] = 0;
   const uint32_t n = load_n(n_max, d_n);
   // the runs that neighbouring chunks write for one digit, adjacent in the
   // output, meet in the same L2, and the cache lines they share are written
   // back whole
-  const uint32_t chunk = xcd_chunk(nblocks);
-  const uint32_t base = chunk * (uint32_t)CHUNK + wave * 64 * ITEMS;
-  if (chunk * (uint32_t)CHUNK >= n) return;  // whole block empty (uniform)
-  uint32_t before, total_d;  // thread d: digit d's keys in earlier chunks, and in all
-  digit_row<RAW>(hist, stride, chunk, threadIdx.x, before, total_d);
-  uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
+  const uint32_t nchunks = P::chunks(n);
+  const uint32_t chunk = xcd_chunk(nchunks);
+  if (chunk >= nchunks) return;  // no keys (uniform)
+  const uint32_t nloc = min((uint32_t)CHUNK, n - chunk * (uint32_t)CHUNK);
+  // this thread's digits: their keys in earlier chunks, and in all
+  uint32_t before[P::PER], total_d[P::PER];
 #pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    const uint32_t i = base + j * 64 + lane;
-    const bool ok = i < n;
-    key[j] = ok ? kin[i] : 0u;
-    val[j] = ok ? (vin != nullptr ? vin[i] : i) : 0u;
+  for (int u = 0; u < P::PER; ++u)
+    digit_row<RAW, P::RADIX>(hist, stride, nchunks, chunk, threadIdx.x * P::PER + u, before[u],
+                             total_d[u]);
+  // Absent keys of the last chunk are all ones: the last digit, and last of their block (their
+  // indices are its highest), so they take local places from nloc on, which are not
+  // written out, and nothing below asks whether a key is there.
+  uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
+  const uint32_t first = chunk * (uint32_t)CHUNK + wave * 64 * ITEMS + lane;
+  if (nloc == (uint32_t)CHUNK) {
+    const uint32_t* kp = kin + first;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) key[j] = kp[j * 64];
+    if (vin != nullptr) {
+      const uint32_t* vp = vin + first;
+#pragma unroll
+      for (int j = 0; j < ITEMS; ++j) val[j] = vp[j * 64];
+    } else {
+#pragma unroll
+      for (int j = 0; j < ITEMS; ++j) val[j] = first + j * 64;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      const uint32_t i = first + j * 64;
+      key[j] = i < n ? kin[i] : ~0u;
+      val[j] = i < n ? (vin != nullptr ? vin[i] : i) : 0u;
+    }
   }
   __syncthreads();
-  const uint64_t lt = lanemask_lt();
+  // Ranking, in index order.  Lanes with the same digit: for every bit, the ballot of the
+  // bit where the lane's bit is set, its complement where it is clear, on the two 32-bit
+  // halves (sbit: the bit sign-extended, 0 or all ones; p & ~(ballot ^ sbit) is one
+  // three-operand instruction).  All of them read the wave's count of the digit, and the
+  // last adds theirs.
 #pragma unroll
   for (int j = 0; j < ITEMS; ++j) {
-    const uint32_t i = base + j * 64 + lane;
-    const bool ok = i < n;
-    const uint32_t d = (key[j] >> shift) & 0xffu;
-    // lanes with the same digit: for every bit, the ballot of the bit where the
-    // lane's bit is set, its complement where it is clear, on the two 32-bit
-    // halves (sbit: the bit sign-extended, 0 or all ones)
-    const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
-    uint32_t plo = (uint32_t)okm, phi = (uint32_t)(okm >> 32);
+    const uint32_t d = __builtin_amdgcn_ubfe(key[j], shift, P::BITS);
+    uint32_t plo = ~0u, phi = ~0u;
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int32_t sbit = (int32_t)(d << (31 - b)) >> 31;
+    for (int b = 0; b < P::BITS; ++b) {
+      const uint32_t sbit = (uint32_t)__builtin_amdgcn_sbfe((int)key[j], shift + b, 1);
       const uint64_t bb = __builtin_amdgcn_ballot_w64(sbit != 0);
-      plo &= ~((uint32_t)bb ^ (uint32_t)sbit);
-      phi &= ~((uint32_t)(bb >> 32) ^ (uint32_t)sbit);
+      plo = __builtin_amdgcn_bitop3_b32(plo, (uint32_t)bb, sbit, kAndXnor);
+      phi = __builtin_amdgcn_bitop3_b32(phi, (uint32_t)(bb >> 32), sbit, kAndXnor);
     }
-    const uint64_t peers = ((uint64_t)phi << 32) | plo;
-    uint32_t old = 0;
-    const int leader = 63 - __clzll((long long)peers);
-    if (ok && lane == leader) {
-      old = cnt[wave][d];
-      cnt[wave][d] = old + (uint32_t)__popcll(peers);
-    }
-    old = __shfl(old, ok ? leader : lane, 64);
-    rank[j] = old + (uint32_t)__popcll(peers & lt);
+    const uint32_t old = cnt[wave][d];
+    rank[j] = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, old));
+    const uint32_t now = old + __popc(plo) + __popc(phi);
+    __builtin_amdgcn_wave_barrier();  // every lane has read before the last one writes
+    if (rank[j] + 1 == now) cnt[wave][d] = (uint16_t)now;
+    __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
   {
-    // thread d: wave prefixes of digit d, the block-local start of d and its
-    // global position (unsigned wrap-around is intended in gofs - start)
-    const int d = threadIdx.x;
-    uint32_t run = 0;
-    for (int w = 0; w < kWaves; ++w) {
-      const uint32_t c = cnt[w][d];
-      cnt[w][d] = run;
-      run += c;
+    // the block-local start of this thread's digits in every wave, and their global
+    // position (unsigned wrap-around is intended in gofs - start)
+    const int d0 = threadIdx.x * P::PER;
+    uint32_t run[P::PER], sum = 0;
+    uint64_t all = 0;
+#pragma unroll
+    for (int u = 0; u < P::PER; ++u) {
+      run[u] = 0;
+#pragma unroll
+      for (int w = 0; w < P::WAVES; ++w) run[u] += cnt[w][d0 + u];
+      sum += run[u];
+      all += total_d[u];
     }
-    // one scan for both: this block's keys of lower digits (at most 4096) in the low
+    // one scan for both: this block's keys of lower digits (at most CHUNK) in the low
     // 16 bits, all chunks' keys of lower digits above them
     uint64_t total;
-    const uint64_t low = block_exclusive_scan(((uint64_t)total_d << 16) | run, scan_tmp, total);
-    const uint32_t start = (uint32_t)low & 0xffffu;
-    lstart[d] = start;
-    gofs[d] = (uint32_t)(low >> 16) + before - start;
+    const uint64_t low = block_exclusive_scan<P::WAVES>((all << 16) | sum, scan_tmp, total);
+    uint32_t start = (uint32_t)low & 0xffffu, g = (uint32_t)(low >> 16);
+#pragma unroll
+    for (int u = 0; u < P::PER; ++u) {
+      gofs[d0 + u] = g + before[u] - start;
+      g += total_d[u];
+#pragma unroll
+      for (int w = 0; w < P::WAVES; ++w) {
+        const uint32_t c = cnt[w][d0 + u];
+        cnt[w][d0 + u] = (uint16_t)start;
+        start += c;
+      }
+    }
+  }
+  __syncthreads();
+  // keys, then values, through the one staging array (half the memory of both at once:
+  // more blocks resident)
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    rank[j] += cnt[wave][__builtin_amdgcn_ubfe(key[j], shift, P::BITS)];
+    stage[rank[j]] = key[j];
+  }
+  __syncthreads();
+  uint32_t pos[ITEMS];
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const uint32_t t = j * P::THREADS + threadIdx.x;
+    const uint32_t k = stage[t];
+    pos[j] = gofs[__builtin_amdgcn_ubfe(k, shift, P::BITS)] + t;
+    if (t < nloc) kout[pos[j]] = k;
   }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    const uint32_t i = base + j * 64 + lane;
-    if (i < n) {
-      const uint32_t d = (key[j] >> shift) & 0xffu;
-      const uint32_t lp = lstart[d] + cnt[wave][d] + rank[j];
-      sk[lp] = key[j];
-      sv[lp] = val[j];
-    }
-  }
+  for (int j = 0; j < ITEMS; ++j) stage[rank[j]] = val[j];
   __syncthreads();
-  const uint32_t nloc = min((uint32_t)CHUNK, n - chunk * (uint32_t)CHUNK);
-  for (uint32_t t = threadIdx.x; t < nloc; t += kThreads) {
-    const uint32_t k = sk[t];
-    const uint32_t pos = gofs[(k >> shift) & 0xffu] + t;
-    kout[pos] = k;
-    vout[pos] = sv[t];
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const uint32_t t = j * P::THREADS + threadIdx.x;
+    if (t < nloc) vout[pos[j]] = stage[t];
   }
 }
 
@@ -651,10 +723,10 @@ inline uint32_t nblocks_of(uint32_t n) {
 // keys whose top byte is below 0xff are the touched entries: all but the total of the last
 // pass's row 255.
 template <bool RAW>
-__global__ void k_visible_count(const uint32_t* __restrict__ hist, uint32_t stride, uint32_t n,
-                                uint32_t* __restrict__ dst) {
+__global__ void k_visible_count(const uint32_t* __restrict__ hist, uint32_t stride,
+                                uint32_t nchunks, uint32_t n, uint32_t* __restrict__ dst) {
   uint32_t before, total;
-  digit_row<RAW>(hist, stride, 0u, 255, before, total);
+  digit_row<RAW, kRadix>(hist, stride, nchunks, 0u, 255, before, total);
   *dst = n - total;
 }
 
@@ -663,7 +735,7 @@ __global__ void k_visible_count(const uint32_t* __restrict__ hist, uint32_t stri
 // the launch, 147 chunks 20.5 against 12.6 and 3).
 constexpr uint32_t kRawChunks = 64;
 
-inline uint32_t row_stride(uint32_t nb) { return (nb + 3u) & ~3u; }
+inline uint32_t row_stride(uint32_t nb) { return row_quads(nb) * 4; }
 
 // Keys per thread of a sort of n pairs: a block's chain of ranking steps sets the time of
 // a small sort (a scatter pass with 4 instead of 16 keys a thread: 10k pairs 5.0 instead of
@@ -671,11 +743,44 @@ inline uint32_t row_stride(uint32_t nb) { return (nb + 3u) & ~3u; }
 // that it writes that of a large one.
 constexpr uint32_t kSmallSort = 1u << 20;
 
-inline int sort_items(uint32_t n) { return n <= kSmallSort ? 4 : kItems; }
-
 inline uint32_t sort_chunks(uint32_t n) {
-  const uint32_t c = (uint32_t)(kThreads * sort_items(n));
-  return (uint32_t)(((uint64_t)n + c - 1) / c);
+  return n <= kSmallSort ? PassSmall::chunks(n) : PassLarge::chunks(n);
+}
+
+// Words of a digit table: RADIX rows and their totals.
+template <class P>
+size_t table_words(uint32_t n) {
+  return (size_t)P::RADIX * (row_stride(P::chunks(n)) + 1);
+}
+
+// The passes of one sort, all of shape P.
+template <class P>
+gs_status run_passes(const uint32_t* ki, const uint32_t* vi, uint32_t* const (&kb)[2],
+                     uint32_t* const (&vb)[2], uint32_t n, const uint32_t* d_n, int bits,
+                     uint32_t* hist, int* result_in_b, hipStream_t s) {
+  const uint32_t nb = P::chunks(n), stride = row_stride(nb);
+  constexpr bool kMayRaw = P::CHUNK == PassSmall::CHUNK;  // the others start at more chunks
+  const bool raw = kMayRaw && nb <= kRawChunks;
+  int out = 0;
+  for (int shift = 0; shift < bits; shift += P::BITS) {
+    hipLaunchKernelGGL(k_radix_hist<P>, dim3(nb), dim3(P::THREADS), 0, s, ki, n, d_n, shift,
+                       stride, hist);
+    GS_LAUNCHED("radix_hist");
+    if (!raw) {
+      hipLaunchKernelGGL(k_digit_rows<P>, dim3(P::RADIX), dim3(kThreads), 0, s, hist, stride, n,
+                         d_n);
+      GS_LAUNCHED("digit_rows");
+    }
+    auto scatter = raw ? k_radix_scatter<kMayRaw, P> : k_radix_scatter<false, P>;
+    hipLaunchKernelGGL(scatter, dim3(nb), dim3(P::THREADS), 0, s, ki, vi, kb[out], vb[out], n,
+                       d_n, shift, stride, (const uint32_t*)hist);
+    GS_LAUNCHED("radix_scatter");
+    ki = kb[out];
+    vi = vb[out];
+    *result_in_b = out;
+    out ^= 1;
+  }
+  return GS_OK;
 }
 
 }  // namespace
@@ -738,39 +843,27 @@ gs_status scan_tile_counts(Ctx* ctx, SortScratch& ss, const uint32_t* sidx, cons
 
 gs_status sort_pairs_u32(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const uint32_t* vin,
                          uint32_t* kA, uint32_t* vA, uint32_t* kB, uint32_t* vB, uint32_t n,
-                         const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s) {
+                         const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s,
+                         uint32_t* spare, size_t spare_words) {
   *result_in_b = 0;
   if (n == 0) return GS_OK;
   gs_status st = sort_reserve(ctx, ss, n, s);
   if (st != GS_OK) return st;
-  const uint32_t nb = sort_chunks(n), stride = row_stride(nb);
-  const bool raw = nb <= kRawChunks, small = sort_items(n) == 4;
   auto* hist = (uint32_t*)ss.hist.p;
-  uint32_t* kb[2] = {kA, kB};
-  uint32_t* vb[2] = {vA, vB};
-  const uint32_t* ki = kin;
-  const uint32_t* vi = vin;
-  int out = 0;
-  for (int shift = 0; shift < bits; shift += 8) {
-    auto count = small ? k_radix_hist<4> : k_radix_hist<kItems>;
-    hipLaunchKernelGGL(count, dim3(nb), dim3(kThreads), 0, s, ki, n, d_n, shift, nb,
-                       stride, hist);
-    GS_LAUNCHED("radix_hist");
-    if (!raw) {
-      hipLaunchKernelGGL(k_digit_rows, dim3(kRadix), dim3(kThreads), 0, s, hist, stride);
-      GS_LAUNCHED("digit_rows");
-    }
-    auto scatter = small ? (raw ? k_radix_scatter<true, 4> : k_radix_scatter<false, 4>)
-                         : (raw ? k_radix_scatter<true, kItems> : k_radix_scatter<false, kItems>);
-    hipLaunchKernelGGL(scatter, dim3(nb), dim3(kThreads), 0, s, ki, vi, kb[out], vb[out], n, d_n,
-                       shift, nb, stride, (const uint32_t*)hist);
-    GS_LAUNCHED("radix_scatter");
-    ki = kb[out];
-    vi = vb[out];
-    *result_in_b = out;
-    out ^= 1;
-  }
-  return GS_OK;
+  uint32_t* const kb[2] = {kA, kB};
+  uint32_t* const vb[2] = {vA, vB};
+  if (n <= kSmallSort)
+    return run_passes<PassSmall>(kin, vin, kb, vb, n, d_n, bits, hist, result_in_b, s);
+  // Keys of 17 to 20 bits (more than 65536 tiles): two passes of nine or ten bits instead of
+  // three of eight, where the caller's spare memory holds their table (as large as the
+  // 8-bit one or twice that).  Faster from the smallest of these sorts on (forward pass of
+  // 1.5M records on 69k tiles 276 -> 259 us, 1.3M on 277k tiles 459 -> 445, 7.5M 526 -> 501
+  // and 658 -> 640; the two passes over 216M records 2.2 ms, the three 3.0).
+  if (bits > 16 && bits <= 18 && table_words<PassWide9>(n) <= spare_words)
+    return run_passes<PassWide9>(kin, vin, kb, vb, n, d_n, bits, spare, result_in_b, s);
+  if (bits > 18 && bits <= 20 && table_words<PassWide10>(n) <= spare_words)
+    return run_passes<PassWide10>(kin, vin, kb, vb, n, d_n, bits, spare, result_in_b, s);
+  return run_passes<PassLarge>(kin, vin, kb, vb, n, d_n, bits, hist, result_in_b, s);
 }
 
 gs_status launch_emit(const ViewTable& vt, Frame& f, const uint32_t* sidx, const uint32_t* srx,
@@ -812,8 +905,8 @@ gs_status launch_visible_count(const SortScratch& ss, uint32_t n, uint32_t* dst,
   if (n == 0) return launch_fill_u32(dst, 0u, 1, s);
   const uint32_t nb = sort_chunks(n);
   auto kern = nb <= kRawChunks ? k_visible_count<true> : k_visible_count<false>;
-  hipLaunchKernelGGL(kern, dim3(1), dim3(1), 0, s, (const uint32_t*)ss.hist.p, row_stride(nb), n,
-                     dst);
+  hipLaunchKernelGGL(kern, dim3(1), dim3(1), 0, s, (const uint32_t*)ss.hist.p, row_stride(nb), nb,
+                     n, dst);
   GS_LAUNCHED("visible_count");
   return GS_OK;
 }

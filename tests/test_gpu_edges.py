@@ -170,6 +170,46 @@ def test_binning_at_sort_sizes(P, ctx, n):
     frame.release()
 
 
+@pytest.mark.parametrize("n,w,h,log_scale,fits", [
+    (300_000, 2100, 2104, -5.6, True),     # 17-bit tile numbers
+    (300_000, 4216, 4200, -6.6, True),     # 19-bit
+    (2_000, 2100, 2104, -3.0, False),      # 17-bit, too many records for the wide digits' table
+    (300_000, 1600, 1600, -5.6, None),     # 16-bit
+])
+def test_binning_of_many_tiles(P, ctx, n, w, h, log_scale, fits):
+    """More than 2^20 records over more than 65536 tiles (sorted by wide digits where the
+    entries' scratch holds their table) against a stable sort of the exported rectangles
+    and depths (whole numbers: equal)."""
+    g = torch.Generator("cuda").manual_seed(w)
+    means = torch.rand((3, n), device="cuda", generator=g) * 2 - 1
+    p = P.Params(means, torch.full((3, n), log_scale, device="cuda"),
+                 torch.tensor([[1.], [0], [0], [0]], device="cuda").repeat(1, n).contiguous(),
+                 torch.zeros(n, device="cuda"), torch.zeros((3, n), device="cuda"), 0)
+    cam = P.orbit_cameras(4, 2.5, 60.0, w, h)[1]
+    _, frame = P.render_fwd(ctx, p, [cam], tile=8, lds_depth=64)
+    st = frame.stats()
+    tiles, nx = st["n_tiles"], -(-w // 8)
+    assert st["n_records"] > 1 << 20
+    bits = (tiles - 1).bit_length()
+    assert (bits > 16) == (fits is not None)
+    if fits is not None:
+        table = (1 << -(-bits // 2)) * (-(-st["n_records"] // 8192) + 4)
+        assert (table <= n) if fits else (table > 2 * n)
+    rect = frame.export("rects").view(n, 2).long() & 0xffffffff
+    depth = frame.export("depths").long() & 0xffffffff
+    x0, y0, x1, y1 = rect[:, 0] & 0xffff, rect[:, 0] >> 16, rect[:, 1] & 0xffff, rect[:, 1] >> 16
+    m = (x1 - x0 + 1).clamp(min=0) * (y1 - y0 + 1).clamp(min=0)
+    order = torch.sort(depth, stable=True)[1]
+    e = torch.repeat_interleave(order, m[order])
+    r = torch.arange(e.numel(), device="cuda") - torch.repeat_interleave(
+        m[order].cumsum(0) - m[order], m[order])
+    wide = (x1 - x0 + 1).clamp(min=1)[e]
+    tile, by = torch.sort((y0[e] + r // wide) * nx + x0[e] + r % wide, stable=True)
+    assert torch.equal(frame.export("values").long(), e[by])
+    assert torch.equal(frame.export("keys"), (tile << 32) | depth[e[by]])
+    frame.release()
+
+
 # ---------------------------------------------------------------- outputs sized inside a call
 def test_outputs_allocated_between_count_and_write(P, ctx, monkeypatch):
     """extract() and densify(), which allocate inside the library's call, against counting
