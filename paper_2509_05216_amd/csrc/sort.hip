@@ -161,16 +161,30 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(F f, uint32_t n, const u
   }
 }
 
+// Chunk of this block, of nchunks that hold keys (blocks from nchunks on have none).
+// Workgroups go to the eight XCDs in turn, so consecutive block indices land in
+// different L2s; this bijection gives each XCD a contiguous run of chunks instead (the
+// last nchunks % 8 keep their place).  nchunks follows the number of keys there are, which
+// may be on the device, and not the capacity that the grid is launched for: with runs cut
+// from the capacity, 108M records in a capacity of 270M were sorted by 3.2 of the XCDs.
+__device__ inline uint32_t xcd_chunk(uint32_t nchunks) {
+  const uint32_t n8 = nchunks / 8;
+  return blockIdx.x < 8 * n8 ? (blockIdx.x % 8) * n8 + blockIdx.x / 8 : blockIdx.x;
+}
+
 // The one random gather of the rectangles: the tile count of every (view,
 // Gaussian) entry in depth order, and the rectangles themselves in that order
-// for the emission.
+// for the emission.  Neighbours in memory are often thousands of entries apart in depth,
+// not millions: with a contiguous run of entries per XCD their line is still in its L2
+// (4M entries 57 -> 39 us, 16M 238 -> 182, 36M 436 -> 426).
 __global__ __launch_bounds__(256) void k_counts(const uint32_t* __restrict__ sidx,
                                                 const uint2* __restrict__ rect, uint32_t n,
                                                 uint32_t* __restrict__ counts,
                                                 uint32_t* __restrict__ srx,
                                                 uint32_t* __restrict__ sry,
                                                 uint64_t* __restrict__ partial) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t block = xcd_chunk(gridDim.x);
+  const uint32_t i = block * blockDim.x + threadIdx.x;
   uint32_t m = 0;
   if (i < n) {
     const uint2 r = rect[sidx[i]];
@@ -185,21 +199,10 @@ __global__ __launch_bounds__(256) void k_counts(const uint32_t* __restrict__ sid
   __shared__ uint64_t sw[kWaves];
   uint64_t total;
   block_exclusive_scan(m, sw, total);
-  if (threadIdx.x == 0) partial[blockIdx.x] = total;
+  if (threadIdx.x == 0) partial[block] = total;
 }
 
 // ---------------------------------------------------------------- radix sort
-// Chunk of this block, of nchunks that hold keys (blocks from nchunks on have none).
-// Workgroups go to the eight XCDs in turn, so consecutive block indices land in
-// different L2s; this bijection gives each XCD a contiguous run of chunks instead (the
-// last nchunks % 8 keep their place).  nchunks follows the number of keys there are, which
-// may be on the device, and not the capacity that the grid is launched for: with runs cut
-// from the capacity, 108M records in a capacity of 270M were sorted by 3.2 of the XCDs.
-__device__ inline uint32_t xcd_chunk(uint32_t nchunks) {
-  const uint32_t n8 = nchunks / 8;
-  return blockIdx.x < 8 * n8 ? (blockIdx.x % 8) * n8 + blockIdx.x / 8 : blockIdx.x;
-}
-
 // Shape of a pass: BITS per digit, blocks of THREADS threads with ITEMS keys each.
 template <int BITS_, int THREADS_, int ITEMS_>
 struct Pass {
@@ -520,10 +523,14 @@ __global__ __launch_bounds__(P::THREADS) void k_radix_scatter(
 // ---------------------------------------------------------------- emission
 // Records of every (view, Gaussian) entry in depth order: (global tile, entry)
 // for each tile of its rectangle, row by row.  A wave writes its 64 entries'
-// records together: lane r of a pass takes the wave's record r (the owning
-// entry found by a search over the wave's prefix sums of record counts), so
+// records together: lane r of a pass takes the wave's record r, so
 // each pass stores 64 consecutive records and no lane idles behind a large
-// rectangle.  An entry whose records would pass the capacity writes none and
+// rectangle.  The owning entry is the last one that starts at or before the record:
+// the starts in a pass are marked in LDS, and their number up to the lane picks the
+// entry, whose fields one 16-byte read brings (a search over the wave's prefix sums, seven
+// dependent shuffles and six more for the fields, took 587 us instead of 511 for the 216M
+// records of two 4096^2 views of 18M Gaussians, 8.8 instead of 6.5 for those of 10k).
+// Bound by the stores.  An entry whose records would pass the capacity writes none and
 // sets the overflow word.
 __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
                                               const uint32_t* __restrict__ sidx,
@@ -540,7 +547,8 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
   for (uint32_t t = i; t < tiles; t += gridDim.x * blockDim.x) ranges[t] = make_uint2(0u, 0u);
   // ... and so do the counts of the tile order
   for (uint32_t t = i; t < (uint32_t)kOrderWords; t += gridDim.x * blockDim.x) order[tiles + t] = 0u;
-  uint32_t need = 0, o = 0, idx = 0, key0 = 0, w = 1, tx = 0;
+  uint32_t need = 0, o = 0, idx = 0, key0 = 0, w = 1, tx = 1;
+  bool over = false;
   if (i < count) {
     idx = sidx[i];
     const uint2 r = make_uint2(srx[i], sry[i]);  // rect[idx], gathered in depth order by k_counts
@@ -552,6 +560,7 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
       o = offs[i];
       const uint32_t nd = (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1));
       if ((uint64_t)o + nd > cap) {
+        over = true;
         if (overflow != nullptr) *overflow = 1u;
       } else {
         need = nd;
@@ -560,6 +569,8 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
       }
     }
   }
+  // no room for the later ones either (their 32-bit offsets may have wrapped)
+  if ((__builtin_amdgcn_ballot_w64(over) & lanemask_lt()) != 0) need = 0;
   // exclusive prefix of the record counts over the wave, and the wave total
   uint32_t incl = need;
 #pragma unroll
@@ -568,26 +579,38 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
     if (lane >= d) incl += t;
   }
   const uint32_t excl = incl - need;
-  const uint32_t total = (uint32_t)__shfl((int)incl, 63, 64);
-  // wave-uniform passes (every lane takes part in the shuffles)
-  for (uint32_t base = 0; base < total; base += 64) {
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+  if (total == 0) return;  // (uniform in the wave; no block barrier follows)
+  // the entries with records, packed: start in the wave's records, first tile, entry, and
+  // the widths of rectangle and image in tiles (at most 65536: less one in 16 bits)
+  __shared__ uint4 ent[kWaves][64];
+  __shared__ uint32_t mark[kWaves][64];
+  uint4* const e = ent[threadIdx.x / 64];
+  uint32_t* const mk = mark[threadIdx.x / 64];
+  const uint64_t has = __builtin_amdgcn_ballot_w64(need != 0);
+  if (need != 0)
+    e[__builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32),
+                                __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u))] =
+        make_uint4(excl, key0, idx, (w - 1) | ((tx - 1) << 16));
+  mk[lane] = 0;
+  // the wave's records are adjacent in the output (entries without room for theirs come
+  // after all those with)
+  const uint32_t o0 = (uint32_t)__builtin_amdgcn_readlane((int)(o - excl), __builtin_ctzll(has));
+  uint32_t before = 0;  // entries that start before this pass
+  for (uint32_t base = 0, pass = 1; base < total; base += 64, ++pass) {
+    // mark the records that start an entry; a record's entry is the last start up to it
+    if (need != 0 && excl - base < 64u) mk[excl - base] = pass;
+    __builtin_amdgcn_wave_barrier();
+    const bool start = mk[lane] == pass;
+    const uint64_t m = __builtin_amdgcn_ballot_w64(start);
+    const uint32_t lower = __builtin_amdgcn_mbcnt_hi(
+        (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, before));
+    const uint4 q = e[lower + (start ? 1u : 0u) - 1u];
+    __builtin_amdgcn_wave_barrier();
+    before += (uint32_t)__popcll(m);
     const uint32_t rr = base + (uint32_t)lane;
-    const bool act = rr < total;
-    // owner: the largest lane l with excl_l <= rr (never a lane without records)
-    int l = 0;
-#pragma unroll
-    for (int step = 32; step >= 1; step >>= 1) {
-      const int c = l + step;
-      const uint32_t e = (uint32_t)__shfl((int)excl, c, 64);
-      if (e <= rr) l = c;
-    }
-    const uint32_t li = rr - (uint32_t)__shfl((int)excl, l, 64);
-    const uint32_t wl = (uint32_t)__shfl((int)w, l, 64);
-    const uint32_t txl = (uint32_t)__shfl((int)tx, l, 64);
-    const uint32_t k0 = (uint32_t)__shfl((int)key0, l, 64);
-    const uint32_t ol = (uint32_t)__shfl((int)o, l, 64);
-    const uint32_t il = (uint32_t)__shfl((int)idx, l, 64);
-    if (act) {
+    if (rr < total) {
+      const uint32_t li = rr - q.x, wl = (q.w & 0xffffu) + 1, txl = (q.w >> 16) + 1;
       // row and column of the record in its rectangle: a float reciprocal
       // estimate of li / wl is off by at most one below 2^20, so one step
       // corrects it (exact integer division beyond)
@@ -600,8 +623,8 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
         yy = li / wl;
       }
       const uint32_t xx = li - yy * wl;
-      tkey[ol + li] = k0 + yy * txl + xx;
-      tval[ol + li] = il;
+      tkey[o0 + rr] = q.y + yy * txl + xx;
+      tval[o0 + rr] = q.z;
     }
   }
 }
