@@ -962,7 +962,7 @@ gs_status forward_stages(Ctx* ctx, Frame& f, const ParamsDev& pd, hipStream_t s,
   }
   if (st != GS_OK) return st;
   uint32_t n_rec = 0;              // host bound on the record count (grid sizes)
-  const uint32_t* d_K = nullptr;   // device record count (device-count pipelines)
+  uint32_t* d_K = nullptr;         // device record count (device-count pipelines)
   uint32_t* overflow = nullptr;
   if (cap == 0) {
     // words 8..11: the record total and the visible count, in one readback
@@ -993,7 +993,7 @@ gs_status forward_stages(Ctx* ctx, Frame& f, const ParamsDev& pd, hipStream_t s,
   // 4. records in depth order, then the stable sort on the tile digits
   {
     StageTimer tm(ctx, ST_EMIT, s);
-    st = launch_emit(f.vt, f, sidx, srx, sry, vn, overflow, s);
+    st = launch_emit(f.vt, f, sidx, srx, sry, vn, overflow, d_K, s);
   }
   if (st != GS_OK) return st;
   {

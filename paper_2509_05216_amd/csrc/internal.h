@@ -347,9 +347,11 @@ gs_status sort_reserve(Ctx* ctx, SortScratch& ss, uint32_t n, hipStream_t s);
 gs_status launch_clamp_count(const uint64_t* total, uint32_t cap, uint32_t* K,
                              uint32_t* overflow, hipStream_t s);
 // Records of count (view, Gaussian) entries; overflow (optional) is set, and the
-// entry skipped, when its records would pass the record buffers' capacity.
+// entry skipped, when its records would pass the record buffers' capacity; the device
+// record count d_K (optional) then ends before it.
 gs_status launch_emit(const ViewTable& vt, Frame& f, const uint32_t* sidx, const uint32_t* srx,
-                      const uint32_t* sry, uint32_t count, uint32_t* overflow, hipStream_t s);
+                      const uint32_t* sry, uint32_t count, uint32_t* overflow, uint32_t* d_K,
+                      hipStream_t s);
 // Per-tile ranges of n_rec records (d_K: device count bounding n_rec, optional).
 gs_status launch_ranges(Frame& f, uint32_t n_rec, const uint32_t* d_K, hipStream_t s);
 // Tiles in descending length class of their lists: the order in which they are blended.

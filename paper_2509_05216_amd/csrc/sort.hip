@@ -539,7 +539,8 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
                                               const uint32_t* __restrict__ offs, uint32_t count,
                                               uint32_t cap, uint32_t* __restrict__ tkey,
                                               uint32_t* __restrict__ tval,
-                                              uint32_t* overflow, uint2* __restrict__ ranges,
+                                              uint32_t* overflow, uint32_t* d_K,
+                                              uint2* __restrict__ ranges,
                                               uint32_t tiles, uint32_t* __restrict__ order) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = __lane_id();
@@ -562,6 +563,9 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
       if ((uint64_t)o + nd > cap) {
         over = true;
         if (overflow != nullptr) *overflow = 1u;
+        // the records end where the first entry without room begins: nothing that was
+        // not written is sorted
+        if (d_K != nullptr) atomicMin(d_K, o);
       } else {
         need = nd;
         w = (uint32_t)(x1 - x0 + 1);
@@ -890,13 +894,14 @@ gs_status sort_pairs_u32(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const u
 }
 
 gs_status launch_emit(const ViewTable& vt, Frame& f, const uint32_t* sidx, const uint32_t* srx,
-                      const uint32_t* sry, uint32_t count, uint32_t* overflow, hipStream_t s) {
+                      const uint32_t* sry, uint32_t count, uint32_t* overflow, uint32_t* d_K,
+                      hipStream_t s) {
   if (count == 0) return GS_OK;
   const size_t cap_bytes = f.tkey[0].cap < f.tval[0].cap ? f.tkey[0].cap : f.tval[0].cap;
   const uint32_t cap = (uint32_t)(cap_bytes / sizeof(uint32_t));
   hipLaunchKernelGGL(k_emit, dim3((count + 255) / 256), dim3(256), 0, s, vt, sidx, srx,
                      sry, (const uint32_t*)f.offs.p, count, cap, (uint32_t*)f.tkey[0].p,
-                     (uint32_t*)f.tval[0].p, overflow, (uint2*)f.ranges.p,
+                     (uint32_t*)f.tval[0].p, overflow, d_K, (uint2*)f.ranges.p,
                      (uint32_t)f.vt.total_tiles, (uint32_t*)f.order.p);
   GS_LAUNCHED("emit");
   return GS_OK;
