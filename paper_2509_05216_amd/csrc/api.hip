@@ -940,7 +940,7 @@ gs_status forward_stages(Ctx* ctx, Frame& f, const ParamsDev& pd, hipStream_t s,
   int in_b = 0;
   {
     StageTimer tm(ctx, ST_DEPTH_SORT, s);
-    st = sort_pairs_u32(ctx, f.ss, (const uint32_t*)f.dkey.p, nullptr, (uint32_t*)f.dkw[0].p,
+    st = sort_pairs(ctx, f.ss, (const uint32_t*)f.dkey.p, nullptr, (uint32_t*)f.dkw[0].p,
                         (uint32_t*)f.sidx[0].p, (uint32_t*)f.dkw[1].p, (uint32_t*)f.sidx[1].p,
                         vn, nullptr, 32, &in_b, s);
   }
@@ -998,10 +998,19 @@ gs_status forward_stages(Ctx* ctx, Frame& f, const ParamsDev& pd, hipStream_t s,
   if (st != GS_OK) return st;
   {
     StageTimer tm(ctx, ST_TILE_SORT, s);
-    st = sort_pairs_u32(ctx, f.ss, (const uint32_t*)f.tkey[0].p, (const uint32_t*)f.tval[0].p,
-                        (uint32_t*)f.tkey[1].p, (uint32_t*)f.tval[1].p, (uint32_t*)f.tkey[0].p,
-                        (uint32_t*)f.tval[0].p, n_rec, d_K, f.key_bits, &in_b, s, srx,
-                        f.dkw[0].cap / sizeof(uint32_t));  // emitted: the rectangles are free
+    auto* v0 = (uint32_t*)f.tval[0].p;
+    auto* v1 = (uint32_t*)f.tval[1].p;
+    if (f.short_keys()) {
+      auto* k0 = (uint16_t*)f.tkey[0].p;
+      auto* k1 = (uint16_t*)f.tkey[1].p;
+      st = sort_pairs(ctx, f.ss, (const uint16_t*)k0, v0, k1, v1, k0, v0, n_rec, d_K, f.key_bits,
+                      &in_b, s);
+    } else {
+      auto* k0 = (uint32_t*)f.tkey[0].p;
+      auto* k1 = (uint32_t*)f.tkey[1].p;
+      st = sort_pairs(ctx, f.ss, (const uint32_t*)k0, v0, k1, v1, k0, v0, n_rec, d_K, f.key_bits,
+                      &in_b, s, srx, f.dkw[0].cap / sizeof(uint32_t));  // srx: emitted, free
+    }
   }
   if (st != GS_OK) return st;
   f.tkey_sel = (n_rec == 0) ? 0 : (in_b ? 0 : 1);

@@ -9,7 +9,7 @@
 //   clampm  u8[V*N]        SH clamp mask (bit c set: channel c clamped at 0)
 //   sidx    u32[V*N]       (view*N + gid) in (depth bits, index) order
 //   offs    u32[V*N]       exclusive scan of tiles touched, in sidx order
-//   tkey    u32[K]         global tile id of each record, tile-sorted
+//   tkey    u32[K]         global tile id of each record, tile-sorted (u16 up to 16 bits)
 //   tval    u32[K]         view*N + gid of each record
 //   ranges  uint2[tiles]   [start, end) per global tile
 //   finalT  f32[P], ncon u32[P]   per pixel over all views
@@ -270,6 +270,9 @@ struct Frame {
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   bool keep_radii = false;    // this forward writes radii
   bool screen_kept = false;   // the last backward kept its screen-space sums
+  // Tile keys of up to 16 bits are held as u16 (in buffers of u32's size): a third less to
+  // move per record.
+  bool short_keys() const { return key_bits <= 16; }
   int tkey_sel = 0;  // which of tkey/tval holds the sorted records
   int sidx_sel = 0;  // which of sidx holds the depth-sorted (view, Gaussian) indices
   bool acc_zeroed = false;
@@ -331,10 +334,13 @@ gs_status launch_init_points(const float* xyz, int64_t n, const gs_init_opts& o,
 // reads kin/vin (vin == nullptr: values are the indices 0..n-1) and passes
 // alternate between buffer pairs A and B; *result_in_b tells where the result is.
 // `spare`: memory that is free during the sort, for larger digit tables.
-gs_status sort_pairs_u32(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const uint32_t* vin,
-                         uint32_t* kA, uint32_t* vA, uint32_t* kB, uint32_t* vB, uint32_t n,
-                         const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s,
-                         uint32_t* spare = nullptr, size_t spare_words = 0);
+gs_status sort_pairs(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const uint32_t* vin,
+                     uint32_t* kA, uint32_t* vA, uint32_t* kB, uint32_t* vB, uint32_t n,
+                     const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s,
+                     uint32_t* spare = nullptr, size_t spare_words = 0);
+gs_status sort_pairs(Ctx* ctx, SortScratch& ss, const uint16_t* kin, const uint32_t* vin,
+                     uint16_t* kA, uint32_t* vA, uint16_t* kB, uint32_t* vB, uint32_t n,
+                     const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s);
 // Tile counts of the depth-ordered entries, scanned into record offsets; the
 // entries' rectangles are also written in that order (srx, sry: the two halves)
 // so the emission reads them coalesced.

@@ -223,8 +223,15 @@ using PassWide10 = Pass<10, 512, kItems>;
 // Uint4 words of a digit's row that hold nchunks counts (zeros follow the last count).
 __host__ __device__ inline uint32_t row_quads(uint32_t nchunks) { return (nchunks + 3) / 4; }
 
-template <class P>
-__global__ __launch_bounds__(P::THREADS) void k_radix_hist(const uint32_t* __restrict__ keys,
+// Four keys from a multiple of four on.
+__device__ inline uint4 load4(const uint32_t* p) { return *reinterpret_cast<const uint4*>(p); }
+__device__ inline uint4 load4(const uint16_t* p) {
+  const uint2 q = *reinterpret_cast<const uint2*>(p);
+  return make_uint4(q.x & 0xffffu, q.x >> 16, q.y & 0xffffu, q.y >> 16);
+}
+
+template <class P, class K>
+__global__ __launch_bounds__(P::THREADS) void k_radix_hist(const K* __restrict__ keys,
                                                            uint32_t n_max, const uint32_t* d_n,
                                                            int shift, uint32_t stride,
                                                            uint32_t* __restrict__ hist) {
@@ -242,7 +249,7 @@ __global__ __launch_bounds__(P::THREADS) void k_radix_hist(const uint32_t* __res
   const uint32_t nchunks = P::chunks(n);
   const uint32_t chunk = xcd_chunk(nchunks);
   if (chunk >= nchunks) return;  // no keys (uniform)
-  // the wave's keys as 16-byte reads, all issued before the
+  // the wave's keys four at a time, all issued before the
   // counting (the order of counting does not matter)
   const uint32_t base = chunk * (uint32_t)P::CHUNK + wave * 64 * ITEMS;
   uint4 q[ITEMS / 4];
@@ -250,7 +257,7 @@ __global__ __launch_bounds__(P::THREADS) void k_radix_hist(const uint32_t* __res
   for (int j = 0; j < ITEMS / 4; ++j) {
     const uint32_t i = base + 4u * (j * 64 + lane);
     if (i + 4 <= n) {
-      q[j] = *reinterpret_cast<const uint4*>(keys + i);
+      q[j] = load4(keys + i);
     } else {  // tail: absent keys marked ~0 and skipped below
       q[j].x = i < n ? keys[i] : ~0u;
       q[j].y = i + 1 < n ? keys[i + 1] : ~0u;
@@ -385,9 +392,9 @@ __device__ inline void digit_row(const uint32_t* __restrict__ hist, uint32_t str
 // pairs 29.3 -> 23.4 us on average, over 16M to 42M 112 -> 92.
 constexpr uint32_t kAndXnor = 0xF0 & ~(0xCC ^ 0xAA);  // bitop3 table of a & ~(b ^ c)
 
-template <bool RAW, class P>
+template <bool RAW, class P, class K>
 __global__ __launch_bounds__(P::THREADS) void k_radix_scatter(
-    const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
+    const K* __restrict__ kin, const uint32_t* __restrict__ vin, K* __restrict__ kout,
     uint32_t* __restrict__ vout, uint32_t n_max, const uint32_t* d_n, int shift, uint32_t stride,
     const uint32_t* __restrict__ hist) {
   constexpr int ITEMS = P::ITEMS, CHUNK = P::CHUNK;
@@ -417,7 +424,7 @@ __global__ __launch_bounds__(P::THREADS) void k_radix_scatter(
   uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
   const uint32_t first = chunk * (uint32_t)CHUNK + wave * 64 * ITEMS + lane;
   if (nloc == (uint32_t)CHUNK) {
-    const uint32_t* kp = kin + first;
+    const K* kp = kin + first;
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) key[j] = kp[j * 64];
     if (vin != nullptr) {
@@ -507,7 +514,7 @@ __global__ __launch_bounds__(P::THREADS) void k_radix_scatter(
     const uint32_t t = j * P::THREADS + threadIdx.x;
     const uint32_t k = stage[t];
     pos[j] = gofs[__builtin_amdgcn_ubfe(k, shift, P::BITS)] + t;
-    if (t < nloc) kout[pos[j]] = k;
+    if (t < nloc) kout[pos[j]] = (K)k;
   }
   __syncthreads();
 #pragma unroll
@@ -532,12 +539,13 @@ __global__ __launch_bounds__(P::THREADS) void k_radix_scatter(
 // records of two 4096^2 views of 18M Gaussians, 8.8 instead of 6.5 for those of 10k).
 // Bound by the stores.  An entry whose records would pass the capacity writes none and
 // sets the overflow word.
+template <class K>
 __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
                                               const uint32_t* __restrict__ sidx,
                                               const uint32_t* __restrict__ srx,
                                               const uint32_t* __restrict__ sry,
                                               const uint32_t* __restrict__ offs, uint32_t count,
-                                              uint32_t cap, uint32_t* __restrict__ tkey,
+                                              uint32_t cap, K* __restrict__ tkey,
                                               uint32_t* __restrict__ tval,
                                               uint32_t* overflow, uint32_t* d_K,
                                               uint2* __restrict__ ranges,
@@ -627,15 +635,16 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
         yy = li / wl;
       }
       const uint32_t xx = li - yy * wl;
-      tkey[o0 + rr] = q.y + yy * txl + xx;
+      tkey[o0 + rr] = (K)(q.y + yy * txl + xx);
       tval[o0 + rr] = q.z;
     }
   }
 }
 
-// Per-tile [start, end) of the sorted keys: four keys per thread (one 16-byte
+// Per-tile [start, end) of the sorted keys: four keys per thread (one wide
 // read, plus the neighbours on either side); a run boundary sets the range.
-__global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tkey, uint32_t K_max,
+template <class KT>
+__global__ __launch_bounds__(256) void k_ranges(const KT* __restrict__ tkey, uint32_t K_max,
                                                 const uint32_t* d_K, uint2* __restrict__ ranges) {
   const uint32_t k0 = 4u * (blockIdx.x * blockDim.x + threadIdx.x);
   const uint32_t K = load_n(K_max, d_K);
@@ -643,7 +652,7 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ tke
   uint32_t t[6];  // keys k0 - 1 .. k0 + 4 (~0 outside [0, K): differs from every tile)
   t[0] = k0 > 0 ? tkey[k0 - 1] : ~0u;
   if (k0 + 4 <= K) {
-    const uint4 q = *reinterpret_cast<const uint4*>(tkey + k0);
+    const uint4 q = load4(tkey + k0);
     t[1] = q.x;
     t[2] = q.y;
     t[3] = q.z;
@@ -733,7 +742,8 @@ __global__ __launch_bounds__(256) void k_order_place(const uint2* __restrict__ r
   }
 }
 
-__global__ __launch_bounds__(256) void k_export_keys(const uint32_t* __restrict__ tkey,
+template <class KT>
+__global__ __launch_bounds__(256) void k_export_keys(const KT* __restrict__ tkey,
                                                      const uint32_t* __restrict__ tval,
                                                      const uint32_t* __restrict__ dkey, uint32_t K,
                                                      uint64_t* __restrict__ out) {
@@ -781,8 +791,8 @@ size_t table_words(uint32_t n) {
 }
 
 // The passes of one sort, all of shape P.
-template <class P>
-gs_status run_passes(const uint32_t* ki, const uint32_t* vi, uint32_t* const (&kb)[2],
+template <class P, class K>
+gs_status run_passes(const K* ki, const uint32_t* vi, K* const (&kb)[2],
                      uint32_t* const (&vb)[2], uint32_t n, const uint32_t* d_n, int bits,
                      uint32_t* hist, int* result_in_b, hipStream_t s) {
   const uint32_t nb = P::chunks(n), stride = row_stride(nb);
@@ -790,7 +800,7 @@ gs_status run_passes(const uint32_t* ki, const uint32_t* vi, uint32_t* const (&k
   const bool raw = kMayRaw && nb <= kRawChunks;
   int out = 0;
   for (int shift = 0; shift < bits; shift += P::BITS) {
-    hipLaunchKernelGGL(k_radix_hist<P>, dim3(nb), dim3(P::THREADS), 0, s, ki, n, d_n, shift,
+    hipLaunchKernelGGL((k_radix_hist<P, K>), dim3(nb), dim3(P::THREADS), 0, s, ki, n, d_n, shift,
                        stride, hist);
     GS_LAUNCHED("radix_hist");
     if (!raw) {
@@ -798,7 +808,7 @@ gs_status run_passes(const uint32_t* ki, const uint32_t* vi, uint32_t* const (&k
                          d_n);
       GS_LAUNCHED("digit_rows");
     }
-    auto scatter = raw ? k_radix_scatter<kMayRaw, P> : k_radix_scatter<false, P>;
+    auto scatter = raw ? k_radix_scatter<kMayRaw, P, K> : k_radix_scatter<false, P, K>;
     hipLaunchKernelGGL(scatter, dim3(nb), dim3(P::THREADS), 0, s, ki, vi, kb[out], vb[out], n,
                        d_n, shift, stride, (const uint32_t*)hist);
     GS_LAUNCHED("radix_scatter");
@@ -868,10 +878,10 @@ gs_status scan_tile_counts(Ctx* ctx, SortScratch& ss, const uint32_t* sidx, cons
   return GS_OK;
 }
 
-gs_status sort_pairs_u32(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const uint32_t* vin,
-                         uint32_t* kA, uint32_t* vA, uint32_t* kB, uint32_t* vB, uint32_t n,
-                         const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s,
-                         uint32_t* spare, size_t spare_words) {
+gs_status sort_pairs(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const uint32_t* vin,
+                     uint32_t* kA, uint32_t* vA, uint32_t* kB, uint32_t* vB, uint32_t n,
+                     const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s,
+                     uint32_t* spare, size_t spare_words) {
   *result_in_b = 0;
   if (n == 0) return GS_OK;
   gs_status st = sort_reserve(ctx, ss, n, s);
@@ -893,16 +903,37 @@ gs_status sort_pairs_u32(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const u
   return run_passes<PassLarge>(kin, vin, kb, vb, n, d_n, bits, hist, result_in_b, s);
 }
 
+gs_status sort_pairs(Ctx* ctx, SortScratch& ss, const uint16_t* kin, const uint32_t* vin,
+                     uint16_t* kA, uint32_t* vA, uint16_t* kB, uint32_t* vB, uint32_t n,
+                     const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s) {
+  *result_in_b = 0;
+  if (n == 0) return GS_OK;
+  gs_status st = sort_reserve(ctx, ss, n, s);
+  if (st != GS_OK) return st;
+  auto* hist = (uint32_t*)ss.hist.p;
+  uint16_t* const kb[2] = {kA, kB};
+  uint32_t* const vb[2] = {vA, vB};
+  return n <= kSmallSort
+             ? run_passes<PassSmall>(kin, vin, kb, vb, n, d_n, bits, hist, result_in_b, s)
+             : run_passes<PassLarge>(kin, vin, kb, vb, n, d_n, bits, hist, result_in_b, s);
+}
+
 gs_status launch_emit(const ViewTable& vt, Frame& f, const uint32_t* sidx, const uint32_t* srx,
                       const uint32_t* sry, uint32_t count, uint32_t* overflow, uint32_t* d_K,
                       hipStream_t s) {
   if (count == 0) return GS_OK;
   const size_t cap_bytes = f.tkey[0].cap < f.tval[0].cap ? f.tkey[0].cap : f.tval[0].cap;
   const uint32_t cap = (uint32_t)(cap_bytes / sizeof(uint32_t));
-  hipLaunchKernelGGL(k_emit, dim3((count + 255) / 256), dim3(256), 0, s, vt, sidx, srx,
-                     sry, (const uint32_t*)f.offs.p, count, cap, (uint32_t*)f.tkey[0].p,
+  auto go = [&](auto kern, auto* tkey) {
+    hipLaunchKernelGGL(kern, dim3((count + 255) / 256), dim3(256), 0, s, vt, sidx, srx,
+                     sry, (const uint32_t*)f.offs.p, count, cap, tkey,
                      (uint32_t*)f.tval[0].p, overflow, d_K, (uint2*)f.ranges.p,
                      (uint32_t)f.vt.total_tiles, (uint32_t*)f.order.p);
+  };
+  if (f.short_keys())
+    go(k_emit<uint16_t>, (uint16_t*)f.tkey[0].p);
+  else
+    go(k_emit<uint32_t>, (uint32_t*)f.tkey[0].p);
   GS_LAUNCHED("emit");
   return GS_OK;
 }
@@ -910,8 +941,14 @@ gs_status launch_emit(const ViewTable& vt, Frame& f, const uint32_t* sidx, const
 gs_status launch_ranges(Frame& f, uint32_t n_rec, const uint32_t* d_K, hipStream_t s) {
   if (n_rec == 0) return GS_OK;
   const uint32_t quads = (n_rec + 3) / 4;
-  hipLaunchKernelGGL(k_ranges, dim3((quads + 255) / 256), dim3(256), 0, s,
-                     (const uint32_t*)f.tkey[f.tkey_sel].p, n_rec, d_K, (uint2*)f.ranges.p);
+  auto go = [&](auto kern, auto* tkey) {
+    hipLaunchKernelGGL(kern, dim3((quads + 255) / 256), dim3(256), 0, s, tkey, n_rec, d_K,
+                       (uint2*)f.ranges.p);
+  };
+  if (f.short_keys())
+    go(k_ranges<uint16_t>, (const uint16_t*)f.tkey[f.tkey_sel].p);
+  else
+    go(k_ranges<uint32_t>, (const uint32_t*)f.tkey[f.tkey_sel].p);
   GS_LAUNCHED("ranges");
   return GS_OK;
 }
@@ -955,9 +992,15 @@ gs_status launch_tile_order(Frame& f, hipStream_t s) {
 
 gs_status launch_export_keys(Frame& f, uint64_t* dst, hipStream_t s) {
   if (f.K == 0) return GS_OK;
-  hipLaunchKernelGGL(k_export_keys, dim3((unsigned)((f.K + 255) / 256)), dim3(256), 0, s,
-                     (const uint32_t*)f.tkey[f.tkey_sel].p, (const uint32_t*)f.tval[f.tkey_sel].p,
-                     (const uint32_t*)f.dkey.p, (uint32_t)f.K, dst);
+  auto go = [&](auto kern, auto* tkey) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)((f.K + 255) / 256)), dim3(256), 0, s, tkey,
+                       (const uint32_t*)f.tval[f.tkey_sel].p, (const uint32_t*)f.dkey.p,
+                       (uint32_t)f.K, dst);
+  };
+  if (f.short_keys())
+    go(k_export_keys<uint16_t>, (const uint16_t*)f.tkey[f.tkey_sel].p);
+  else
+    go(k_export_keys<uint32_t>, (const uint32_t*)f.tkey[f.tkey_sel].p);
   GS_LAUNCHED("export_keys");
   return GS_OK;
 }
