@@ -75,13 +75,16 @@ __device__ inline uint32_t classify(const DensityCfg& c, long long i) {
 
 __device__ inline uint32_t popc(unsigned long long b) { return (uint32_t)__popcll(b); }
 
-__global__ __launch_bounds__(kDB) void k_density_count(DensityCfg c, uint4* __restrict__ tot) {
+// Also leaves every Gaussian's class in flags (when given) for the writing kernel.
+__global__ __launch_bounds__(kDB) void k_density_count(DensityCfg c, uint4* __restrict__ tot,
+                                                       uint8_t* __restrict__ flags) {
   __shared__ uint32_t sh[kDW][4];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t a = 0, b = 0, d = 0, e = 0;
   for (int k = 0; k < kDI; ++k) {
     const long long i = (long long)blockIdx.x * kDG + k * kDB + threadIdx.x;
     const uint32_t f = i < c.n ? classify(c, i) : 0u;
+    if (flags != nullptr && i < c.n) flags[i] = (uint8_t)f;
     a += popc(__ballot((f & kKeep) != 0));
     b += popc(__ballot((f & kClone) != 0));
     d += popc(__ballot((f & kChild) != 0));
@@ -175,59 +178,73 @@ struct ApplyArgs {
   gs_params out[3];            // the same of the densified set (n_out entries)
   int32_t* src;                // optional source index per output
   const uint4* off;            // block offsets; off[nb] = totals
+  const uint8_t* flags;        // classes of the Gaussians, or null: classify again
   int nb, rows, n_split;
   uint32_t k0, k1;             // Philox key
 };
 
-constexpr int kRowsAhead = 4;  // rows whose loads a thread issues before its first store
+constexpr int kRowsAhead = 2;  // rows whose loads a thread issues before its first store
+constexpr int kRowsPerBlock = 6;  // rows that a block writes, about
 constexpr int kOut = 5;        // outputs per thread and run: 1280, a block's in one run as a rule
 
 // Bound by memory: every row of the parameters and both moments is read and written
-// once (24 B per parameter).  A block classifies its 1024 Gaussians again (cheap: five
-// values each), lists its kept originals, clones and split parents in LDS, and then
+// once (24 B per parameter).  A block reads the classes of its 1024 Gaussians (or
+// classifies them again), lists its kept originals, clones and split parents in LDS, and then
 // moves whole rows of all its outputs together: consecutive threads take consecutive
 // outputs, whose sources ascend, so both sides are coalesced, and a thread keeps its
 // outputs over all rows with kOut x kRowsAhead loads in flight.  blockIdx.y picks the set
-// (parameters, first, second moment) and one of `rsplit` runs of its rows, so that small
-// sets still fill the chip.  (One thread per Gaussian walking all 3 x 59 rows, a row's
-// load waiting for the row before it, took 1528 us for 1M Gaussians at degree 3; the
-// three lists moved one after the other 490 us.)
+// (parameters, first, second moment) and one of `rsplit` runs of its rows.  Short runs: the
+// blocks in flight then stream a few rows and not all 59 (1M Gaussians at degree 3: whole
+// sets per block 404 us, 395 with the classes read; runs of 10 rows 309, of 6 rows 290 (4.9
+// TB/s), of 4 rows 292; one thread per Gaussian walking all 3 x 59 rows, a row's load
+// waiting for the row before it, took 1528; the three lists moved one after the other 490).
 __global__ __launch_bounds__(kDB) void k_density_apply(DensityCfg c, ApplyArgs a, int rsplit) {
-  __shared__ uint32_t sh[kDW][3];
+  __shared__ uint32_t sh[kDI][kDW][3];
   __shared__ uint16_t list[3][kDG];  // offsets in the block: kept, clones, split parents
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   const uint4 tot = a.off[a.nb];
   const uint4 bo = a.off[blockIdx.x];
+  uint32_t f[kDI];
+#pragma unroll
+  for (int k = 0; k < kDI; ++k) {
+    const long long i = (long long)blockIdx.x * kDG + k * kDB + threadIdx.x;
+    f[k] = i >= c.n ? 0u : (a.flags != nullptr ? a.flags[i] : classify(c, i));
+  }
+#pragma unroll
+  for (int k = 0; k < kDI; ++k) {
+    const uint32_t t0 = popc(__ballot((f[k] & kKeep) != 0));
+    const uint32_t t1 = popc(__ballot((f[k] & kClone) != 0));
+    const uint32_t t2 = popc(__ballot((f[k] & kChild) != 0));
+    if (lane == 0) {
+      sh[k][w][0] = t0;
+      sh[k][w][1] = t1;
+      sh[k][w][2] = t2;
+    }
+  }
+  __syncthreads();
   uint32_t n0 = 0, n1 = 0, n2 = 0;  // entries of the three lists so far
+#pragma unroll
   for (int k = 0; k < kDI; ++k) {
     const uint32_t li = k * kDB + threadIdx.x;
-    const long long i = (long long)blockIdx.x * kDG + li;
-    const uint32_t f = i < c.n ? classify(c, i) : 0u;
-    const unsigned long long b0 = __ballot((f & kKeep) != 0);
-    const unsigned long long b1 = __ballot((f & kClone) != 0);
-    const unsigned long long b2 = __ballot((f & kChild) != 0);
-    if (lane == 0) {
-      sh[w][0] = popc(b0);
-      sh[w][1] = popc(b1);
-      sh[w][2] = popc(b2);
-    }
-    __syncthreads();
     uint32_t p0 = n0, p1 = n1, p2 = n2;
+#pragma unroll
     for (int q = 0; q < kDW; ++q) {
       if (q < w) {
-        p0 += sh[q][0];
-        p1 += sh[q][1];
-        p2 += sh[q][2];
+        p0 += sh[k][q][0];
+        p1 += sh[k][q][1];
+        p2 += sh[k][q][2];
       }
-      n0 += sh[q][0];
-      n1 += sh[q][1];
-      n2 += sh[q][2];
+      n0 += sh[k][q][0];
+      n1 += sh[k][q][1];
+      n2 += sh[k][q][2];
     }
-    __syncthreads();
-    if (f & kKeep) list[0][p0 + popc(b0 & below)] = (uint16_t)li;
-    if (f & kClone) list[1][p1 + popc(b1 & below)] = (uint16_t)li;
-    if (f & kChild) list[2][p2 + popc(b2 & below)] = (uint16_t)li;
+    const unsigned long long b0 = __ballot((f[k] & kKeep) != 0);
+    const unsigned long long b1 = __ballot((f[k] & kClone) != 0);
+    const unsigned long long b2 = __ballot((f[k] & kChild) != 0);
+    if (f[k] & kKeep) list[0][p0 + popc(b0 & below)] = (uint16_t)li;
+    if (f[k] & kClone) list[1][p1 + popc(b1 & below)] = (uint16_t)li;
+    if (f[k] & kChild) list[2][p2 + popc(b2 & below)] = (uint16_t)li;
   }
   __syncthreads();
   const int set = (int)blockIdx.y / rsplit, part = (int)blockIdx.y % rsplit;
@@ -393,21 +410,31 @@ static DensityCfg density_cfg(const gs_params& p, const gs_density_stats& st,
   return c;
 }
 
+static size_t density_bytes(int nb) { return sizeof(uint4) * (2 * (size_t)nb + 1); }
+
+// Where the classes of n Gaussians go, behind the offsets; null without room.
+static uint8_t* density_flags(const Ctx* ctx, int nb, long long n) {
+  return ctx->dens_blk.cap >= density_bytes(nb) + (size_t)n
+             ? (uint8_t*)ctx->dens_blk.p + density_bytes(nb)
+             : nullptr;
+}
+
 gs_status densify_count(Ctx* ctx, const gs_params& p, const gs_density_stats& st,
                         const gs_density_opts& o, gs_density_info* info, hipStream_t s) {
   const long long n = p.n;
   const int nb = (int)((n + kDG - 1) / kDG);
   const DensityCfg c = density_cfg(p, st, o);
-  // block totals [nb], offsets [nb + 1]
-  const size_t bytes = sizeof(uint4) * (2 * (size_t)nb + 1);
-  gs_status stt = buf_ensure(ctx, ctx->dens_blk, bytes, s);
+  // block totals [nb], offsets [nb + 1], and the classes where there is room for them
+  gs_status stt = buf_ensure(ctx, ctx->dens_blk, density_bytes(nb) + (size_t)n, s);
+  if (stt != GS_OK) stt = buf_ensure(ctx, ctx->dens_blk, density_bytes(nb), s);
   if (stt != GS_OK) return stt;
   if (ctx->dens_host == nullptr)
     GS_HIP(hipHostMalloc((void**)&ctx->dens_host, sizeof(uint4), hipHostMallocDefault));
   uint4* tot = (uint4*)ctx->dens_blk.p;
   uint4* off = tot + nb;
   if (nb > 0) {
-    hipLaunchKernelGGL(k_density_count, dim3(nb), dim3(kDB), 0, s, c, tot);
+    hipLaunchKernelGGL(k_density_count, dim3(nb), dim3(kDB), 0, s, c, tot,
+                       density_flags(ctx, nb, n));
     GS_LAUNCHED("density_count");
   }
   hipLaunchKernelGGL(k_density_scan, dim3(1), dim3(1024), 0, s, (const uint4*)tot, nb, off);
@@ -452,13 +479,13 @@ gs_status densify_apply(Ctx* ctx, const gs_params& p, const gs_params& m, const 
   a.out[2] = v_out;
   a.src = src_index;
   a.off = off;
+  a.flags = density_flags(ctx, nb, p.n);
   a.nb = nb;
   a.rows = 11 + (p.sh_degree + 1) * (p.sh_degree + 1) * 3;
   a.n_split = o.n_split;
   a.k0 = (uint32_t)o.seed;
   a.k1 = (uint32_t)(o.seed >> 32);
-  // rows are split over enough blocks to fill the chip (about 2048 resident ones)
-  const int rsplit = std::max(1, std::min(a.rows / kRowsAhead, 2048 / (3 * nb)));
+  const int rsplit = std::max(1, a.rows / kRowsPerBlock);
   hipLaunchKernelGGL(k_density_apply, dim3(nb, 3 * rsplit), dim3(kDB), 0, s, c, a, rsplit);
   GS_LAUNCHED("density_apply");
   return GS_OK;

@@ -3,7 +3,7 @@
 // Data layout in HBM (per frame of V views over N Gaussians):
 //   splat   float4[V*N*3]  per (view, Gaussian): {A, B, C, opacity},
 //                          {int(floor(mx)), int(floor(my)), 0.5-frac(mx), 0.5-frac(my)},
-//                          {r, g, b, depth}
+//                          {r, g, b, half-widths of the alpha >= 1/255 box (2 x fp16)}
 //   rect    uint2[V*N]     tile rectangle, x0 | y0 << 16 and x1 | y1 << 16
 //   dkey    u32[V*N]       float32 depth bits, 0xffffffff when untouched
 //   clampm  u8[V*N]        SH clamp mask (bit c set: channel c clamped at 0)
@@ -13,7 +13,8 @@
 //   tval    u32[K]         view*N + gid of each record
 //   ranges  uint2[tiles]   [start, end) per global tile
 //   finalT  f32[P], ncon u32[P]   per pixel over all views
-//   acc     f32[V][9][N]   screen-space gradient accumulators
+//   acc     f32[V][N][8], then f32[V][N][4]   screen-space gradient accumulators (below)
+//   order   u32[tiles + 512]  tiles, longest list first, and the counters that place them
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -35,7 +36,7 @@ constexpr int kOrderWords = 512;  // tile order: 256 class counts, 256 cursors
 // dL/d(r, g, b) + 1 pad float.  The projection backward's geometry and colour
 // kernels each read (and clear) only their own array.
 // Largest record count of a frame: the sort kernels index records with 32-bit
-// integers and round grids up to 4096-record chunks, so the count stays 2^20
+// integers and round grids up to chunks of at most 8192 records, so the count stays 2^20
 // below 2^32 (every index + chunk offset then fits).
 constexpr uint64_t kMaxRecords = 0xFFF00000ull;
 
@@ -168,7 +169,7 @@ struct Ctx {
   int cu_count = 0;
   hipDeviceProp_t prop;
   struct LossScratch* loss_scratch = nullptr;  // workspace of eager gs_loss_grad calls
-  DevBuf dens_blk;                 // gs_densify: block totals and offsets
+  DevBuf dens_blk;                 // gs_densify: block totals, offsets and the Gaussians' classes
   uint32_t* dens_host = nullptr;   // gs_densify: pinned read-back of the totals
   DevBuf iso_blk;                  // gs_iso_extract: block totals and offsets
   DevBuf ray_blk;                  // gs_raycast: cell classes (guarded by ray_mutex)

@@ -313,3 +313,26 @@ def test_tiles_in_length_order(P, ctx, views, size, tile):
     for a, b in zip(got.tensors(), want.tensors()):
         assert rel_l2(a.cpu().numpy(), b.cpu().numpy()) < 1e-5
     frame.release()
+
+
+@pytest.mark.parametrize("n,degree", [(1, 0), (4096, 1), (5121, 2), (70_001, 3)])
+def test_densify_with_and_without_room_for_classes(P, ctx, n, degree):
+    """The writing pass reading the counting pass's classes, and (in a context whose scratch
+    holds the offsets only) classifying again: equal; children and clones among them."""
+    from paper_2509_05216_amd import density as D
+    g = torch.Generator("cuda").manual_seed(n)
+    r = lambda *s: torch.rand(s, device="cuda", generator=g)  # noqa: E731
+    rows = 3 * (degree + 1) ** 2
+    p, m, v = (P.Params(r(3, n), r(3, n) * 2 - 5, r(4, n) - 0.5, r(n) * 6 - 4, r(rows, n), degree)
+               for _ in range(3))
+    st = D.DensityStats(r(n) ** 3 * 2e-3, torch.ones(n, dtype=torch.int32, device="cuda"),
+                        torch.zeros(n, dtype=torch.int32, device="cuda"))
+    small = P.Context(0, mem_budget=4096)
+    a = D.densify(ctx, p, m, v, st, 2.5, seed=5, want_src=True)
+    b = D.densify(small, p, m, v, st, 2.5, seed=5, want_src=True)
+    assert a[3] == b[3] and (n < 1000 or (a[3]["cloned"] and a[3]["split"]))
+    assert torch.equal(a[4], b[4])
+    for x, y in zip(a[:3], b[:3]):
+        for t, u in zip(x.tensors(), y.tensors()):
+            assert torch.equal(t, u)
+    small.close()
