@@ -938,24 +938,28 @@ gs_status forward_stages(Ctx* ctx, Frame& f, const ParamsDev& pd, hipStream_t s,
   if (st != GS_OK) return st;
   // 2. (view, Gaussian) entries in (depth bits, index) order
   int in_b = 0;
-  {
-    StageTimer tm(ctx, ST_DEPTH_SORT, s);
-    st = sort_pairs(ctx, f.ss, (const uint32_t*)f.dkey.p, nullptr, (uint32_t*)f.dkw[0].p,
-                        (uint32_t*)f.sidx[0].p, (uint32_t*)f.dkw[1].p, (uint32_t*)f.sidx[1].p,
-                        vn, nullptr, 32, &in_b, s);
-  }
-  if (st != GS_OK) return st;
+  const bool few = few_entries(vn);
   uint32_t* words = (uint32_t*)f.words.p;
-  st = launch_visible_count(f.ss, vn, words + kWordVisible, s);
-  if (st != GS_OK) return st;
-  f.sidx_sel = in_b;
-  const uint32_t* sidx = (const uint32_t*)f.sidx[in_b].p;
-  // 3. record offsets and the total K; the depth sort's key buffers are free now
-  // and take the rectangles in depth order (x0|y0 words, x1|y1 words)
+  // the depth sort's key buffers, free after it, take the rectangles in depth order (x0|y0
+  // words, x1|y1 words)
   uint64_t* d_total = (uint64_t*)(words + kWordTotal);
   uint32_t* srx = (uint32_t*)f.dkw[0].p;
   uint32_t* sry = (uint32_t*)f.dkw[1].p;
   {
+    StageTimer tm(ctx, ST_DEPTH_SORT, s);
+    st = few ? launch_few_entries((const uint32_t*)f.dkey.p, (const uint2*)f.rect.p, vn,
+                                  (uint32_t*)f.sidx[0].p, (uint32_t*)f.offs.p, srx, sry,
+                                  words + kWordVisible, d_total, s)
+             : sort_pairs(ctx, f.ss, (const uint32_t*)f.dkey.p, nullptr, (uint32_t*)f.dkw[0].p,
+                          (uint32_t*)f.sidx[0].p, (uint32_t*)f.dkw[1].p, (uint32_t*)f.sidx[1].p,
+                          vn, nullptr, 32, &in_b, s);
+  }
+  if (st == GS_OK && !few) st = launch_visible_count(f.ss, vn, words + kWordVisible, s);
+  if (st != GS_OK) return st;
+  f.sidx_sel = in_b;
+  const uint32_t* sidx = (const uint32_t*)f.sidx[in_b].p;
+  // 3. record offsets and the total K
+  if (!few) {
     StageTimer tm(ctx, ST_SCAN, s);
     st = scan_tile_counts(ctx, f.ss, sidx, (const uint2*)f.rect.p, vn, (uint32_t*)f.offs.p, srx,
                           sry, d_total, s);

@@ -342,6 +342,12 @@ gs_status sort_pairs(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const uint3
 gs_status sort_pairs(Ctx* ctx, SortScratch& ss, const uint16_t* kin, const uint32_t* vin,
                      uint16_t* kA, uint32_t* vA, uint16_t* kB, uint32_t* vB, uint32_t n,
                      const uint32_t* d_n, int bits, int* result_in_b, hipStream_t s);
+// Whether launch_few_entries takes n entries: their depth order (sidx), visible count,
+// record offsets and total, and their rectangles in that order, in two launches.
+bool few_entries(uint32_t n);
+gs_status launch_few_entries(const uint32_t* dkey, const uint2* rect, uint32_t n, uint32_t* sidx,
+                             uint32_t* offs, uint32_t* srx, uint32_t* sry, uint32_t* visible,
+                             uint64_t* total, hipStream_t s);
 // Tile counts of the depth-ordered entries, scanned into record offsets; the
 // entries' rectangles are also written in that order (srx, sry: the two halves)
 // so the emission reads them coalesced.

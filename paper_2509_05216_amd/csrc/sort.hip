@@ -392,6 +392,35 @@ __device__ inline void digit_row(const uint32_t* __restrict__ hist, uint32_t str
 // pairs 29.3 -> 23.4 us on average, over 16M to 42M 112 -> 92.
 constexpr uint32_t kAndXnor = 0xF0 & ~(0xCC ^ 0xAA);  // bitop3 table of a & ~(b ^ c)
 
+// Ranks of a wave's keys among its keys of the same digit, in index order, on top of the
+// wave's counts cnt, which they join.  Lanes with the same digit: for every bit, the ballot
+// of the bit where the lane's bit is set, its complement where it is clear, on the two
+// 32-bit halves (sbit: the bit sign-extended, 0 or all ones; p & ~(ballot ^ sbit) is one
+// three-operand instruction).  All of them read the wave's count of the digit, and the
+// last adds theirs.
+template <int BITS, int ITEMS>
+__device__ inline void rank_keys(const uint32_t (&key)[ITEMS], int shift, uint16_t* cnt,
+                                 uint32_t (&rank)[ITEMS]) {
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const uint32_t d = __builtin_amdgcn_ubfe(key[j], shift, BITS);
+    uint32_t plo = ~0u, phi = ~0u;
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+      const uint32_t sbit = (uint32_t)__builtin_amdgcn_sbfe((int)key[j], shift + b, 1);
+      const uint64_t bb = __builtin_amdgcn_ballot_w64(sbit != 0);
+      plo = __builtin_amdgcn_bitop3_b32(plo, (uint32_t)bb, sbit, kAndXnor);
+      phi = __builtin_amdgcn_bitop3_b32(phi, (uint32_t)(bb >> 32), sbit, kAndXnor);
+    }
+    const uint32_t old = cnt[d];
+    rank[j] = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, old));
+    const uint32_t now = old + __popc(plo) + __popc(phi);
+    __builtin_amdgcn_wave_barrier();  // every lane has read before the last one writes
+    if (rank[j] + 1 == now) cnt[d] = (uint16_t)now;
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 template <bool RAW, class P, class K>
 __global__ __launch_bounds__(P::THREADS) void k_radix_scatter(
     const K* __restrict__ kin, const uint32_t* __restrict__ vin, K* __restrict__ kout,
@@ -444,29 +473,7 @@ __global__ __launch_bounds__(P::THREADS) void k_radix_scatter(
     }
   }
   __syncthreads();
-  // Ranking, in index order.  Lanes with the same digit: for every bit, the ballot of the
-  // bit where the lane's bit is set, its complement where it is clear, on the two 32-bit
-  // halves (sbit: the bit sign-extended, 0 or all ones; p & ~(ballot ^ sbit) is one
-  // three-operand instruction).  All of them read the wave's count of the digit, and the
-  // last adds theirs.
-#pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    const uint32_t d = __builtin_amdgcn_ubfe(key[j], shift, P::BITS);
-    uint32_t plo = ~0u, phi = ~0u;
-#pragma unroll
-    for (int b = 0; b < P::BITS; ++b) {
-      const uint32_t sbit = (uint32_t)__builtin_amdgcn_sbfe((int)key[j], shift + b, 1);
-      const uint64_t bb = __builtin_amdgcn_ballot_w64(sbit != 0);
-      plo = __builtin_amdgcn_bitop3_b32(plo, (uint32_t)bb, sbit, kAndXnor);
-      phi = __builtin_amdgcn_bitop3_b32(phi, (uint32_t)(bb >> 32), sbit, kAndXnor);
-    }
-    const uint32_t old = cnt[wave][d];
-    rank[j] = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, old));
-    const uint32_t now = old + __popc(plo) + __popc(phi);
-    __builtin_amdgcn_wave_barrier();  // every lane has read before the last one writes
-    if (rank[j] + 1 == now) cnt[wave][d] = (uint16_t)now;
-    __builtin_amdgcn_wave_barrier();
-  }
+  rank_keys<P::BITS, ITEMS>(key, shift, cnt[wave], rank);
   __syncthreads();
   {
     // the block-local start of this thread's digits in every wave, and their global
@@ -524,6 +531,105 @@ __global__ __launch_bounds__(P::THREADS) void k_radix_scatter(
   for (int j = 0; j < ITEMS; ++j) {
     const uint32_t t = j * P::THREADS + threadIdx.x;
     if (t < nloc) vout[pos[j]] = stage[t];
+  }
+}
+
+// ---------------------------------------------------------------- few entries
+// Depth order of few (view, Gaussian) entries by counting: an entry's place is the number
+// of entries with a smaller key, or the same key and a smaller index.  A block places 64
+// entries (one per lane); its sixteen waves each count over a sixteenth of the keys, which
+// are uniform and come by scalar loads.  The entry, its rectangle and its tile count then go
+// straight to their place.  Two instructions a pair and n^2 pairs, but up to one block per
+// CU less than the latency of four sorting passes, the gather and the scans (eleven
+// launches, these two): whole forward pass of 1000 Gaussians at 256^2 113 -> 65 us, 4000
+// 117 -> 77, 12000 127 -> 105, 16384 205 -> 181.  (All in one block with the keys in
+// registers: 73, 81, 130, 192; keys from LDS, or a ballot and a scalar bit count per 64
+// pairs: 21 and 22 us instead of 18 for the counting of 10k.)
+constexpr int kRankWaves = 16;
+constexpr uint32_t kFewEntries = 16384;  // 256 blocks of 64
+
+__global__ __launch_bounds__(64 * kRankWaves) void k_rank_entries(
+    const uint32_t* __restrict__ dkey, const uint2* __restrict__ rect, uint32_t n,
+    uint32_t* __restrict__ sidx, uint32_t* __restrict__ counts, uint32_t* __restrict__ srx,
+    uint32_t* __restrict__ sry) {
+  __shared__ uint32_t part[kRankWaves][64];
+  const int lane = __lane_id();
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+  const uint32_t i0 = blockIdx.x * 64, i = i0 + lane;
+  const uint32_t mine = i < n ? dkey[i] : 0u;
+  const uint32_t per = (n + kRankWaves - 1) / kRankWaves;
+  const uint32_t lo = min(wave * per, n), hi = min(lo + per, n);
+  // before this block's entries equal keys count, after them they do not
+  const uint32_t mid0 = max(lo, min(hi, i0)), mid1 = max(lo, min(hi, i0 + 64));
+  uint32_t c = 0;
+#pragma unroll 16
+  for (uint32_t j = lo; j < mid0; ++j) c += dkey[j] <= mine ? 1u : 0u;
+#pragma unroll 4
+  for (uint32_t j = mid0; j < mid1; ++j) {
+    const uint32_t k = dkey[j];
+    c += k < mine || (k == mine && j < i) ? 1u : 0u;
+  }
+#pragma unroll 16
+  for (uint32_t j = mid1; j < hi; ++j) c += dkey[j] < mine ? 1u : 0u;
+  part[wave][lane] = c;
+  __syncthreads();
+  if (wave != 0 || i >= n) return;
+  uint32_t place = 0;
+#pragma unroll
+  for (int w = 0; w < kRankWaves; ++w) place += part[w][lane];
+  const uint2 r = rect[i];
+  const int x0 = (int)(r.x & 0xffffu), y0 = (int)(r.x >> 16);
+  const int x1 = (int)(r.y & 0xffffu), y1 = (int)(r.y >> 16);
+  sidx[place] = i;
+  srx[place] = r.x;
+  sry[place] = r.y;
+  counts[place] = (x1 < x0 || y1 < y0) ? 0u : (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1));
+}
+
+// Their record offsets (counts, in place), the total, and the touched entries' number, by
+// one block: sixteen consecutive entries a thread.
+__global__ __launch_bounds__(1024) void k_few_offsets(const uint32_t* __restrict__ dkey,
+                                                      uint32_t n, uint32_t* __restrict__ counts,
+                                                      uint32_t* __restrict__ visible,
+                                                      uint64_t* __restrict__ total) {
+  static_assert(kFewEntries == 1024 * 16, "sixteen entries a thread");
+  __shared__ uint64_t tmp[16];
+  const uint32_t i0 = threadIdx.x * 16;
+  uint32_t m[16], touched = 0;
+  uint64_t sum = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t i = i0 + 4 * k;
+    uint4 q = make_uint4(0u, 0u, 0u, 0u), d = make_uint4(~0u, ~0u, ~0u, ~0u);
+    if (i + 4 <= n) {
+      q = load4(counts + i);
+      d = load4(dkey + i);
+    } else if (i < n) {
+      q.x = counts[i];
+      d.x = dkey[i];
+      if (i + 1 < n) q.y = counts[i + 1], d.y = dkey[i + 1];
+      if (i + 2 < n) q.z = counts[i + 2], d.z = dkey[i + 2];
+    }
+    const uint32_t qq[4] = {q.x, q.y, q.z, q.w}, dd[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      m[4 * k + u] = qq[u];
+      sum += qq[u];
+      touched += (dd[u] >> 24) != 0xffu ? 1u : 0u;
+    }
+  }
+  // the number of touched entries (at most 2^14) above the records (at most 2^45)
+  uint64_t all;
+  const uint64_t base = block_exclusive_scan<16>(((uint64_t)touched << 48) | sum, tmp, all);
+  uint32_t run = (uint32_t)base;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    if (i0 + k < n) counts[i0 + k] = run;
+    run += m[k];
+  }
+  if (threadIdx.x == 0) {
+    *total = all & ((1ull << 48) - 1);
+    *visible = (uint32_t)(all >> 48);
   }
 }
 
@@ -916,6 +1022,19 @@ gs_status sort_pairs(Ctx* ctx, SortScratch& ss, const uint16_t* kin, const uint3
   return n <= kSmallSort
              ? run_passes<PassSmall>(kin, vin, kb, vb, n, d_n, bits, hist, result_in_b, s)
              : run_passes<PassLarge>(kin, vin, kb, vb, n, d_n, bits, hist, result_in_b, s);
+}
+
+bool few_entries(uint32_t n) { return n >= 1 && n <= kFewEntries; }
+
+gs_status launch_few_entries(const uint32_t* dkey, const uint2* rect, uint32_t n, uint32_t* sidx,
+                             uint32_t* offs, uint32_t* srx, uint32_t* sry, uint32_t* visible,
+                             uint64_t* total, hipStream_t s) {
+  hipLaunchKernelGGL(k_rank_entries, dim3((n + 63) / 64), dim3(64 * kRankWaves), 0, s, dkey, rect,
+                     n, sidx, offs, srx, sry);
+  GS_LAUNCHED("rank_entries");
+  hipLaunchKernelGGL(k_few_offsets, dim3(1), dim3(1024), 0, s, dkey, n, offs, visible, total);
+  GS_LAUNCHED("few_offsets");
+  return GS_OK;
 }
 
 gs_status launch_emit(const ViewTable& vt, Frame& f, const uint32_t* sidx, const uint32_t* srx,

@@ -170,6 +170,40 @@ def test_binning_at_sort_sizes(P, ctx, n):
     frame.release()
 
 
+@pytest.mark.parametrize("n,views", [(1, 1), (63, 1), (64, 1), (65, 2), (1025, 1), (4096, 3),
+                                     (8192, 2), (16383, 1), (16385, 1)])
+def test_binning_of_few_entries_with_equal_depths(P, ctx, n, views):
+    """Depth order of few entries (placed by counting up to 16384 of them) where many depths
+    are equal and some entries are off the view, against a stable sort (whole numbers:
+    equal), and the records' total."""
+    g = torch.Generator("cuda").manual_seed(n)
+    means = torch.rand((3, n), device="cuda", generator=g) * 3 - 1.5
+    means = (means * 4).round() / 4                    # few distinct places
+    p = P.Params(means, torch.full((3, n), -3.6, device="cuda"),
+                 torch.tensor([[1.], [0], [0], [0]], device="cuda").repeat(1, n).contiguous(),
+                 torch.zeros(n, device="cuda"), torch.zeros((3, n), device="cuda"), 0)
+    cams = P.orbit_cameras(4, 2.5, 60.0, 130, 70)[:views]
+    _, frame = P.render_fwd(ctx, p, cams, tile=16, lds_depth=64)
+    st = frame.stats()
+    rect = frame.export("rects").view(-1, 2).long() & 0xffffffff
+    depth = frame.export("depths").long() & 0xffffffff
+    x0, y0, x1, y1 = rect[:, 0] & 0xffff, rect[:, 0] >> 16, rect[:, 1] & 0xffff, rect[:, 1] >> 16
+    m = (x1 - x0 + 1).clamp(min=0) * (y1 - y0 + 1).clamp(min=0)
+    assert depth.numel() == n * views
+    assert st["n_visible"] == int((m > 0).sum()) and st["n_records"] == int(m.sum())
+    order = torch.sort(depth, stable=True)[1]
+    e = torch.repeat_interleave(order, m[order])
+    r = torch.arange(e.numel(), device="cuda") - torch.repeat_interleave(
+        m[order].cumsum(0) - m[order], m[order])
+    wide = (x1 - x0 + 1).clamp(min=1)[e]
+    tile = (e // n) * (9 * 5) + (y0[e] + r // wide) * 9 + x0[e] + r % wide
+    tile, by = torch.sort(tile, stable=True)
+    if e.numel():
+        assert torch.equal(frame.export("values").long(), e[by])
+        assert torch.equal(frame.export("keys"), (tile << 32) | depth[e[by]])
+    frame.release()
+
+
 @pytest.mark.parametrize("n,w,h,log_scale,fits", [
     (300_000, 2100, 2104, -5.6, True),     # 17-bit tile numbers
     (300_000, 4216, 4200, -6.6, True),     # 19-bit
