@@ -184,7 +184,7 @@ def wide_scales(P, ctx, params, cams, targets, steps, warmup, torch):
             "options": rows,
             "workload": ("kingsnake4m points, log-scales U(-5,-3) per axis (seeded), SH3; the "
                          "headline's 4 views per step, one hipGraph replay per step, the faster "
-                         "of tile 16 and tile 32 (persistent longest-first, LDS depth 256)")}
+                         "of tile 16 and tile 32 (longest list first, LDS depth 256)")}
 
 
 def run_steps(P, ctx, params, cams, targets, steps, warmup, tile, depth, torch, flags=0):
@@ -865,7 +865,7 @@ def main():
         how = "one hipGraph replay" if form == "batched_graph" else "eager launches"
         wl = (f"{args.workload}: {n} Gaussians on a {field}, SH3; "
               f"batched form: {views_desc} per step, {how} "
-              f"(projection, sort, persistent/grid blend, loss gradient, backward), tuned "
+              f"(projection, sort, blend, loss gradient, backward), tuned "
               f"tile {tune['best']['tile']}, LDS depth {tune['best']['lds_depth']}, "
               f"flags {tune['best']['flags']}")
     else:
