@@ -108,8 +108,8 @@ __global__ __launch_bounds__(kThreads) void k_scan_partials(uint64_t* partial, u
 // Down-sweep.  With few blocks each forms its carry-in by summing the totals of
 // the blocks before it (read from L2), so no separate scan of the totals is
 // launched, and the last block writes the grand total when d_total is given
-// (`per` totals stand for one block's elements); with many (prescanned), k_scan_partials has already turned the totals into
-// the carries and written the grand total.
+// (`per` totals stand for one block's elements); with many (prescanned), k_scan_partials
+// has already turned the totals into the carries and written the grand total.
 template <class F>
 __global__ __launch_bounds__(kThreads) void k_scan_down(F f, uint32_t n, const uint64_t* partial,
                                                         uint32_t* out, uint64_t* d_total,
@@ -166,7 +166,8 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(F f, uint32_t n, const u
 // different L2s; this bijection gives each XCD a contiguous run of chunks instead (the
 // last nchunks % 8 keep their place).  nchunks follows the number of keys there are, which
 // may be on the device, and not the capacity that the grid is launched for: with runs cut
-// from the capacity, 108M records in a capacity of 270M were sorted by 3.2 of the XCDs.
+// from the capacity, 216M records in a capacity of 270M were sorted by 6.4 of the
+// XCDs (scatter passes 429 -> 405 us on average).
 __device__ inline uint32_t xcd_chunk(uint32_t nchunks) {
   const uint32_t n8 = nchunks / 8;
   return blockIdx.x < 8 * n8 ? (blockIdx.x % 8) * n8 + blockIdx.x / 8 : blockIdx.x;
@@ -306,9 +307,9 @@ __global__ __launch_bounds__(P::THREADS) void k_radix_hist(const K* __restrict__
 }
 
 // Rows of the digit table: row d (stride words, a multiple of four) holds digit d's count
-// in every chunk that has keys, and the totals of the rows follow the table.  One block per digit turns
-// its row into the exclusive prefix over the chunks and writes the total; the scatter
-// itself scans the 256 totals.  One launch instead of the two of a scan over the whole
+// in every chunk that has keys, and the totals of the rows follow the table.  One block per
+// digit turns its row into the exclusive prefix over the chunks and writes the total; the
+// scatter itself scans the totals.  One launch instead of the two of a scan over the whole
 // table (passes over 16M and 42M keys: 7 us on average instead of 18).
 template <class P>
 __global__ __launch_bounds__(kThreads) void k_digit_rows(uint32_t* __restrict__ hist,
@@ -874,16 +875,17 @@ __global__ void k_visible_count(const uint32_t* __restrict__ hist, uint32_t stri
 }
 
 // Digit tables of up to this many chunks are summed by each scatter block itself instead
-// of scanned by a launch of their own (16-key passes: 17 chunks 9.5 us against 9.5 and 3 for
-// the launch, 147 chunks 20.5 against 12.6 and 3).
+// of scanned by a launch of their own (passes of 4 keys a thread: 20 chunks 5.0 us against
+// 4.5 and 2.9 for the launch, 63 chunks 7.0 against 4.8 and 2.9, 147 chunks 15.4 against 4.9
+// and 3.0).
 constexpr uint32_t kRawChunks = 64;
 
 inline uint32_t row_stride(uint32_t nb) { return row_quads(nb) * 4; }
 
 // Keys per thread of a sort of n pairs: a block's chain of ranking steps sets the time of
-// a small sort (a scatter pass with 4 instead of 16 keys a thread: 10k pairs 5.0 instead of
-// 9.6 us, 600k 9.8 instead of 12.5, 1M 9.7 instead of 11.1), the lengths of the digit runs
-// that it writes that of a large one.
+// a small sort (histogram and scatter with 4 instead of 16 keys a thread: 600k pairs 11.1
+// instead of 14.5 us, 1M 13.5 instead of 15.9), the lengths of the digit runs that it writes
+// that of a large one.
 constexpr uint32_t kSmallSort = 1u << 20;
 
 inline uint32_t sort_chunks(uint32_t n) {
