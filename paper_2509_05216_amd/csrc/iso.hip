@@ -595,7 +595,9 @@ __device__ inline uint32_t block_at(const int* i, int s, const int* n) {
 
 // The side of the level on which the interpolant at coordinates m s + b lies, from its
 // float32 evaluation, whose error is below 1e-5 of the cell's values and of the level;
-// kMixed where that cannot tell.
+// kMixed where that cannot tell, and for values outside the range in which it holds:
+// differences of corners overflow from about 1.7e38 on, and near 1e-38 the rounding stops
+// shrinking with the values.
 __device__ inline int quick_side(const VolDev& V, const CellGrid& G, double m, const double* s,
                                  const double* b) {
   int i[3];
@@ -614,7 +616,9 @@ __device__ inline int quick_side(const VolDev& V, const CellGrid& G, double m, c
   const float big =
       fmaxf(fmaxf(fmaxf(fabsf(e00[0]), fabsf(e00[1])), fmaxf(fabsf(e10[0]), fabsf(e10[1]))),
             fmaxf(fmaxf(fabsf(e01[0]), fabsf(e01[1])), fmaxf(fabsf(e11[0]), fabsf(e11[1]))));
-  return fabsf(f) > 1e-5f * (big + fabsf(V.iso)) ? (f < 0.f ? kBelow : kAbove) : kMixed;
+  const float scale = big + fabsf(V.iso);
+  if (!(fabsf(f) > 1e-5f * scale && scale > 1e-30f && big < 1e37f)) return kMixed;
+  return f < 0.f ? kBelow : kAbove;
 }
 
 // Place (in blocks of 16 x 16 pixels) of block L of a view.  Workgroups go to the eight XCDs

@@ -370,3 +370,39 @@ def test_densify_with_and_without_room_for_classes(P, ctx, n, degree):
         for t, u in zip(x.tensors(), y.tensors()):
             assert torch.equal(t, u)
     small.close()
+
+
+# ---------------------------------------------------------------- ray-cast at the limits of float32
+def _cast_and_check(P, vol, level, step, cams, lo=(-1.0, -1.0, -1.0), hi=(1.0, 1.0, 1.0)):
+    """One ray-cast against the float64 oracle's images, which it returns."""
+    from oracle import iso as OI
+    from paper_2509_05216_amd import iso
+    step, level = float(np.float32(step)), float(np.float32(level))
+    V = iso.Volume(torch.tensor(vol, device="cuda"), lo, hi)
+    imgs = iso.raycast(P.Context(0), V, [P.camera_from_dict(c) for c in cams], level, step)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        want = [OI.raycast(vol, lo, hi, level, c, step) for c in cams]
+    for img, w in zip(imgs, want):
+        got = img.cpu().numpy().astype(np.float64)
+        assert np.array_equal(np.isnan(got), np.isnan(w))
+        assert np.nanmax(np.abs(got - w)) < 1e-5
+    return want
+
+
+@pytest.mark.parametrize("shape,step", [((7, 6, 400), 0.005), ((9, 8, 7), 0.05)])
+@pytest.mark.parametrize("size,level", [
+    (3.2e38, 0.5),                  # differences of corners pass the largest float32
+    (2e38, -1e38), (5e36, 3e38),
+    (1e-42, 0.0), (3e-44, 0.0),     # subnormal: float32 rounds by a fixed amount
+    (1e-42, 2e-43), (1e-36, 0.0)])
+def test_raycast_of_very_large_and_subnormal_values(P, shape, step, size, level):
+    """Rays through volumes whose values leave the range in which a float32 sample's error
+    follows the size of the values, through cell classes (the long volume) and without."""
+    from oracle import camera as ocam
+    rng = np.random.default_rng(11)
+    vol = (rng.uniform(-1, 1, shape) * size).astype(np.float32)
+    assert np.isfinite(vol).all()
+    cams = [ocam.to_float32(c) for c in ocam.orbit_cameras(5, 2.5, 60.0, 13, 9)][1:3]
+    want = _cast_and_check(P, vol, level, step, cams)
+    assert any(w.max() > 0 for w in want) or abs(level) > size
