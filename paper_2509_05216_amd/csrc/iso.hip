@@ -593,11 +593,20 @@ __device__ inline uint32_t block_at(const int* i, int s, const int* n) {
   return __umul24(__umul24(i[2] >> s, n[1]) + (i[1] >> s), n[0]) + (i[0] >> s);
 }
 
+// Within 1e-6 of a cell's face a sample may belong to another cell than cell_of says (the
+// coordinates round by less than 1e-7, as the host checks).  Between finite cells that
+// changes nothing, but the cell that the sample belongs to may have corners that are not.
+constexpr float kFace = 0.499999f;
+__device__ inline float off_centre(const float* fr) {
+  return fmaxf(fmaxf(fabsf(fr[0] - 0.5f), fabsf(fr[1] - 0.5f)), fabsf(fr[2] - 0.5f));
+}
+
 // The side of the level on which the interpolant at coordinates m s + b lies, from its
 // float32 evaluation, whose error is below 1e-5 of the cell's values and of the level;
-// kMixed where that cannot tell, and for values outside the range in which it holds:
-// differences of corners overflow from about 1.7e38 on, and near 1e-38 the rounding stops
-// shrinking with the values.
+// kMixed where that cannot tell, and outside the range in which it holds (two terms of the
+// bound): differences of corners overflow from about 1.7e38 on, and near 1e-38 the rounding
+// stops shrinking with the values.  FACE: also kMixed beside a cell's face.
+template <bool FACE>
 __device__ inline int quick_side(const VolDev& V, const CellGrid& G, double m, const double* s,
                                  const double* b) {
   int i[3];
@@ -616,9 +625,18 @@ __device__ inline int quick_side(const VolDev& V, const CellGrid& G, double m, c
   const float big =
       fmaxf(fmaxf(fmaxf(fabsf(e00[0]), fabsf(e00[1])), fmaxf(fabsf(e10[0]), fabsf(e10[1]))),
             fmaxf(fmaxf(fabsf(e01[0]), fabsf(e01[1])), fmaxf(fabsf(e11[0]), fabsf(e11[1]))));
-  const float scale = big + fabsf(V.iso);
-  if (!(fabsf(f) > 1e-5f * scale && scale > 1e-30f && big < 1e37f)) return kMixed;
-  return f < 0.f ? kBelow : kAbove;
+  // infinite from 3.4e36 on, at least 1e-35
+  const float bound = fmaf((big + fabsf(V.iso)) * 100.f, 1e-7f, 1e-35f);
+  if (FACE && off_centre(fr) > kFace) return kMixed;
+  return fabsf(f) > bound ? (f < 0.f ? kBelow : kAbove) : kMixed;
+}
+
+// Whether the sample at coordinates m s + b is beside a face of its cell.
+__device__ inline bool beside_face(const CellGrid& G, double m, const double* s, const double* b) {
+  int i[3];
+  float fr[3];
+  cell_of(G, m, s, b, i, fr);
+  return off_centre(fr) > kFace;
 }
 
 // Place (in blocks of 16 x 16 pixels) of block L of a view.  Workgroups go to the eight XCDs
@@ -639,10 +657,12 @@ __device__ inline void ray_block(const RayView& c, uint32_t L, int& bx, int& by)
 // quick_side, and by the cell classes where they were built (same views: 2190 us without,
 // 568 with them, of which the classes 125); else all in float64.  Without classes bound by
 // the gathers' cache lines, with them by the latency of a ray's steps (23 blocks and 20
-// samples a wave on average, 116 and 161 in the longest) and float64 issue.
+// samples a wave on average, 116 and 161 in the longest) and float64 issue.  Five waves per
+// SIMD: left to itself the compiler takes registers for four (572 us instead of 546 for
+// those views, averages of two runs each).
 template <bool QUICK>
-__global__ __launch_bounds__(256) void k_raycast(VolDev V, RayViews rv, CellGrid G, double step,
-                                                 double hi0, double hi1, double hi2) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_raycast(
+    VolDev V, RayViews rv, CellGrid G, double step, double hi0, double hi1, double hi2) {
   const RayView& c = rv.v[blockIdx.y];
   int bx, by;
   ray_block(c, blockIdx.x, bx, by);
@@ -715,7 +735,7 @@ __global__ __launch_bounds__(256) void k_raycast(VolDev V, RayViews rv, CellGrid
         }
         if (cls == kMixed) {
           for (; k <= ke; ++k) {
-            int at = quick_side(V, G, (double)k, us, u0);
+            int at = quick_side<false>(V, G, (double)k, us, u0);
             if (at == kMixed) {
               const double f = value(tn + (double)k * step);
               at = f < 0.0 ? kBelow : (f >= 0.0 ? kAbove : kMixed);
@@ -731,6 +751,17 @@ __global__ __launch_bounds__(256) void k_raycast(VolDev V, RayViews rv, CellGrid
           k = ke + 1;
         }
         if (risen) {
+          // the two samples whose sides make the rise, where a neighbouring cell's values
+          // may have stood for theirs
+          if (beside_face(G, (double)(k - 1), us, u0) || beside_face(G, (double)k, us, u0)) {
+            const double f = value(tn + (double)k * step);
+            risen = f >= 0.0 && value(tn + (double)(k - 1) * step) < 0.0;
+            if (!risen) {
+              below = f < 0.0;
+              ++k;
+              continue;
+            }
+          }
           lo_t = tn + (double)(k - 1) * step;
           hi_t = tn + (double)k * step;
           break;
@@ -754,7 +785,7 @@ __global__ __launch_bounds__(256) void k_raycast(VolDev V, RayViews rv, CellGrid
       for (int it = 0; it < 10; ++it) {
         const double mid = 0.5 * (lo_t + hi_t);
         int at = kMixed;
-        if constexpr (QUICK) at = quick_side(V, G, mid, ut, uo);
+        if constexpr (QUICK) at = quick_side<true>(V, G, mid, ut, uo);
         if (at == kBelow || (at == kMixed && value(mid) < 0.0))
           lo_t = mid;
         else

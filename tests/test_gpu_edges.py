@@ -406,3 +406,23 @@ def test_raycast_of_very_large_and_subnormal_values(P, shape, step, size, level)
     cams = [ocam.to_float32(c) for c in ocam.orbit_cameras(5, 2.5, 60.0, 13, 9)][1:3]
     want = _cast_and_check(P, vol, level, step, cams)
     assert any(w.max() > 0 for w in want) or abs(level) > size
+
+
+@pytest.mark.parametrize("nz", [9, 400])
+@pytest.mark.parametrize("nx,nan_from,nan_to", [
+    (59, 30, 59),      # sample in cell 29; its coordinate by reciprocal falls into cell 28
+    (51, 0, 25)])      # sample in cell 24; by reciprocal in cell 25
+def test_raycast_beside_values_that_are_not_finite(P, nx, nan_from, nan_to, nz):
+    """A ray along a grid plane whose cells are finite on one side only: the cell of a sample
+    is that of the float64 division, whose NaN hides the surface."""
+    lo, hi, x0 = (-0.75, -1.0, -1.0), (1.0, 1.0, 1.0), 0.125
+    h = (hi[0] - lo[0]) / (nx - 1)
+    assert np.floor((x0 - lo[0]) / h) != np.floor((x0 - lo[0]) * (1.0 / h))
+    z = np.linspace(0, 1, nz, dtype=np.float32)[:, None, None]
+    vol = np.broadcast_to(z, (nz, 5, nx)).copy()
+    cam = dict(R=np.eye(3), t=np.array([-x0, 0.1, 2.0]), fx=10.0, fy=10.0, cx=0.5, cy=0.5,
+               width=1, height=1, z_near=0.2)
+    step = 0.05 if nz == 9 else 0.005
+    assert _cast_and_check(P, vol, 0.43, step, [cam], lo, hi)[0].max() > 0   # finite: a surface
+    vol[:, :, nan_from:nan_to] = np.nan
+    assert _cast_and_check(P, vol, 0.43, step, [cam], lo, hi)[0].max() == 0
