@@ -410,7 +410,8 @@ static void frame_delete(gs_frame* fr) {
 // frame: a program that takes a new one per step (the autograd form) otherwise spends
 // most of the step in the allocator and its device-wide waits (100k Gaussians, six
 // 397 x 301 views, forward and backward: 4.3 ms a step, of which the kernels take 1.2).
-// A pooled frame is idle (its release waited for it), so any stream may take it over,
+// A pooled frame is idle (its release waited for the device: calls on it may have used
+// several streams, and last_use names the last one only), so any stream may take it over,
 // and it holds the context no longer.  At most four frames of kPoolBytes together are
 // kept; they are freed with the context, and before an allocation fails for want of
 // budget or device memory.
@@ -481,17 +482,17 @@ static gs_frame* frame_new(Ctx* ctx, int64_t entries) {
   return fr;
 }
 
-static void frame_wait(gs_frame* fr) {
+// Waits for all work on the frame's device; false when that cannot be had (a stream that is
+// being captured, an earlier error).
+static bool frame_wait(gs_frame* fr) {
   (void)hipSetDevice(fr->ctx->device);
-  // every call that enqueues work on the frame's buffers records last_use after it
-  if (fr->last_use != nullptr)
-    (void)hipEventSynchronize(fr->last_use);
-  else
-    (void)hipDeviceSynchronize();
+  if (hipDeviceSynchronize() == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
 }
 
 void frame_destroy(gs_frame* fr) {
-  frame_wait(fr);
+  (void)frame_wait(fr);
   frame_delete(fr);
 }
 
@@ -1673,9 +1674,8 @@ gs_status gs_frame_export(gs_frame* frame, int32_t what, int32_t view, void* dst
 
 void gs_frame_release(gs_frame* frame) {
   if (frame == nullptr) return;
-  frame_wait(frame);
   Ctx* ctx = frame->ctx;
-  if (frame_pool_give(frame))
+  if (frame_wait(frame) && frame_pool_give(frame))
     ctx_release(ctx);  // the last release of a destroyed context frees the pool with it
   else
     frame_delete(frame);

@@ -278,7 +278,7 @@ struct Frame {
   int sidx_sel = 0;  // which of sidx holds the depth-sorted (view, Gaussian) indices
   bool acc_zeroed = false;
   size_t acc_zero_bytes = 0;  // how much of acc the last fill cleared (acc_zeroed)
-  bool settled = false;       // the last call on the frame recorded last_use after its work
+  bool settled = false;       // the last call on the frame went through (else it is not pooled)
   bool ordered = false;               // tiles are blended longest list first
   const uint32_t* tile_order = nullptr;  // blending order of the tiles (null: by id)
   DevBuf words;                       // kWordCount device words

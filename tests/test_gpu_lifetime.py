@@ -244,3 +244,30 @@ def test_released_frames_are_reused_and_given_back(P):
         assert torch.equal(a, b)
     assert c1.memory()[0] <= int(1.3 * one)
     f3.release()
+
+
+def test_release_waits_for_every_stream_of_the_frame(P):
+    """A frame used on two streams, the first still at work when it is released: the next
+    forward, which takes over its buffers, does not reach the first stream's results."""
+    ctx = P.Context(0)
+    one = P.Params.from_numpy(gsscenes.make_scene("tiny", n=6000).params)
+    two = P.Params.from_numpy(gsscenes.make_scene("iso1m", n=6000, G=96).params)
+    cams = _views(P, [(160, 96)] * 3)
+    _, frame = P.render_fwd(ctx, one, cams)
+    want = [frame.export(k) for k in ("splats", "rects")]
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(300_000_000)
+        got = [frame.export(k) for k in ("splats", "rects")]
+    with torch.cuda.stream(other):
+        frame.export("depths")
+    held = ctx.memory()[0]
+    frame.release()
+    _, again = P.render_fwd(ctx, two, cams)
+    torch.cuda.synchronize()
+    assert ctx.memory()[0] <= 1.2 * held        # the released frame's buffers, not new ones
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+    again.release()
+    ctx.close()
