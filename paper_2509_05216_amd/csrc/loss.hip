@@ -660,6 +660,11 @@ gs_status loss_reserve(Ctx* ctx, LossScratch& ls, const int* W, const int* H, in
   return buf_ensure(ctx, ls.part, pb, s, ls.last_use);
 }
 
+// Whether two arrays of na and nb floats share memory (null: no array).
+static bool meet(const float* a, size_t na, const float* b, size_t nb) {
+  return a != nullptr && b != nullptr && a < b + nb && b < a + na;
+}
+
 // Launches `go` on runs of consecutive views that fit the workspace together (grad: their
 // partials; without gradients all views at once).  Views that share an output, or read
 // what another writes, go one after the other.
@@ -678,9 +683,12 @@ static gs_status loss_groups(const LossScratch& ls, const float* const* x, const
       if (v1 > v0 && grad && used + plane > cap) break;
       float* d = grad && dl != nullptr ? dl[v1] : nullptr;
       bool apart = false;
-      for (int k = 0; k < lv.n; ++k)
-        apart |= (d != nullptr && (d == lv.dl[k] || d == lv.x[k] || d == lv.y[k])) ||
-                 (lv.dl[k] != nullptr && (lv.dl[k] == x[v1] || lv.dl[k] == y[v1]));
+      for (int k = 0; k < lv.n; ++k) {
+        const size_t ak = 3 * (size_t)lv.W[k] * lv.H[k], a1 = 3 * plane;
+        apart |= meet(d, a1, lv.dl[k], ak) || meet(d, a1, lv.x[k], ak) ||
+                 meet(d, a1, lv.y[k], ak) || meet(lv.dl[k], ak, x[v1], a1) ||
+                 meet(lv.dl[k], ak, y[v1], a1);
+      }
       if (apart) break;
       const int k = lv.n++;
       lv.x[k] = x[v1];

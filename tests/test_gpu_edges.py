@@ -426,3 +426,39 @@ def test_raycast_beside_values_that_are_not_finite(P, nx, nan_from, nan_to, nz):
     assert _cast_and_check(P, vol, 0.43, step, [cam], lo, hi)[0].max() > 0   # finite: a surface
     vol[:, :, nan_from:nan_to] = np.nan
     assert _cast_and_check(P, vol, 0.43, step, [cam], lo, hi)[0].max() == 0
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("kind", ["rendered", "target", "gradient"])
+def test_loss_of_views_whose_buffers_overlap(P, ctx, kind, noalloc):
+    """A view's gradient written over part of the next view's image, target or gradient: the
+    views are taken one after the other, so the next one reads (or writes) it as it is then."""
+    h, w = 61, 93
+    n, off = 3 * h * w, 1000
+    g = torch.Generator("cuda").manual_seed(5)
+    x0, x1, y0, y1 = (torch.rand((3, h, w), device="cuda", generator=g) for _ in range(4))
+    cams = [P.camera(np.eye(3), np.zeros(3), 200.0, 200.0, w / 2, h / 2, w, h)] * 2
+
+    def call(xs, ys, dl):
+        loss = torch.zeros(1, device="cuda")
+        P.loss_grad_into(ctx, xs, ys, cams, loss, dl, 0.2, noalloc=noalloc)
+        torch.cuda.synchronize()
+        return loss
+
+    buf = torch.zeros(n + off, device="cuda")
+    over, first = buf[:n].view(3, h, w), buf[off:].view(3, h, w)
+    d0, d1, e1 = (torch.zeros((3, h, w), device="cuda") for _ in range(3))
+    call([x0, x1], [y0, y1], [d0, d1])             # the first view's gradient, apart
+    if kind == "gradient":
+        call([x0, x1], [y0, y1], [first, over])
+        assert torch.equal(over, d1)               # the second view's is written last
+        assert torch.equal(buf[n:], d0.view(-1)[n - off:])
+        return
+    hit = (x1 if kind == "rendered" else y1).clone()
+    over.copy_(hit)
+    hit.view(-1)[off:] = d0.view(-1)[:n - off]     # what the second view finds
+    want = call([x0, hit if kind == "rendered" else x1], [y0, y1 if kind == "rendered" else hit],
+                [d0, e1])
+    got = call([x0, over if kind == "rendered" else x1],
+               [y0, y1 if kind == "rendered" else over], [first, d1])
+    assert torch.equal(first, d0) and torch.equal(d1, e1) and torch.equal(got, want)
