@@ -251,8 +251,10 @@ gs_status gs_render_fwd_multi(gs_ctx* ctx, const gs_params* params, const gs_cam
  * uses without stating it (SSIM is also one of its quality metrics, Sec. IV).
  * loss_out: device float (may be NULL); dl_dimg[v]: device [3][H_v][W_v]
  * (NULL: the loss value only).  The context's loss workspace grows to the
- * largest view seen; calls on one context must not overlap on different
- * streams (they share that workspace). */
+ * largest view seen, and while there is room to the views of a call together
+ * (up to 2^22 pixels, 36 bytes each); it is given back when another call on
+ * the context needs the memory.  Calls on one context must not overlap on
+ * different streams (they share that workspace). */
 gs_status gs_loss_grad(gs_ctx* ctx, const float* const* rendered,
                        const float* const* target, const gs_camera* cams,
                        int32_t n_views, float lambda_dssim, float* loss_out,

@@ -1,8 +1,10 @@
 // C ABI of the isogs library: contexts, device scratch, cameras and the
 // orchestration of the forward/backward passes on a caller's HIP stream.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <initializer_list>
 #include <new>
 
 #include "internal.h"
@@ -23,6 +25,24 @@ gs_status hip_fail(hipError_t e, const char* what) {
   return (e == hipErrorOutOfMemory) ? GS_ERR_NOMEM : GS_ERR_HIP;
 }
 
+static size_t padded(size_t bytes) { return (bytes + bytes / 8 + 4095) & ~(size_t)4095; }
+
+// Books a buffer's memory in and out.
+static void taken(Ctx* ctx, DevBuf& b, size_t bytes) {
+  std::lock_guard<std::mutex> lk(ctx->mem_mutex);
+  b.cap = bytes;
+  ctx->in_use += bytes;
+  if (ctx->in_use > ctx->peak) ctx->peak = ctx->in_use;
+}
+
+static void freed(Ctx* ctx, DevBuf& b) {
+  std::lock_guard<std::mutex> lk(ctx->mem_mutex);
+  ctx->in_use -= b.cap;
+  ctx->refused = 0;
+  b.p = nullptr;
+  b.cap = 0;
+}
+
 gs_status buf_ensure(Ctx* ctx, DevBuf& b, size_t bytes, hipStream_t s, hipEvent_t prior) {
   if (bytes <= b.cap) return GS_OK;
   if (ctx->capturing) {
@@ -30,16 +50,16 @@ gs_status buf_ensure(Ctx* ctx, DevBuf& b, size_t bytes, hipStream_t s, hipEvent_
               bytes);
     return GS_ERR_CAPACITY;
   }
-  size_t want = bytes + bytes / 8;
-  want = (want + 4095) & ~(size_t)4095;
-  // pooled frames give way to the budget and to the device's memory
+  const size_t want = padded(bytes);
+  // pooled frames and then optional scratch give way to the budget and to the device's memory
   auto over_budget = [&](size_t* after) {
     std::lock_guard<std::mutex> lk(ctx->mem_mutex);
     *after = ctx->in_use - b.cap + want;
     return ctx->budget != 0 && *after > ctx->budget;
   };
   size_t after = 0;
-  if (over_budget(&after) && !(frame_pool_trim(ctx) && !over_budget(&after))) {
+  if (over_budget(&after) && !(frame_pool_trim(ctx) && !over_budget(&after)) &&
+      !(scratch_trim(ctx) && !over_budget(&after))) {
     set_error("device scratch budget exceeded: need %zu bytes, budget %zu", after, ctx->budget);
     return GS_ERR_NOMEM;
   }
@@ -48,38 +68,64 @@ gs_status buf_ensure(Ctx* ctx, DevBuf& b, size_t bytes, hipStream_t s, hipEvent_
     GS_HIP(hipStreamSynchronize(s));
     if (prior != nullptr) GS_HIP(hipEventSynchronize(prior));
     GS_HIP(hipFree(b.p));
-    {
-      std::lock_guard<std::mutex> lk(ctx->mem_mutex);
-      ctx->in_use -= b.cap;
-    }
-    b.p = nullptr;
-    b.cap = 0;
+    freed(ctx, b);
   }
   hipError_t e = hipMalloc(&b.p, want);
-  if (e != hipSuccess && frame_pool_trim(ctx)) {
-    (void)hipGetLastError();
-    e = hipMalloc(&b.p, want);
-  }
+  for (auto trim : {frame_pool_trim, scratch_trim})
+    if (e != hipSuccess && trim(ctx)) {
+      (void)hipGetLastError();
+      e = hipMalloc(&b.p, want);
+    }
   if (e != hipSuccess) {
     b.p = nullptr;
     set_error("hipMalloc(%zu) failed: %s", want, hipGetErrorString(e));
     return GS_ERR_NOMEM;
   }
-  b.cap = want;
-  std::lock_guard<std::mutex> lk(ctx->mem_mutex);
-  ctx->in_use += want;
-  if (ctx->in_use > ctx->peak) ctx->peak = ctx->in_use;
+  taken(ctx, b, want);
   return GS_OK;
 }
 
-void buf_free(Ctx* ctx, DevBuf& b) {
-  if (b.p != nullptr) {
-    (void)hipFree(b.p);
+bool buf_try(Ctx* ctx, DevBuf& b, size_t bytes, hipStream_t s, hipEvent_t prior) {
+  if (bytes <= b.cap) return true;
+  if (ctx->capturing || stream_captured(s)) return false;
+  const size_t want = padded(bytes);
+  {
     std::lock_guard<std::mutex> lk(ctx->mem_mutex);
-    ctx->in_use -= b.cap;
+    if (ctx->budget != 0 && ctx->in_use + want > ctx->budget) return false;
+    if (ctx->refused != 0 && want >= ctx->refused) return false;
   }
-  b.p = nullptr;
-  b.cap = 0;
+  DevBuf grown;
+  if (hipMalloc(&grown.p, want) != hipSuccess) {
+    (void)hipGetLastError();
+    std::lock_guard<std::mutex> lk(ctx->mem_mutex);
+    ctx->refused = ctx->refused == 0 ? want : std::min(ctx->refused, want);
+    return false;
+  }
+  if (b.p != nullptr) {
+    if (hipStreamSynchronize(s) != hipSuccess ||
+        (prior != nullptr && hipEventSynchronize(prior) != hipSuccess)) {
+      (void)hipGetLastError();
+      (void)hipFree(grown.p);
+      return false;
+    }
+    buf_free(ctx, b);
+  }
+  b.p = grown.p;
+  taken(ctx, b, want);
+  return true;
+}
+
+void buf_free(Ctx* ctx, DevBuf& b) {
+  if (b.p == nullptr) return;
+  (void)hipFree(b.p);
+  freed(ctx, b);
+}
+
+bool stream_captured(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
 }
 
 // ------------------------------------------------------------ stage timing
@@ -432,6 +478,27 @@ bool frame_pool_trim(Ctx* ctx) {
       any = true;
       frame_free(f);
       delete static_cast<gs_frame*>(f);
+    }
+  return any;
+}
+
+bool scratch_trim(Ctx* ctx) {
+  std::unique_lock<std::mutex> ray(ctx->ray_mutex, std::try_to_lock);
+  std::lock_guard<std::mutex> lk(ctx->use_mutex);
+  DevBuf* idle[3] = {nullptr, nullptr, nullptr};
+  if (ray.owns_lock()) idle[0] = &ctx->ray_blk;
+  if (ctx->loss_users == 0 && ctx->loss_scratch != nullptr) idle[1] = &ctx->loss_scratch->gmap;
+  if (ctx->dens_users == 0) idle[2] = &ctx->dens_blk;
+  bool any = false;
+  for (DevBuf* b : idle)
+    if (b != nullptr && b->p != nullptr) {
+      // queued work may still use it
+      if (!any && hipDeviceSynchronize() != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+      }
+      any = true;
+      buf_free(ctx, *b);
     }
   return any;
 }
@@ -1086,6 +1153,7 @@ gs_status gs_loss_grad(gs_ctx* ctx, const float* const* rendered, const float* c
   st = set_device(ctx);
   if (st != GS_OK) return st;
   hipStream_t s = (hipStream_t)stream;
+  const ScratchUse use(ctx, &Ctx::loss_users);
   if (ctx->loss_scratch == nullptr) {
     ctx->loss_scratch = new (std::nothrow) LossScratch();
     if (ctx->loss_scratch == nullptr) {
@@ -1094,7 +1162,7 @@ gs_status gs_loss_grad(gs_ctx* ctx, const float* const* rendered, const float* c
     }
   }
   LossScratch& ls = *ctx->loss_scratch;
-  st = loss_reserve(ctx, ls, W, H, n_views, s);
+  st = loss_reserve(ctx, ls, W, H, n_views, s, true);
   if (st != GS_OK) return st;
   {
     StageTimer tm(ctx, ST_LOSS, s);
@@ -1119,6 +1187,7 @@ gs_status gs_image_metrics(gs_ctx* ctx, const float* const* rendered,
   st = set_device(ctx);
   if (st != GS_OK) return st;
   hipStream_t s = (hipStream_t)stream;
+  const ScratchUse use(ctx, &Ctx::loss_users);
   if (ctx->loss_scratch == nullptr) {
     ctx->loss_scratch = new (std::nothrow) LossScratch();
     if (ctx->loss_scratch == nullptr) {
@@ -1127,7 +1196,7 @@ gs_status gs_image_metrics(gs_ctx* ctx, const float* const* rendered,
     }
   }
   LossScratch& ls = *ctx->loss_scratch;
-  st = loss_reserve(ctx, ls, W, H, n_views, s);
+  st = loss_reserve(ctx, ls, W, H, n_views, s, true);
   if (st != GS_OK) return st;
   st = launch_metrics(ls, rendered, reference, W, H, n_views, out, s);
   if (st != GS_OK) return st;
@@ -1342,6 +1411,7 @@ gs_status gs_densify(gs_ctx* ctx, gs_params p, gs_params m, gs_params v, gs_dens
   st = set_device(ctx);
   if (st != GS_OK) return st;
   const hipStream_t s = (hipStream_t)stream;
+  const ScratchUse use(ctx, &Ctx::dens_users);
   StageTimer tm(ctx, ST_DENSIFY, s);
   st = densify_count(ctx, p, stats, *opts, info, s);
   if (st != GS_OK || !write) return st;
@@ -1361,6 +1431,7 @@ gs_status gs_densify_alloc(gs_ctx* ctx, gs_params p, gs_params m, gs_params v,
   st = set_device(ctx);
   if (st != GS_OK) return st;
   const hipStream_t s = (hipStream_t)stream;
+  const ScratchUse use(ctx, &Ctx::dens_users);
   StageTimer tm(ctx, ST_DENSIFY, s);
   st = densify_count(ctx, p, stats, *opts, info, s);
   if (st != GS_OK) return st;

@@ -425,9 +425,10 @@ gs_status densify_count(Ctx* ctx, const gs_params& p, const gs_density_stats& st
   const int nb = (int)((n + kDG - 1) / kDG);
   const DensityCfg c = density_cfg(p, st, o);
   // block totals [nb], offsets [nb + 1], and the classes where there is room for them
-  gs_status stt = buf_ensure(ctx, ctx->dens_blk, density_bytes(nb) + (size_t)n, s);
-  if (stt != GS_OK) stt = buf_ensure(ctx, ctx->dens_blk, density_bytes(nb), s);
-  if (stt != GS_OK) return stt;
+  if (!buf_try(ctx, ctx->dens_blk, density_bytes(nb) + (size_t)n, s)) {
+    const gs_status stt = buf_ensure(ctx, ctx->dens_blk, density_bytes(nb), s);
+    if (stt != GS_OK) return stt;
+  }
   if (ctx->dens_host == nullptr)
     GS_HIP(hipHostMalloc((void**)&ctx->dens_host, sizeof(uint4), hipHostMallocDefault));
   uint4* tot = (uint4*)ctx->dens_blk.p;

@@ -107,7 +107,7 @@ gs_status reserve_and_capture(gs_graph* g) {
   const uint32_t vn = (uint32_t)f.entries;
   const uint32_t most = std::max(std::max(g->cap, vn), (uint32_t)f.vt.total_tiles);
   gs_status st = sort_reserve(ctx, f.ss, most, cs);
-  if (st == GS_OK) st = loss_reserve(ctx, g->loss, g->W, g->H, g->nv, cs);
+  if (st == GS_OK) st = loss_reserve(ctx, g->loss, g->W, g->H, g->nv, cs, false);
   if (st != GS_OK) return st;
   GS_HIP(hipStreamSynchronize(cs));
   drop_graph(g);

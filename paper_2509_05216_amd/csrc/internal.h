@@ -147,7 +147,14 @@ struct DevBuf {
 // Both are waited for before the old buffer is freed; nothing else on the
 // device is (so the streams of other frames keep running).
 gs_status buf_ensure(Ctx* ctx, DevBuf& b, size_t bytes, hipStream_t s, hipEvent_t prior = nullptr);
+// The same for a size that only makes the call faster: false, with b as it was and no error
+// text, where there is no room for it.  Nothing is given up for it, the old buffer goes only
+// once there is a new one, a size that the device refused is not asked of it again before
+// this library frees something, and a stream that is being captured allocates nothing.
+bool buf_try(Ctx* ctx, DevBuf& b, size_t bytes, hipStream_t s, hipEvent_t prior = nullptr);
 void buf_free(Ctx* ctx, DevBuf& b);
+// Whether s is being captured (or cannot be asked).
+bool stream_captured(hipStream_t s);
 
 // Pipeline stages timed with HIP events when a context enables timing.
 enum Stage {
@@ -165,7 +172,8 @@ struct Ctx {
   size_t budget = 0;
   size_t in_use = 0;
   size_t peak = 0;
-  std::mutex mem_mutex;  // guards in_use / peak (render server workers share a context)
+  std::mutex mem_mutex;  // guards in_use / peak / refused (render server workers share a context)
+  size_t refused = 0;    // least optional size the device had no room for (0: none since a free)
   int cu_count = 0;
   hipDeviceProp_t prop;
   struct LossScratch* loss_scratch = nullptr;  // workspace of eager gs_loss_grad calls
@@ -177,6 +185,9 @@ struct Ctx {
   std::mutex ray_mutex;
   DevBuf init_xyz;                 // gs_init_from_points: device copy of host points
   unsigned long long* iso_host = nullptr;  // gs_iso_extract: pinned read-back of the count
+  // calls at work with loss_scratch and dens_blk, which scratch_trim leaves alone then
+  std::mutex use_mutex;
+  int loss_users = 0, dens_users = 0;
   // set while a graph is being captured: no allocation, no stage events
   bool capturing = false;
   // stage timing
@@ -199,12 +210,31 @@ struct Ctx {
 
 // Frees the pooled frames; true when there were any.
 bool frame_pool_trim(Ctx* ctx);
+// Frees the scratch that holds optional parts (the loss workspace, the cell classes, the
+// densification's classes) where no call is at work with it; true when there was any.
+bool scratch_trim(Ctx* ctx);
+
+// Marks a call as at work with one of those (a counter of Ctx) while it lives.
+struct ScratchUse {
+  Ctx* c;
+  int Ctx::*users;
+  ScratchUse(Ctx* c_, int Ctx::*u) : c(c_), users(u) {
+    std::lock_guard<std::mutex> lk(c->use_mutex);
+    ++(c->*users);
+  }
+  ~ScratchUse() {
+    std::lock_guard<std::mutex> lk(c->use_mutex);
+    --(c->*users);
+  }
+  ScratchUse(const ScratchUse&) = delete;
+  ScratchUse& operator=(const ScratchUse&) = delete;
+};
 
 void ctx_retain(Ctx* ctx);
 void ctx_release(Ctx* ctx);
 
-// Workspace of the loss kernels: per-pixel SSIM partial derivatives of one view
-// (9 floats per pixel) and per-block loss partials.  The context holds one for
+// Workspace of the loss kernels: per-pixel SSIM partial derivatives of one view or of
+// several (9 floats per pixel) and per-block loss partials.  The context holds one for
 // eager calls; every step graph holds its own, sized before capture, so a later
 // eager call that needs more room never frees memory a graph replays into.
 struct LossScratch {
@@ -214,8 +244,9 @@ struct LossScratch {
 // Bytes of the two workspace arrays for views of these sizes.
 void loss_scratch_bytes(const int* W, const int* H, int nv, size_t* gmap_bytes,
                         size_t* part_bytes);
+// `shared`: the context's workspace, which can be given back (scratch_trim).
 gs_status loss_reserve(Ctx* ctx, LossScratch& ls, const int* W, const int* H, int nv,
-                       hipStream_t s);
+                       hipStream_t s, bool shared);
 void loss_scratch_free(Ctx* ctx, LossScratch& ls);
 
 // Records HIP events around a stage on stream s when the context times stages.

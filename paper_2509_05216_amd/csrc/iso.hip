@@ -883,7 +883,7 @@ bool build_grid(Ctx* ctx, const VolDev& V, CellGrid& G, hipStream_t s) {
   const size_t bytes = nb * sizeof(float2) + nb + nc;
   // growing waits for the earlier rays that read the old buffer; other calls' rays on
   // other streams are waited for on the device
-  if (buf_ensure(ctx, ctx->ray_blk, bytes, s, ctx->ray_use) != GS_OK ||
+  if (!buf_try(ctx, ctx->ray_blk, bytes, s, ctx->ray_use) ||
       hipStreamWaitEvent(s, ctx->ray_use, 0) != hipSuccess) {
     (void)hipGetLastError();
     return false;
@@ -1023,13 +1023,7 @@ gs_status launch_raycast(Ctx* ctx, const gs_volume& vol, float iso, const gs_cam
     cells += (double)(G.last[a] + 1) * (G.last[a] + 1);
   }
   // a stream that is being captured goes without the classes (their scratch is shared)
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  bool capturing = ctx->capturing;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    capturing = true;
-  }
-  capturing = capturing || cap != hipStreamCaptureStatusNone;
+  const bool capturing = ctx->capturing || stream_captured(s);
   std::unique_lock<std::mutex> lk(ctx->ray_mutex, std::defer_lock);
   if (!capturing && classes_pay((double)V.nx * V.ny * V.nz, (double)pix, std::sqrt(diag) / step,
                                 std::sqrt(cells))) {

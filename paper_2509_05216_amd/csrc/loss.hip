@@ -645,19 +645,21 @@ void loss_scratch_bytes(const int* W, const int* H, int nv, size_t* gmap_bytes,
 }
 
 gs_status loss_reserve(Ctx* ctx, LossScratch& ls, const int* W, const int* H, int nv,
-                       hipStream_t s) {
+                       hipStream_t s, bool shared) {
   if (ls.last_use == nullptr)
     GS_HIP(hipEventCreateWithFlags(&ls.last_use, hipEventDisableTiming));
   size_t gb = 0, pb = 0;
   loss_scratch_bytes(W, H, nv, &gb, &pb);
-  // room for several small views at once (up to 2^22 pixels together), if there is any
+  gs_status st = buf_ensure(ctx, ls.part, pb, s, ls.last_use);
+  if (st != GS_OK) return st;
+  // room for several small views at once (up to 2^22 pixels together), if there is any; a
+  // graph's workspace cannot be given back, so under a budget it takes no more than it needs
   size_t pix = 0;
   for (int v = 0; v < nv; ++v) pix += (size_t)W[v] * H[v];
   const size_t want = sizeof(float) * 9 * std::min(pix, (size_t)1 << 22);
-  gs_status st = buf_ensure(ctx, ls.gmap, std::max(gb, want), s, ls.last_use);
-  if (st != GS_OK && want > gb) st = buf_ensure(ctx, ls.gmap, gb, s, ls.last_use);
-  if (st != GS_OK) return st;
-  return buf_ensure(ctx, ls.part, pb, s, ls.last_use);
+  if (want > gb && (shared || ctx->budget == 0) && buf_try(ctx, ls.gmap, want, s, ls.last_use))
+    return GS_OK;
+  return buf_ensure(ctx, ls.gmap, gb, s, ls.last_use);
 }
 
 // Whether two arrays of na and nb floats share memory (null: no array).
