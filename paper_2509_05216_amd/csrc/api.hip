@@ -121,6 +121,10 @@ void buf_free(Ctx* ctx, DevBuf& b) {
   freed(ctx, b);
 }
 
+bool frame_try(Ctx* ctx, DevBuf& b, size_t bytes, hipStream_t s, hipEvent_t prior) {
+  return bytes <= b.cap || (ctx->budget == 0 && buf_try(ctx, b, bytes, s, prior));
+}
+
 bool stream_captured(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
@@ -335,9 +339,11 @@ static gs_status build_views(Frame& f, const gs_camera* cams, int nv, float* con
 // of four views 7.88 against 7.46 ms): the hardware hands out the workgroups.
 constexpr int kOrderTiles = 2048;
 
-static void choose_order(Frame& f) {
-  f.ordered = f.vt.total_tiles >= kOrderTiles;
+// Without room for the order, by tile id.
+static void choose_order(Frame& f, hipStream_t s) {
   f.tile_order = nullptr;
+  f.ordered = f.vt.total_tiles >= kOrderTiles &&
+              frame_try(f.ctx, f.order_at(), (size_t)f.vt.total_tiles * 4, s, f.last_use);
 }
 
 // Sizes the frame's buffers for its views; s: the stream of the calling pass.
@@ -364,7 +370,6 @@ static gs_status frame_buffers(Frame& f, hipStream_t s) {
   ENS(f.clampm, vn);
   ENS(f.offs, vn * 4);
   ENS(f.ranges, (size_t)f.vt.total_tiles * 8);
-  ENS(f.order, (size_t)(f.vt.total_tiles + kOrderWords) * 4);
   ENS(f.finalT, (size_t)f.total_pix * 4);
   ENS(f.ncon, (size_t)f.total_pix * 4);
   if (f.keep_radii) ENS(f.radii, vn * 4);
@@ -383,13 +388,14 @@ static gs_status frame_buffers(Frame& f, hipStream_t s) {
   }
 #undef ENS
   if (f.words.cap == 0) {
-    st = buf_ensure(c, f.words, kWordCount * 4, s);
+    st = buf_ensure(c, f.words, (kWordCount + kOrderWords) * 4, s);
     if (st != GS_OK) return st;
     // cleared on the pass's own stream, ahead of the kernels that use the words
     st = launch_fill_u32(f.words.p, 0u, kWordCount, s);
     if (st != GS_OK) return st;
   }
   if (f.pinned == nullptr) GS_HIP(hipHostMalloc((void**)&f.pinned, 64, hipHostMallocDefault));
+  choose_order(f, s);
   return GS_OK;
 }
 
@@ -824,7 +830,6 @@ gs_status gs_render_fwd(gs_ctx* ctx, gs_params params, const gs_camera* cams, in
   f.keep_radii = (flags & GS_RENDER_RADII) != 0;
   f.screen_kept = false;
   st = build_views(f, cams, n_views, images, bg);
-  if (st == GS_OK) choose_order(f);
   if (st == GS_OK) st = frame_buffers(f, s);
   if (st != GS_OK) {
     if (fresh) frame_delete(fr);
@@ -944,7 +949,6 @@ gs_status gs_render_fwd_multi(gs_ctx* ctx, const gs_params* params, const gs_cam
   f.screen_kept = false;
   st = build_views(f, oc, n_views, oi, bg);
   if (st == GS_OK) {
-    choose_order(f);
     uint32_t base = 0;
     int v = 0;
     f.n_groups = ng;

@@ -14,7 +14,7 @@
 //   ranges  uint2[tiles]   [start, end) per global tile
 //   finalT  f32[P], ncon u32[P]   per pixel over all views
 //   acc     f32[V][N][8], then f32[V][N][4]   screen-space gradient accumulators (below)
-//   order   u32[tiles + 512]  tiles, longest list first, and the counters that place them
+//   order   u32[tiles]     tiles, longest list first (in dkw[1] where they fit)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -52,7 +52,7 @@ enum Word {
   kWordStep = 6,        // int64: Adam step of the next graph launch
   kWordTotal = 8,       // u64: record count from the scan
   kWordVisible = 10,    // (view, Gaussian) entries touching at least one tile
-  kWordCount = 16
+  kWordCount = 16,      // of these; the kOrderWords of the tile order follow
 };
 
 // Guard band on t_x/t_z, t_y/t_z for the projection Jacobian: 1.3 times the
@@ -153,6 +153,9 @@ gs_status buf_ensure(Ctx* ctx, DevBuf& b, size_t bytes, hipStream_t s, hipEvent_
 // this library frees something, and a stream that is being captured allocates nothing.
 bool buf_try(Ctx* ctx, DevBuf& b, size_t bytes, hipStream_t s, hipEvent_t prior = nullptr);
 void buf_free(Ctx* ctx, DevBuf& b);
+// buf_try for a frame's buffer: that cannot be given back while the frame lives, so under a
+// budget nothing is taken.
+bool frame_try(Ctx* ctx, DevBuf& b, size_t bytes, hipStream_t s, hipEvent_t prior);
 // Whether s is being captured (or cannot be asked).
 bool stream_captured(hipStream_t s);
 
@@ -302,6 +305,9 @@ struct Frame {
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   bool keep_radii = false;    // this forward writes radii
   bool screen_kept = false;   // the last backward kept its screen-space sums
+  // Where the tile order goes: the depth-ordered rectangles' second half, free once the
+  // records are emitted, else a buffer of its own.
+  DevBuf& order_at() { return dkw[1].cap / 4 >= (size_t)vt.total_tiles ? dkw[1] : order; }
   // Tile keys of up to 16 bits are held as u16 (in buffers of u32's size): a third less to
   // move per record.
   bool short_keys() const { return key_bits <= 16; }
@@ -312,8 +318,8 @@ struct Frame {
   bool settled = false;       // the last call on the frame went through (else it is not pooled)
   bool ordered = false;               // tiles are blended longest list first
   const uint32_t* tile_order = nullptr;  // blending order of the tiles (null: by id)
-  DevBuf words;                       // kWordCount device words
-  DevBuf order;                       // tile order [tiles], class counts and cursors
+  DevBuf words;                       // kWordCount + kOrderWords device words
+  DevBuf order;                       // tile order [tiles], where dkw[1] is too small
   SortScratch ss;
   uint64_t* pinned = nullptr;  // host-pinned readback words (K, visible count)
   // recorded on the call's stream after each call that enqueues work on the

@@ -656,13 +656,14 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
                                               uint32_t* __restrict__ tval,
                                               uint32_t* overflow, uint32_t* d_K,
                                               uint2* __restrict__ ranges,
-                                              uint32_t tiles, uint32_t* __restrict__ order) {
+                                              uint32_t tiles, uint32_t* __restrict__ order_words) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = __lane_id();
   // the tiles' ranges start empty (k_ranges, after the sort, writes those with records)
   for (uint32_t t = i; t < tiles; t += gridDim.x * blockDim.x) ranges[t] = make_uint2(0u, 0u);
-  // ... and so do the counts of the tile order
-  for (uint32_t t = i; t < (uint32_t)kOrderWords; t += gridDim.x * blockDim.x) order[tiles + t] = 0u;
+  // ... and so do the counts of the tile order (null: none is formed)
+  if (order_words != nullptr)
+    for (uint32_t t = i; t < (uint32_t)kOrderWords; t += gridDim.x * blockDim.x) order_words[t] = 0u;
   uint32_t need = 0, o = 0, idx = 0, key0 = 0, w = 1, tx = 1;
   bool over = false;
   if (i < count) {
@@ -885,17 +886,19 @@ inline uint32_t row_stride(uint32_t nb) { return row_quads(nb) * 4; }
 // Keys per thread of a sort of n pairs: a block's chain of ranking steps sets the time of
 // a small sort (histogram and scatter with 4 instead of 16 keys a thread: 600k pairs 11.1
 // instead of 14.5 us, 1M 13.5 instead of 15.9), the lengths of the digit runs that it writes
-// that of a large one.
+// that of a large one.  Its digit table is up to four times that of sixteen keys a thread,
+// which serves where there is no room for it.
 constexpr uint32_t kSmallSort = 1u << 20;
-
-inline uint32_t sort_chunks(uint32_t n) {
-  return n <= kSmallSort ? PassSmall::chunks(n) : PassLarge::chunks(n);
-}
 
 // Words of a digit table: RADIX rows and their totals.
 template <class P>
 size_t table_words(uint32_t n) {
   return (size_t)P::RADIX * (row_stride(P::chunks(n)) + 1);
+}
+
+// Whether the sorts of n pairs take four keys a thread.
+inline bool small_sort(const SortScratch& ss, uint32_t n) {
+  return n <= kSmallSort && table_words<PassSmall>(n) * sizeof(uint32_t) <= ss.hist.cap;
 }
 
 // The passes of one sort, all of shape P.
@@ -960,8 +963,9 @@ gs_status scan_tile_counts(Ctx* ctx, SortScratch& ss, const uint32_t* sidx, cons
   // few entries: the gather's blocks leave their totals, which the down-sweep sums (16 to
   // a block of its own); many: totals per chunk by a launch of their own (the gather runs
   // best at one entry per thread)
-  const bool fused = ng <= kDirectBlocks;
-  gs_status st = ensure_scratch(ctx, ss, fused ? ng : nb, 0, s);
+  const bool fused = ng <= kDirectBlocks &&
+                     frame_try(ctx, ss.partial, sizeof(uint64_t) * (size_t)(ng + 1), s, ss.prior);
+  const gs_status st = ensure_scratch(ctx, ss, nb, 0, s);
   if (st != GS_OK) return st;
   auto* partial = (uint64_t*)ss.partial.p;
   // gather the counts once (random rect reads), then scan them in place, coalesced
@@ -997,7 +1001,7 @@ gs_status sort_pairs(Ctx* ctx, SortScratch& ss, const uint32_t* kin, const uint3
   auto* hist = (uint32_t*)ss.hist.p;
   uint32_t* const kb[2] = {kA, kB};
   uint32_t* const vb[2] = {vA, vB};
-  if (n <= kSmallSort)
+  if (small_sort(ss, n))
     return run_passes<PassSmall>(kin, vin, kb, vb, n, d_n, bits, hist, result_in_b, s);
   // Keys of 17 to 20 bits (more than 65536 tiles): two passes of nine or ten bits instead of
   // three of eight, where the caller's spare memory holds their table (as large as the
@@ -1021,7 +1025,7 @@ gs_status sort_pairs(Ctx* ctx, SortScratch& ss, const uint16_t* kin, const uint3
   auto* hist = (uint32_t*)ss.hist.p;
   uint16_t* const kb[2] = {kA, kB};
   uint32_t* const vb[2] = {vA, vB};
-  return n <= kSmallSort
+  return small_sort(ss, n)
              ? run_passes<PassSmall>(kin, vin, kb, vb, n, d_n, bits, hist, result_in_b, s)
              : run_passes<PassLarge>(kin, vin, kb, vb, n, d_n, bits, hist, result_in_b, s);
 }
@@ -1049,7 +1053,8 @@ gs_status launch_emit(const ViewTable& vt, Frame& f, const uint32_t* sidx, const
     hipLaunchKernelGGL(kern, dim3((count + 255) / 256), dim3(256), 0, s, vt, sidx, srx,
                      sry, (const uint32_t*)f.offs.p, count, cap, tkey,
                      (uint32_t*)f.tval[0].p, overflow, d_K, (uint2*)f.ranges.p,
-                     (uint32_t)f.vt.total_tiles, (uint32_t*)f.order.p);
+                     (uint32_t)f.vt.total_tiles,
+                     f.ordered ? (uint32_t*)f.words.p + kWordCount : nullptr);
   };
   if (f.short_keys())
     go(k_emit<uint16_t>, (uint16_t*)f.tkey[0].p);
@@ -1082,15 +1087,18 @@ gs_status launch_clamp_count(const uint64_t* total, uint32_t cap, uint32_t* K,
 }
 
 gs_status sort_reserve(Ctx* ctx, SortScratch& ss, uint32_t n, hipStream_t s) {
-  // (any smaller sort's table fits too: the small form's is of at most 1024 chunks)
-  const uint32_t nb = std::max(sort_chunks(n), sort_chunks(std::min(n, kSmallSort)));
-  return ensure_scratch(ctx, ss, nblocks_of(n), (size_t)kRadix * (row_stride(nb) + 1), s);
+  // with the tables of four keys a thread (at most 1024 chunks), also of any smaller sort
+  const size_t words = table_words<PassLarge>(n);
+  const size_t more = std::max(words, table_words<PassSmall>(std::min(n, kSmallSort)));
+  (void)frame_try(ctx, ss.hist, sizeof(uint32_t) * (more + 1), s, ss.prior);
+  return ensure_scratch(ctx, ss, nblocks_of(n), words, s);
 }
 
 gs_status launch_visible_count(const SortScratch& ss, uint32_t n, uint32_t* dst, hipStream_t s) {
   if (n == 0) return launch_fill_u32(dst, 0u, 1, s);
-  const uint32_t nb = sort_chunks(n);
-  auto kern = nb <= kRawChunks ? k_visible_count<true> : k_visible_count<false>;
+  const bool small = small_sort(ss, n);
+  const uint32_t nb = small ? PassSmall::chunks(n) : PassLarge::chunks(n);
+  auto kern = small && nb <= kRawChunks ? k_visible_count<true> : k_visible_count<false>;
   hipLaunchKernelGGL(kern, dim3(1), dim3(1), 0, s, (const uint32_t*)ss.hist.p, row_stride(nb), nb,
                      n, dst);
   GS_LAUNCHED("visible_count");
@@ -1100,12 +1108,13 @@ gs_status launch_visible_count(const SortScratch& ss, uint32_t n, uint32_t* dst,
 gs_status launch_tile_order(Frame& f, hipStream_t s) {
   const uint32_t tiles = (uint32_t)f.vt.total_tiles;
   const uint32_t blocks = (tiles + 256 * kOrderItems - 1) / (256 * kOrderItems);
-  auto* order = (uint32_t*)f.order.p;
+  auto* order = (uint32_t*)f.order_at().p;
+  auto* counts = (uint32_t*)f.words.p + kWordCount;
   auto* ranges = (const uint2*)f.ranges.p;
-  hipLaunchKernelGGL(k_order_count, dim3(blocks), dim3(256), 0, s, ranges, tiles, order + tiles);
+  hipLaunchKernelGGL(k_order_count, dim3(blocks), dim3(256), 0, s, ranges, tiles, counts);
   GS_LAUNCHED("order_count");
   hipLaunchKernelGGL(k_order_place, dim3(blocks), dim3(256), 0, s, ranges, tiles,
-                     (const uint32_t*)(order + tiles), order + tiles + 256, order);
+                     (const uint32_t*)counts, counts + 256, order);
   GS_LAUNCHED("order_place");
   f.tile_order = order;
   return GS_OK;

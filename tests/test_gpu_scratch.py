@@ -130,3 +130,34 @@ def test_captured_loss_takes_the_workspace_as_it_is(P):
         assert torch.equal(loss.view(-1), want.view(-1)), rep
         for a, b in zip(got, dl):
             assert torch.equal(a, b), rep
+
+
+@pytest.mark.parametrize("n,side,tile,log_scale,less", [
+    (3_000, 1024, 8, -4.5, 60 << 10),       # the tile order, of more tiles than entries
+    (20_000, 1024, 8, -3.9, 500 << 10),     # digit tables of four keys a thread
+    (20_000, 400, 16, -4.5, 0)])
+def test_forward_without_room_for_faster_sorts(P, n, side, tile, log_scale, less):
+    """A budget short of what a frame takes without one by memory that only makes its sorts
+    and its schedule faster: the same frame, images and gradients."""
+    g = torch.Generator("cuda").manual_seed(n + side)
+    r = lambda *s: torch.rand(s, device="cuda", generator=g)  # noqa: E731
+    ls = log_scale + torch.tensor([[0.2], [0.0], [-0.2]], device="cuda").repeat(1, n)
+    p = P.Params(r(3, n) * 1.6 - 0.8, ls.contiguous(), r(4, n) - 0.5, r(n) * 4 - 2, r(3, n), 0)
+    cams = P.orbit_cameras(3, 2.5, 60.0, side, side)[1:2]
+    free = P.Context(0)
+    want, frame = P.render_fwd(free, p, cams, tile=tile, lds_depth=64)
+    torch.cuda.synchronize()
+    total, st = free.memory()[0], frame.stats()
+    assert (st["n_records"] > 1 << 19) == (n > 3000 and side > 400)
+    tight = P.Context(0, mem_budget=total - less)
+    imgs, frame2 = P.render_fwd(tight, p, cams, tile=tile, lds_depth=64)
+    assert torch.equal(imgs[0], want[0])
+    st2 = frame2.stats()
+    assert all(st[k] == st2[k] for k in st if k != "device_bytes")
+    for k in ("keys", "values", "ranges"):
+        assert torch.equal(frame.export(k), frame2.export(k)), k
+    dl = [r(3, side, side)]
+    a, b = P.render_bwd(free, frame, p, dl), P.render_bwd(tight, frame2, p, dl)
+    torch.cuda.synchronize()
+    for x, y in zip(a.tensors(), b.tensors()):
+        assert (x - y).abs().max().item() <= 1e-5 * max(y.abs().max().item(), 1e-6)
