@@ -176,8 +176,13 @@ gs_status gs_ctx_create(int device, size_t mem_budget, gs_ctx** out);
  * release (gs_frame_release, gs_step_graph_destroy, gs_server_destroy) frees it.
  * No other call may use the context after this one. */
 void gs_ctx_destroy(gs_ctx* ctx);
-/* Bytes of device scratch currently held by the context and its frames. */
+/* Bytes of device scratch currently held by the context and its frames, kept
+ * ones (gs_frame_release) included. */
 gs_status gs_ctx_memory(gs_ctx* ctx, size_t* in_use, size_t* peak);
+/* Gives back what the context keeps for later calls only: the frames kept by
+ * gs_frame_release and scratch that no call is at work with.  Frames that are
+ * in use, step graphs and servers are untouched.  Waits for the device. */
+gs_status gs_ctx_trim(gs_ctx* ctx);
 
 /* Stage timing.  When enabled, every pipeline stage the context launches is
  * bracketed by HIP events on its stream (the events add no work to the
@@ -331,6 +336,10 @@ gs_status gs_frame_stats_get(gs_frame* frame, gs_frame_stats* out);
  * export, a short or misaligned dst. */
 gs_status gs_frame_export(gs_frame* frame, int32_t what, int32_t view, void* dst,
                           size_t bytes, void* stream);
+/* Releases a frame, waiting for the device's work on it.  Its memory is kept for
+ * the next forward on the context that creates a frame of this size (at most four
+ * frames of 2 GB together are kept) until the context is destroyed, another of the
+ * library's allocations on it needs the room or gs_ctx_trim is called. */
 void gs_frame_release(gs_frame* frame);
 
 /* ------------------------------------------------------- batched step graph

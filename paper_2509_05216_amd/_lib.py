@@ -131,6 +131,7 @@ SIGNATURES = [
     ("gs_ctx_create", C.c_int, [C.c_int, C.c_size_t, C.POINTER(_P)]),
     ("gs_ctx_destroy", None, [_P]),
     ("gs_ctx_memory", C.c_int, [_P, C.POINTER(C.c_size_t), C.POINTER(C.c_size_t)]),
+    ("gs_ctx_trim", C.c_int, [_P]),
     ("gs_ctx_set_timing", C.c_int, [_P, C.c_int32]),
     ("gs_ctx_stage_time", C.c_int, [_P, C.c_int32, C.POINTER(C.c_double),
                                     C.POINTER(C.c_int64)]),

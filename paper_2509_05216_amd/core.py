@@ -39,6 +39,10 @@ class Context:
         L.check(L.lib().gs_ctx_memory(self.handle, C.byref(a), C.byref(b)))
         return a.value, b.value
 
+    def trim(self):
+        """Give back what is kept for later calls only (released frames, idle scratch)."""
+        L.check(L.lib().gs_ctx_trim(self.handle))
+
     def set_timing(self, enable=True):
         """Bracket every stage with HIP events (resets the totals)."""
         L.check(L.lib().gs_ctx_set_timing(self.handle, 1 if enable else 0))

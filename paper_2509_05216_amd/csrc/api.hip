@@ -528,17 +528,25 @@ static bool frame_pool_give(gs_frame* fr) {
 }
 
 // A frame for a new forward of `entries` (view, Gaussian) entries: the smallest pooled
-// one whose arrays hold them, else a new one (a frame that would have to grow is not
-// taken: a larger call would find its memory gone all the same).  nullptr: no host memory.
+// one whose arrays hold them, else a new one.  A frame whose arrays would have to grow is
+// not taken (a larger call would find its memory gone all the same), nor, from kAnyBytes on,
+// one for more than kMostTimes the entries: the caller may keep it for good.  nullptr: no
+// host memory.
+constexpr size_t kAnyBytes = (size_t)64 << 20, kMostTimes = 4;
+
 static gs_frame* frame_new(Ctx* ctx, int64_t entries) {
   gs_frame* fr = nullptr;
   {
     std::lock_guard<std::mutex> lk(ctx->pool_mutex);
     int at = -1;
-    for (int i = 0; i < 4; ++i)
-      if (ctx->pool[i] != nullptr && ctx->pool[i]->splat.cap >= (size_t)entries * 48 &&
-          (at < 0 || ctx->pool[i]->splat.cap < ctx->pool[at]->splat.cap))
+    const size_t need = (size_t)entries * 48;
+    for (int i = 0; i < 4; ++i) {
+      const Frame* f = ctx->pool[i];
+      if (f != nullptr && f->splat.cap >= need &&
+          (f->bytes() <= kAnyBytes || f->splat.cap <= kMostTimes * need) &&
+          (at < 0 || f->splat.cap < ctx->pool[at]->splat.cap))
         at = i;
+    }
     if (at >= 0) {
       fr = static_cast<gs_frame*>(ctx->pool[at]);
       ctx->pool[at] = nullptr;
@@ -672,6 +680,18 @@ gs_status gs_ctx_memory(gs_ctx* ctx, size_t* in_use, size_t* peak) {
   }
   if (in_use) *in_use = ctx->in_use;
   if (peak) *peak = ctx->peak;
+  return GS_OK;
+}
+
+gs_status gs_ctx_trim(gs_ctx* ctx) {
+  if (ctx == nullptr) {
+    set_error("gs_ctx_trim: null context");
+    return GS_ERR_INVALID;
+  }
+  const gs_status st = set_device(ctx);
+  if (st != GS_OK) return st;
+  (void)frame_pool_trim(ctx);
+  (void)scratch_trim(ctx);
   return GS_OK;
 }
 

@@ -271,3 +271,39 @@ def test_release_waits_for_every_stream_of_the_frame(P):
         assert torch.equal(a, b)
     again.release()
     ctx.close()
+
+
+def test_a_small_forward_leaves_a_large_kept_frame(P):
+    """A released frame much larger than a new forward needs stays for a forward of its own
+    size; trim() gives back what is kept."""
+    n = 500_000
+    g = torch.Generator("cuda").manual_seed(1)
+    r = lambda *s: torch.rand(s, device="cuda", generator=g)  # noqa: E731
+    big = P.Params(r(3, n) - 0.5, r(3, n) - 6, r(4, n) - 0.5, r(n), r(3, n), 0)
+    small = P.Params.from_numpy(gsscenes.make_scene("tiny", n=900).params)
+    cams = _views(P, [(160, 96)] * 2)
+    ctx = P.Context(0)
+    want, frame = P.render_fwd(ctx, big, cams)
+    large = frame.stats()["device_bytes"]
+    assert large > 64 << 20
+    frame.release()
+    _, little = P.render_fwd(ctx, small, cams)
+    assert little.stats()["device_bytes"] < 64 << 20
+    before = ctx.memory()[0]
+    again, frame = P.render_fwd(ctx, big, cams)
+    assert ctx.memory()[0] == before and frame.stats()["device_bytes"] == large
+    torch.cuda.synchronize()
+    for a, b in zip(again, want):
+        assert torch.equal(a, b)
+    frame.release()
+    ctx.trim()
+    assert ctx.memory()[0] == little.stats()["device_bytes"]
+    dl = [torch.ones((3, 96, 160), device="cuda")] * 2     # a frame in use is untouched
+    ref, fresh = _step(P, P.Context(0), small, cams, dl)
+    for a, b in zip(P.render_bwd(ctx, little, small, dl).tensors(), ref.tensors()):
+        assert (a - b).abs().max().item() <= 1e-5 * max(b.abs().max().item(), 1e-6)
+    little.release()
+    fresh.release()
+    ctx.trim()
+    assert ctx.memory()[0] == 0
+    ctx.close()
