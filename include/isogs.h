@@ -589,9 +589,11 @@ gs_status gs_raycast(gs_ctx* ctx, gs_volume volume, float iso, const gs_camera* 
                      int32_t n_views, float step, float* const* images, void* stream);
 
 /* -------------------------------------------------------------- autotuner
- * Times forward + backward of the given views for tile sizes {8, 16, 32},
- * LDS depths {32, 64, 128, 256} and values of the schedule flags, `reps` timed repetitions each after a warm-up, and returns the
- * fastest options in *best.  table (optional, host) receives up to table_cap
+ * Times forward + backward of the given views for tile sizes {8, 16, 32} and
+ * LDS depths {32, 64, 128, 256}, `reps` timed repetitions each after a warm-up,
+ * and returns the fastest options in *best.  The schedule flags change nothing:
+ * *best has none, and the table's entries with them repeat the time of the same
+ * options without.  table (optional, host) receives up to table_cap
  * entries; *table_n their number.  Synchronous. */
 typedef struct {
   int32_t tile, lds_depth, flags;

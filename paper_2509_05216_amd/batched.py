@@ -1,6 +1,6 @@
 """Batched multi-view training step: autotuned render options and a hipGraph.
 
-``autotune`` asks the library to time the tile / LDS-depth / flag
+``autotune`` asks the library to time the tile / LDS-depth
 choices for a scene and view set, and caches the winner in a JSON file keyed
 by the Gaussian count, SH degree and view sizes.  ``StepGraph`` captures one
 whole step (forward, loss gradient, backward, Adam) for a fixed set of views

@@ -344,14 +344,31 @@ gs_status gs_autotune(gs_ctx* ctx, gs_params params, const gs_camera* cams, int3
       {8, 32, 0},   {8, 64, 0},   {16, 32, 0},  {16, 64, 0},  {16, 128, 0}, {16, 256, 0},
       {32, 32, 0},  {32, 64, 0},  {32, 128, 0}, {32, 256, 0}, {8, 64, 3},   {16, 64, 3},
       {16, 128, 3}, {16, 256, 3}, {32, 64, 3},  {32, 128, 3}, {32, 256, 3}};
+  constexpr int kPlain = 10;  // without flags, ahead of the others
   gs_frame* frame = nullptr;
   hipEvent_t a = nullptr, b = nullptr;
   if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess)
     st = hip_fail(hipErrorUnknown, "hipEventCreate");
   float best_ms = 1e30f;
   int count = 0;
+  auto enter = [&](const Cfg& c, float ms) {
+    if (table != nullptr && count < table_cap) {
+      table[count].tile = c.tile;
+      table[count].lds_depth = c.depth;
+      table[count].flags = c.flags;
+      table[count].ms = ms;
+    }
+    ++count;
+  };
+  float timed[kPlain];
   for (const Cfg& c : cfgs) {
     if (st != GS_OK) break;
+    if (c.flags != 0) {
+      // the schedule flags change no launch: the time of the same options without them
+      for (int k = 0; k < kPlain; ++k)
+        if (cfgs[k].tile == c.tile && cfgs[k].depth == c.depth) enter(c, timed[k]);
+      continue;
+    }
     gs_render_opts o;
     std::memset(&o, 0, sizeof(o));
     o.tile = c.tile;
@@ -370,13 +387,8 @@ gs_status gs_autotune(gs_ctx* ctx, gs_params params, const gs_camera* cams, int3
       break;
     }
     ms /= (float)reps;
-    if (table != nullptr && count < table_cap) {
-      table[count].tile = c.tile;
-      table[count].lds_depth = c.depth;
-      table[count].flags = c.flags;
-      table[count].ms = ms;
-    }
-    ++count;
+    timed[count] = ms;
+    enter(c, ms);
     if (ms < best_ms) {
       best_ms = ms;
       *best = o;

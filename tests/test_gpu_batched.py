@@ -197,3 +197,17 @@ def test_autotune_returns_a_valid_option(P, ctx, scene, tmp_path):
                                               (best["tile"], best["lds_depth"], best["flags"]))
     best2, _ = P.autotune(ctx, params, cams, reps=1, cache=str(tmp_path / "tune.json"))
     assert best2 == best
+
+
+def test_autotune_times_each_launch_form_once(P, ctx, scene):
+    """Options that differ in the schedule flags only are one launch form: one time for
+    both, and the best options carry no flags."""
+    cams = _mixed_views(P)[1]
+    params = P.Params.from_numpy(scene.params)
+    best, table = P.autotune(ctx, params, cams, reps=1, use_cache=False, cache=None)
+    plain = {(r["tile"], r["lds_depth"]): r["ms"] for r in table if r["flags"] == 0}
+    assert len(plain) == 10 and len(table) == 17
+    for r in table:
+        assert r["ms"] == plain[r["tile"], r["lds_depth"]]
+    assert best["flags"] == 0
+    assert plain[best["tile"], best["lds_depth"]] == min(plain.values())
