@@ -1237,7 +1237,7 @@ gs_status gs_loss_grad_noalloc(gs_ctx* ctx, const float* const* rendered,
                            lambda_dssim, W, H);
   if (st != GS_OK) return st;
   LossScratch ws;
-  st = loss_noalloc_workspace(ctx->device, W, H, n_views, &ws);
+  st = loss_noalloc_workspace(ctx, W, H, n_views, &ws);
   if (st != GS_OK) return st;
   st = set_device(ctx);
   if (st != GS_OK) return st;

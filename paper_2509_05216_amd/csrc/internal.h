@@ -243,6 +243,7 @@ void ctx_release(Ctx* ctx);
 struct LossScratch {
   DevBuf gmap, part;
   hipEvent_t last_use = nullptr;  // recorded after each eager use
+  int cus = 0;                    // of the device
 };
 // Bytes of the two workspace arrays for views of these sizes.
 void loss_scratch_bytes(const int* W, const int* H, int nv, size_t* gmap_bytes,
@@ -424,7 +425,7 @@ gs_status launch_export_screen_grads(Frame& f, int view, float* dst, hipStream_t
 // LossScratch view (GS_ERR_CAPACITY when the views need more than it holds).
 constexpr size_t kNoAllocMaxPixels = (size_t)1 << 20;  // per view
 gs_status loss_noalloc_setup(int device);
-gs_status loss_noalloc_workspace(int device, const int* W, const int* H, int nv,
+gs_status loss_noalloc_workspace(const Ctx* ctx, const int* W, const int* H, int nv,
                                  LossScratch* out);
 gs_status launch_loss(const LossScratch& ls, const float* const* x, const float* const* y,
                       const int* W, const int* H, int nv, float lambda, float* loss_out,

@@ -462,11 +462,11 @@ __global__ __launch_bounds__(256, STRIP ? kBwdBlocks : 1) void k_ssim_bwd(LossVi
   }
 }
 
-// Tiles per strip for kernels of which `per_cu` blocks run at once on each of the 256 CUs:
+// Tiles per strip for kernels of which `per_cu` blocks run at once on each of `cus` CUs:
 // the length that costs a CU least, a strip's start taken as 0.7 tiles and k < per_cu
 // blocks as 1 - (1 - k / per_cu)^2 of a full CU's rate (1024^2, three channels, forward:
 // strips of 4 tiles 33 us, of 1 tile 41).
-static int strip_len(const int* W, const int* H, int n, int per_cu) {
+static int strip_len(const int* W, const int* H, int n, int per_cu, int cus) {
   int longest = 1, best = 1;
   double least = 1e30;
   for (int k = 0; k < n; ++k) longest = std::max(longest, (H[k] + kT - 1) / kT);
@@ -474,7 +474,7 @@ static int strip_len(const int* W, const int* H, int n, int per_cu) {
     size_t blocks = 0;
     for (int k = 0; k < n; ++k)
       blocks += (size_t)((W[k] + kT - 1) / kT) * 3 * (((H[k] + kT - 1) / kT + len - 1) / len);
-    const size_t per = (blocks + 255) / 256, rest = per % per_cu;
+    const size_t per = (blocks + cus - 1) / cus, rest = per % per_cu;
     const double idle = 1.0 - (double)rest / per_cu;
     const double cost =
         (len + 0.7) * ((double)(per - rest) + (rest != 0 ? rest / (1.0 - idle * idle) : 0.0));
@@ -486,10 +486,10 @@ static int strip_len(const int* W, const int* H, int n, int per_cu) {
   return best;
 }
 
-// Up to this many tiles (four blocks per CU) a launch takes them one per block (loss and
-// gradient of 64^2 and of 640 x 480: 20 and 33 us, in strips 27 and 35; of 1024^2, 3072
-// tiles: 62 and 61).
-constexpr uint32_t kSingleTiles = 1024;
+// Up to this many tiles per CU a launch takes them one per block (256 CUs: loss and gradient
+// of 64^2 and of 640 x 480 20 and 33 us, in strips 27 and 35; of 1024^2, 3072 tiles, 62
+// and 61).
+constexpr uint32_t kSinglePerCu = 4;
 
 inline uint32_t tiles_of(int W, int H) {
   return (uint32_t)((W + kT - 1) / kT) * (uint32_t)((H + kT - 1) / kT) * 3u;
@@ -507,17 +507,17 @@ static dim3 set_strips(LossViews& lv, int len) {
 
 // The passes over the views of lv: moments (and partials), then, with gradients, theirs.
 template <bool GRAD>
-static gs_status launch_views(LossViews& lv, const Win& win, double* part, float lambda,
+static gs_status launch_views(LossViews& lv, const Win& win, double* part, float lambda, int cus,
                               hipStream_t s) {
   uint32_t tiles = 0;
   for (int k = 0; k < lv.n; ++k) tiles += tiles_of(lv.W[k], lv.H[k]);
-  const bool single = tiles <= kSingleTiles;
-  dim3 grid = set_strips(lv, single ? 1 : strip_len(lv.W, lv.H, lv.n, kFwdBlocks));
+  const bool single = tiles <= kSinglePerCu * (uint32_t)cus;
+  dim3 grid = set_strips(lv, single ? 1 : strip_len(lv.W, lv.H, lv.n, kFwdBlocks, cus));
   auto fwd = single ? k_ssim_fwd<GRAD, false> : k_ssim_fwd<GRAD, true>;
   hipLaunchKernelGGL(fwd, grid, dim3(256), 0, s, lv, win, part);
   GS_LAUNCHED("ssim_fwd");
   if constexpr (GRAD) {
-    grid = set_strips(lv, single ? 1 : strip_len(lv.W, lv.H, lv.n, kBwdBlocks));
+    grid = set_strips(lv, single ? 1 : strip_len(lv.W, lv.H, lv.n, kBwdBlocks, cus));
     auto bwd = single ? k_ssim_bwd<false> : k_ssim_bwd<true>;
     hipLaunchKernelGGL(bwd, grid, dim3(256), 0, s, lv, win, lambda);
     GS_LAUNCHED("ssim_bwd");
@@ -648,6 +648,7 @@ gs_status loss_reserve(Ctx* ctx, LossScratch& ls, const int* W, const int* H, in
                        hipStream_t s, bool shared) {
   if (ls.last_use == nullptr)
     GS_HIP(hipEventCreateWithFlags(&ls.last_use, hipEventDisableTiming));
+  ls.cus = ctx->cu_count;
   size_t gb = 0, pb = 0;
   loss_scratch_bytes(W, H, nv, &gb, &pb);
   gs_status st = buf_ensure(ctx, ls.part, pb, s, ls.last_use);
@@ -749,8 +750,8 @@ gs_status launch_loss(const LossScratch& ls, const float* const* x, const float*
   const gs_status st =
       loss_groups(ls, x, y, W, H, nv, dl, grad, [&](LossViews& lv, int v0) -> gs_status {
         double* part = (double*)ls.part.p + 2 * lr.off[v0];
-        return grad ? launch_views<true>(lv, win, part, lambda, s)
-                    : launch_views<false>(lv, win, part, lambda, s);
+        return grad ? launch_views<true>(lv, win, part, lambda, ls.cus, s)
+                    : launch_views<false>(lv, win, part, lambda, ls.cus, s);
       });
   if (st != GS_OK) return st;
   if (loss_out != nullptr) {
@@ -811,8 +812,9 @@ gs_status loss_noalloc_setup(int device) {
   return GS_OK;
 }
 
-gs_status loss_noalloc_workspace(int device, const int* W, const int* H, int nv,
+gs_status loss_noalloc_workspace(const Ctx* ctx, const int* W, const int* H, int nv,
                                  LossScratch* out) {
+  const int device = ctx->device;
   size_t gb = 0, pb = 0;
   loss_scratch_bytes(W, H, nv, &gb, &pb);
   if (gb > kNoAllocGmapBytes || pb > kNoAllocPartBytes) {
@@ -833,6 +835,7 @@ gs_status loss_noalloc_workspace(int device, const int* W, const int* H, int nv,
   out->part.p = (unsigned char*)base + kNoAllocGmapBytes;
   out->part.cap = kNoAllocPartBytes;
   out->last_use = nullptr;
+  out->cus = ctx->cu_count;
   return GS_OK;
 }
 
@@ -869,7 +872,7 @@ gs_status launch_metrics(const LossScratch& ls, const float* const* x, const flo
   double* part3 = part2 + 2 * (size_t)kRedBlocks * kMaxViews;
   const gs_status st = loss_groups(
       ls, x, y, W, H, nv, nullptr, false, [&](LossViews& lv, int v0) -> gs_status {
-        return launch_views<false>(lv, win, part + 2 * lr.off[v0], 0.f, s);
+        return launch_views<false>(lv, win, part + 2 * lr.off[v0], 0.f, ls.cus, s);
       });
   if (st != GS_OK) return st;
   hipLaunchKernelGGL(k_loss_partial, dim3(kRedBlocks, nv), dim3(256), 0, s, (const double*)part,
