@@ -39,6 +39,15 @@ __device__ inline uint64_t lanemask_lt() {
   return (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
 }
 
+// Orders this wave's LDS accesses before and after it among its lanes.  LDS serves a wave's
+// accesses in order, so this costs no instruction; it keeps the compiler from answering a
+// lane's read from what that lane itself wrote last.
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------- block scan
 // Exclusive scan of one u64 value per thread over a block of WAVES waves.
 template <int WAVES = kWaves>
@@ -416,9 +425,9 @@ __device__ inline void rank_keys(const uint32_t (&key)[ITEMS], int shift, uint16
     const uint32_t old = cnt[d];
     rank[j] = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, old));
     const uint32_t now = old + __popc(plo) + __popc(phi);
-    __builtin_amdgcn_wave_barrier();  // every lane has read before the last one writes
+    wave_sync();  // every lane has read before the last one writes
     if (rank[j] + 1 == now) cnt[d] = (uint16_t)now;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
   }
 }
 
@@ -713,6 +722,7 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
                                 __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u))] =
         make_uint4(excl, key0, idx, (w - 1) | ((tx - 1) << 16));
   mk[lane] = 0;
+  wave_sync();
   // the wave's records are adjacent in the output (entries without room for theirs come
   // after all those with)
   const uint32_t o0 = (uint32_t)__builtin_amdgcn_readlane((int)(o - excl), __builtin_ctzll(has));
@@ -720,13 +730,13 @@ __global__ __launch_bounds__(256) void k_emit(ViewTable vt,
   for (uint32_t base = 0, pass = 1; base < total; base += 64, ++pass) {
     // mark the records that start an entry; a record's entry is the last start up to it
     if (need != 0 && excl - base < 64u) mk[excl - base] = pass;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     const bool start = mk[lane] == pass;
     const uint64_t m = __builtin_amdgcn_ballot_w64(start);
     const uint32_t lower = __builtin_amdgcn_mbcnt_hi(
         (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, before));
     const uint4 q = e[lower + (start ? 1u : 0u) - 1u];
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     before += (uint32_t)__popcll(m);
     const uint32_t rr = base + (uint32_t)lane;
     if (rr < total) {
