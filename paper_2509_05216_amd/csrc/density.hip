@@ -15,9 +15,9 @@
 //         children, and splits, from wave ballots;
 //  scan   one block turns the block totals into exclusive block offsets and
 //         the grand totals (read back by the host to size the output);
-//  apply  classify again, rank each Gaussian inside its block in index order
-//         (ballot prefix counts), list the block's outputs in LDS and write them
-//         row by row: originals and clones copy their 11 + 3(d+1)^2 parameter
+//  apply  read the classes that the count left (classify again where there was no
+//         room for them), rank each Gaussian inside its block in index order (ballot
+//         prefix counts), list the block's outputs in LDS and write them row by row: originals and clones copy their 11 + 3(d+1)^2 parameter
 //         rows (and, for originals, both Adam moments); children get drawn means
 //         and reduced log-scales; the moments of new Gaussians are zero.
 #include <algorithm>

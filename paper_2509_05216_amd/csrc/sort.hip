@@ -552,7 +552,7 @@ __global__ __launch_bounds__(P::THREADS) void k_radix_scatter(
 // straight to their place.  Two instructions a pair and n^2 pairs, but up to one block per
 // CU less than the latency of four sorting passes, the gather and the scans (eleven
 // launches, these two): whole forward pass of 1000 Gaussians at 256^2 113 -> 65 us, 4000
-// 117 -> 77, 12000 127 -> 105, 16384 205 -> 181.  (All in one block with the keys in
+// 115 -> 77, 12000 125 -> 106, 16384 205 to 220 -> 181.  (All in one block with the keys in
 // registers: 73, 81, 130, 192; keys from LDS, or a ballot and a scalar bit count per 64
 // pairs: 21 and 22 us instead of 18 for the counting of 10k.)
 constexpr int kRankWaves = 16;
